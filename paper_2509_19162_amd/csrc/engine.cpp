@@ -122,9 +122,7 @@ Engine::Engine(hipStream_t user_stream) {
         own_stream_ = true;
     }
     w_.init(stream_);
-    for (DevBuf *b : {&gsel_, &cand0_, &cand1_, &lay_[0], &lay_[1], &lay_[2], &arena_, &stage_, &chunk_hist_, &vis_[0],
-                      &vis_[1], &rk_[0], &rk_[1], &rk_[2]})
-        b->stream = stream_;
+    for (DevBuf *b : buffers()) b->stream = stream_;
     prof_.stream = stream_;
     CG_HIP(hipHostMalloc((void **)&host_small_, kHostSmallBytes, hipHostMallocDefault));
 }
@@ -133,35 +131,32 @@ Engine::~Engine() {
     delete wg_;
     if (host_small_) (void)hipHostFree(host_small_);
     // buffers go back to the device cache while their stream still exists
-    for (DevBuf *b : {&gsel_, &cand0_, &cand1_, &lay_[0], &lay_[1], &lay_[2], &arena_, &stage_, &chunk_hist_,
-                      &vis_[0], &vis_[1], &rk_[0], &rk_[1], &rk_[2]})
-        b->release();
-    for (DevBuf *b : {&w_.hist, &w_.base, &w_.small, &w_.status, &w_.bounds, &w_.tile_cnt, &w_.tile_off,
-                      &w_.kill, &w_.tcnt, &w_.toff, &w_.bsum})
-        b->release();
+    for (DevBuf *b : buffers()) b->release();
+    for (DevBuf *b : w_.buffers()) b->release();
     if (own_stream_) {
         (void)hipStreamSynchronize(stream_);
         (void)hipStreamDestroy(stream_);
     }
 }
 
-uint64_t Engine::device_bytes() const {
+std::vector<DevBuf *> Engine::buffers() {
+    return {&gsel_,   &cand0_,       &cand1_,       &lay_[0], &lay_[1], &lay_[2],   &arena_,    &stage_, &chunk_hist_,
+            &vis_[0], &vis_[1],      &rk_[0],       &rk_[1],  &rk_[2],  &part_[0],  &part_[1],  &tab_[0], &tab_[1],
+            &tab_[2], &part_cnt_[0], &part_cnt_[1], &hctr_,   &ssz_,    &small_[0], &small_[1], &small_[2],
+            &order_[0], &order_[1]};
+}
+
+uint64_t Engine::device_bytes() {
     uint64_t b = 0;
-    for (const DevBuf *x : {&gsel_, &cand0_, &cand1_, &lay_[0], &lay_[1], &lay_[2], &arena_, &stage_, &chunk_hist_,
-                            &vis_[0], &vis_[1], &rk_[0], &rk_[1], &rk_[2]})
-        b += x->bytes;
-    for (const DevBuf *x : {&w_.hist, &w_.base, &w_.small, &w_.status, &w_.bounds, &w_.tile_cnt, &w_.tile_off,
-                            &w_.kill, &w_.tcnt, &w_.toff, &w_.bsum})
-        b += x->bytes;
+    for (const DevBuf *x : buffers()) b += x->bytes;
+    for (const DevBuf *x : w_.buffers()) b += x->bytes;
     if (wg_) b += wg_->device_bytes();
     return b;
 }
 
 void Engine::release_buffers() {
     if (wg_) wg_->release();
-    for (DevBuf *x : {&gsel_, &cand0_, &cand1_, &lay_[0], &lay_[1], &lay_[2], &arena_, &stage_, &chunk_hist_,
-                      &vis_[0], &vis_[1], &rk_[0], &rk_[1], &rk_[2]})
-        x->release();
+    for (DevBuf *x : buffers()) x->release();
     // the pipeline's small buffers stay (init sized them); the large ones go
     for (DevBuf *x : {&w_.status, &w_.bounds, &w_.tile_cnt, &w_.tile_off, &w_.kill, &w_.tcnt, &w_.toff, &w_.bsum})
         x->release();
@@ -374,22 +369,50 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
         wg_->run(one, t, t0);
         return;
     }
+    const int n = spec.n;
+    hipEvent_t ev0, ev1;
+    CG_HIP(hipEventCreate(&ev0));
+    CG_HIP(hipEventCreate(&ev1));
+    CG_HIP(hipEventRecord(ev0, stream_));
+
+    const bool binary = spec.binary;
+    binary_ = binary;
+    const uint64_t key0 = binary ? pack_bits_host(n, spec.start) : pack_host(n, spec.start);
+    Progress pg;
+    const bool hashed = hash_layers(spec);
+    const bool finished = hashed && run_hashed(spec, res, key0, pg);
+    if (!finished) run_sorted(spec, res, key0, pg, hashed);
+
+    CG_HIP(hipEventRecord(ev1, stream_));
+    CG_HIP(hipEventSynchronize(ev1));
+    if (!finished) (void)read_counter();  // surfaces an error flag raised by the last gather
+    float ms = 0;
+    CG_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+    (void)hipEventDestroy(ev0);
+    (void)hipEventDestroy(ev1);
+    prof_.collect();
+    fill_kstats(prof_, res);
+    res->device_ms = ms;
+    res->status = pg.status;
+    res->num_layers = pg.layers;
+    const double t1 = now_seconds();
+    res->t_submit = t0;
+    res->t_admit = t0;
+    res->t_done = t1;
+}
+
+// The layer loop by sorting, from layer 0 or (resume) from where the hash
+// buckets stopped.
+void Engine::run_sorted(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &pg, bool resume) {
     const int n = spec.n, k = spec.k;
     const bool keep_all = (spec.flags & CG_KEEP_ALL_LAYERS) != 0;
     // A set not closed under inverses can reach any earlier layer, so the
     // new layer is taken against every state seen so far: a sorted visited
     // array into which each new layer is merged.
     const bool directed = !spec.inverse_closed;
-
-    hipEvent_t ev0, ev1;
-    CG_HIP(hipEventCreate(&ev0));
-    CG_HIP(hipEventCreate(&ev1));
-    CG_HIP(hipEventRecord(ev0, stream_));
-
-    uint64_t written = 0;
     const bool binary = spec.binary;
-    binary_ = binary;
-    const uint64_t key0 = binary ? pack_bits_host(n, spec.start) : pack_host(n, spec.start);
+    uint64_t *sizes = res->layer_sizes;
+    uint64_t &written = pg.written;
     if (binary) {
         // per generator, the byte tables of its bit permutation
         const std::vector<uint64_t> t = make_bit_tables(n, spec.gens.data(), k);
@@ -434,9 +457,11 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
             : nullptr;
 
     // layer storage
-    std::vector<uint64_t> off;  // keep_all: offsets of the layers in the arena
-    uint64_t total = 1;         // states recorded so far
-    if (keep_all) {
+    std::vector<uint64_t> &off = pg.off;  // keep_all: offsets of the layers in the arena
+    uint64_t &total = pg.total;           // states recorded so far
+    if (resume) {
+        // layers d-1 and d are in place
+    } else if (keep_all) {
         // the whole orbit when it fits comfortably, else grow on demand
         size_t free_b = 0, total_b = 0;
         CG_HIP(hipMemGetInfo(&free_b, &total_b));
@@ -452,7 +477,7 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
         CG_HIP(hipMemcpyAsync(lay_[1].p, &key0, 8, hipMemcpyHostToDevice, stream_));
     }
     int ip = 0, ic = 1, in = 2;  // indices of L_{d-1}, L_d, L_{d+1} in lay_
-    uint64_t np = 0, F = 1;
+    uint64_t &np = pg.np, &F = pg.F;
     int iv = 0;          // directed: vis_[iv] holds every visited state, sorted
     uint64_t nvis = 0;
     if (directed) {
@@ -460,7 +485,7 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
         CG_HIP(hipMemcpyAsync(vis_[0].p, &key0, 8, hipMemcpyHostToDevice, stream_));
         nvis = 1;
     }
-    export_layer(spec, keep_all ? arena_.as<uint64_t>() : lay_[1].as<uint64_t>(), 1, written);
+    if (!resume) export_layer(spec, keep_all ? arena_.as<uint64_t>() : lay_[1].as<uint64_t>(), 1, written);
 
     // binary keys use bits [0, n); 4-bit keys [4, 4n) (the last entry of a
     // state follows from the others)
@@ -494,7 +519,9 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
     // none; the next two steps then rank the packed layers on the fly.
     int kp = 0, kc = 1, kn = 2;
     bool rk_cur = false, rk_prev = false;
-    if (ranked && !directed) {
+    if (resume) {
+        // no ranks beside the layers: the next two steps rank them on the fly
+    } else if (ranked && !directed) {
         const uint32_t r0 = perm_rank(key0, n);
         rk_[kc].ensure(64);
         CG_HIP(hipMemcpyAsync(rk_[kc].p, &r0, sizeof r0, hipMemcpyHostToDevice, stream_));
@@ -508,8 +535,8 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
     }
     int rank_bits = 0;
     while (rank_bits < 63 && (1ull << rank_bits) < spec.orbit_bound) ++rank_bits;
-    int layers = 1;
-    int status = CG_OK;
+    int &layers = pg.layers;
+    int &status = pg.status;
     for (;;) {
         if (k == 0) {
             status = CG_OK;
@@ -689,23 +716,6 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
         np = F;
         F = N;
     }
-
-    CG_HIP(hipEventRecord(ev1, stream_));
-    CG_HIP(hipEventSynchronize(ev1));
-    (void)read_counter();  // surfaces an error flag raised by the last gather
-    float ms = 0;
-    CG_HIP(hipEventElapsedTime(&ms, ev0, ev1));
-    (void)hipEventDestroy(ev0);
-    (void)hipEventDestroy(ev1);
-    prof_.collect();
-    fill_kstats(prof_, res);
-    res->device_ms = ms;
-    res->status = status;
-    res->num_layers = layers;
-    const double t1 = now_seconds();
-    res->t_submit = t0;
-    res->t_admit = t0;
-    res->t_done = t1;
 }
 
 }  // namespace cg

@@ -4,6 +4,7 @@
 #include <vector>
 
 #include "../../include/cayleygrowth.h"
+#include "buckets.h"
 #include "internal.h"
 
 namespace cg {
@@ -27,6 +28,11 @@ struct JobSpec {
 // Validates and canonicalises a job; throws Error(CG_E_INVAL / _UNSUPPORTED).
 JobSpec canonicalize(const cg_job_t &job, bool batch);
 
+// Whether a job's layers go by hash buckets (Engine::run_hashed).
+bool hash_layers(const JobSpec &spec);
+// Upper bound of the device bytes such a job makes an engine hold.
+uint64_t hash_layers_bytes(const JobSpec &spec);
+
 double now_seconds();
 
 // Sets the calling thread's cg_last_error() string.
@@ -49,10 +55,25 @@ public:
     uint64_t read_counter();
     // Device bytes the engine's buffers hold now (they are kept between
     // runs); release_buffers() frees them.
-    uint64_t device_bytes() const;
+    uint64_t device_bytes();
     void release_buffers();
 
 private:
+    // Where a growth stands between layers: L_{d-1} has np states, L_d F.
+    struct Progress {
+        uint64_t np = 0, F = 1, total = 1, written = 0;
+        int layers = 1, status = CG_OK;
+        std::vector<uint64_t> off;  // keep_all: offsets of the layers in arena_
+    };
+    // Layers by hash buckets (buckets.hip). True when the growth ended;
+    // false when the sort path has to go on from `p`: L_{d-1} and L_d are
+    // then sorted in lay_[0] and lay_[1] (keep_all: in arena_).
+    bool run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p);
+    void run_sorted(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p, bool resume);
+    void hand_to_sort(const JobSpec &spec, const HashLayer &prev, const HashLayer &cur, const Progress &p);
+    uint64_t *sorted_copy(const JobSpec &spec, const uint64_t *keys, uint64_t n, DevBuf &a, DevBuf &b);
+    // every device buffer beside the pipeline's own (w_)
+    std::vector<DevBuf *> buffers();
     void export_layer(const JobSpec &spec, const uint64_t *d_keys, uint64_t count,
                       uint64_t &written);
     uint64_t forced_chunk(uint64_t C);
@@ -68,9 +89,13 @@ private:
     Profiler prof_;
     DevBuf gsel_, cand0_, cand1_, lay_[3], arena_, stage_, chunk_hist_, vis_[2];
     DevBuf rk_[3];  // ranked runs: 32-bit ranks of layers d-1, d, d+1
+    // hash buckets: both partitions and their counts, the layers' bucket
+    // tables, runs of small layers, counters and small-layer sizes, sort
+    // space of layers that are read back
+    DevBuf part_[2], part_cnt_[2], tab_[3], small_[3], hctr_, ssz_, order_[2];
     class WgRunner *wg_ = nullptr;  // small-job engine (created on first use)
-    static constexpr size_t kHostSmallBytes = 512;
-    uint64_t *host_small_ = nullptr;  // pinned: error flag .. counter
+    static constexpr size_t kHostSmallBytes = 16384;
+    uint64_t *host_small_ = nullptr;  // pinned: counters read back, inputs uploaded
 };
 
 void fill_kstats(const Profiler &p, cg_result_t *res);

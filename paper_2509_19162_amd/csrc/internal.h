@@ -55,7 +55,10 @@ enum KernelKind {
     K_SORT = 4,       // later sort passes
     K_DEDUP = 5,      // unique + set difference + compaction
     K_AUX = 6,        // small bookkeeping kernels
-    K_NUM = 7
+    K_SPLIT = 7,      // hash buckets: second partition
+    K_BUCKET = 8,     // hash buckets: unique + set difference in LDS tables
+    K_SMALL = 9,      // small layers in one workgroup
+    K_NUM = 10
 };
 const char *kernel_kind_name(int k);
 
@@ -104,6 +107,7 @@ struct DevBuf {
         return ensure(need, slack);
     }
     void release();
+    bool holds(const void *x) const { return p && x >= p && x < (const char *)p + bytes; }
     // Exchanges the memory of two buffers (with where it came from; the
     // streams stay with their owners).
     void swap(DevBuf &o) {
@@ -153,6 +157,9 @@ struct PipeWork {
     uint32_t *tickets() const { return small.as<uint32_t>(); }          // 32
     uint32_t *err() const { return small.as<uint32_t>() + 32; }        // 1
     uint64_t *counter() const { return small.as<uint64_t>() + 32; }    // 8 x u64
+    std::vector<DevBuf *> buffers() {
+        return {&hist, &base, &small, &status, &bounds, &tile_cnt, &tile_off, &kill, &tcnt, &toff, &bsum};
+    }
     void init(hipStream_t s);
     // Make room for `words` look-back words (new memory is cleared).
     void ensure_status(uint64_t words);

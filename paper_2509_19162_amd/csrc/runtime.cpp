@@ -283,8 +283,7 @@ void DevBuf::release() {
 
 void PipeWork::init(hipStream_t s) {
     stream = s;
-    for (DevBuf *b : {&hist, &base, &small, &status, &bounds, &tile_cnt, &tile_off, &kill, &tcnt, &toff, &bsum})
-        b->stream = s;
+    for (DevBuf *b : buffers()) b->stream = s;
     hist.ensure(kMaxPasses * 256 * sizeof(uint64_t));
     base.ensure(kMaxPasses * 256 * sizeof(uint64_t));
     small.ensure(32 * sizeof(uint32_t) + 4 * sizeof(uint32_t) + 8 * sizeof(uint64_t) + 256);
@@ -309,7 +308,8 @@ uint32_t PipeWork::next_epoch() {
 
 const char *kernel_kind_name(int k) {
     static const char *names[K_NUM] = {"expand",      "digit_hist", "digit_scan", "sort_pass_expand",
-                                       "sort_pass",   "dedup_compact", "aux"};
+                                       "sort_pass",   "dedup_compact", "aux",
+                                       "bucket_split", "bucket_dedup", "small_layers"};
     return (k >= 0 && k < K_NUM) ? names[k] : "?";
 }
 
