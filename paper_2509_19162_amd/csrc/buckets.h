@@ -24,6 +24,7 @@ constexpr uint32_t kHashFlagTable = 2;       // a bucket's table overran
 // one-workgroup layers: states of three layers together, candidates of one
 constexpr uint32_t kSmallStates = 9216;
 constexpr uint32_t kSmallMaxCand = 16384;
+constexpr uint32_t kSmallSortStates = 16384; // longest run that launch_hash_sort_small takes
 constexpr uint32_t kSmallMaxLayers = 1024;   // layers of one launch
 // why a launch ended: buffers full or the next layer beyond the limits; the
 // growth's end; a stop rule; the next layer's states did not fit the table
@@ -101,7 +102,7 @@ struct HashSmallArgs {
     uint32_t *state;           // [0] layers added (an empty one included), [1] kSmall*
 };
 void launch_hash_small(const HashSmallArgs &a, const HashGens &g, PipeWork &w);
-// Sorts `layers` consecutive runs of keys (at most kSmallStates each) in
+// Sorts `layers` consecutive runs of keys (at most kSmallSortStates each) in
 // place; the runs' lengths are at sizes[0..layers).
 void launch_hash_sort_small(uint64_t *keys, const uint64_t *sizes, uint32_t layers, hipStream_t s);
 

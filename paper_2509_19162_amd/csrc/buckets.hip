@@ -12,7 +12,7 @@
 // raises a flag, and the host takes more buckets or hands the layer to the
 // sort path.
 //
-//   hash_expand_kernel  expand + first partition: candidates are formed in
+//   hash_expand_kernel  expand + first partition (partition_device.h): candidates are formed in
 //                       registers and go to up to 512 digits;
 //   hash_split_kernel   second partition (large layers): one workgroup per
 //                       first-level digit;
@@ -28,25 +28,19 @@
 #include "buckets.h"
 
 #include <algorithm>
-#include <cmath>
 #include <cstring>
 
 #include "device_util.h"
 #include "expand_device.h"
+#include "partition_device.h"
 
 namespace cg {
 
 namespace {
 
-constexpr int kPartBlock = 1024;           // threads of a partition workgroup (one per CU: LDS)
 constexpr int kPartRows = 4;               // candidates per thread and round
 constexpr uint32_t kPartTile = kPartBlock * kPartRows;
-constexpr uint32_t kLgBuf = 14;            // keys of the LDS write buffers in all: 128 KB
-constexpr uint32_t kMaxLines = 1u << (kLgBuf - 3);
-constexpr uint32_t kMaxDigits = 1u << kHashMaxLgDigits;
-// keys per line written to memory: 128 B, or 64 B with 1024 digits (whose
-// rings hold 16 keys)
-__device__ __forceinline__ uint32_t lg_line_of(uint32_t lg) { return lg > 9 ? 3u : 4u; }
+static_assert(kHashMaxLgDigits <= kPartMaxLgDigits, "digits of a partition");
 
 constexpr int kBucketBlock = 1024;         // threads of a bucket workgroup
 constexpr uint32_t kBucketWaves = kBucketBlock / kWave;
@@ -70,112 +64,6 @@ __device__ __forceinline__ uint32_t key_hash(uint64_t key) {
     const uint32_t rl = (uint32_t)r, rh = (uint32_t)(r >> 32);
     const uint64_t t = (uint64_t)(rl ^ rh ^ 0x27D4EB2Fu) * ((rh ^ 0x165667B1u) | 1u);
     return (uint32_t)t ^ (uint32_t)(t >> 32);
-}
-
-// ---- partition ----------------------------------------------------------------
-// Write-combining partition of one workgroup. Every digit owns a ring of
-// 2^lg_depth keys in LDS; whole lines (128 or 64 bytes) go to the digit's own
-// part of the output, so no line of memory is written twice or in pieces
-// and no position is shared with another workgroup. A round inserts up to
-// kPartTile keys; a key whose ring is full waits for the round's flush and
-// tries again.
-struct PartLds {
-    uint64_t buf[1u << kLgBuf];
-    uint32_t tail[kMaxDigits];   // keys taken in so far (may overshoot within a round)
-    uint32_t head[kMaxDigits];   // keys written out so far, this round's lines included
-    // the lines to write this round: first key in buf, position in the
-    // digit's part (past its end: dropped), digit
-    uint16_t line[kMaxLines];
-    uint16_t dig[kMaxLines];
-    uint32_t at[kMaxLines];
-    uint32_t lines[2];           // how many (by round parity)
-    uint32_t more[2];            // some key of the block waits (by round parity)
-};
-
-struct PartOut {
-    uint64_t *base;     // digit d's part: base + d * stride, cap keys
-    uint64_t stride;
-    uint32_t cap;
-    uint32_t *count;    // count[d * count_stride] = keys of digit d
-    uint32_t count_stride;
-    uint32_t *flags;
-};
-
-__device__ __forceinline__ void part_begin(PartLds &L, uint32_t digits) {
-    for (uint32_t i = threadIdx.x; i < digits; i += kPartBlock) L.tail[i] = L.head[i] = 0;
-    if (threadIdx.x < 2) L.more[threadIdx.x] = L.lines[threadIdx.x] = 0;
-    __syncthreads();
-}
-
-// One round: key[r] for the set bits r of `pend`. digit = (hash << skip) >>
-// (32 - lg). Every thread of the block calls it the same number of times.
-__device__ __forceinline__ void part_round(PartLds &L, const uint64_t (&key)[kPartRows], uint32_t pend,
-                                           uint32_t skip, uint32_t lg, const PartOut &o, uint32_t &parity) {
-    const uint32_t lg_depth = kLgBuf - lg, depth = 1u << lg_depth, lg_line = lg_line_of(lg);
-    const uint32_t tid = threadIdx.x, sub = tid & ((1u << lg_line) - 1), grp = tid >> lg_line;
-    uint32_t dig[kPartRows];
-#pragma unroll
-    for (int r = 0; r < kPartRows; ++r) dig[r] = (key_hash(key[r]) << skip) >> (32 - lg);
-    for (;;) {
-#pragma unroll
-        for (int r = 0; r < kPartRows; ++r) {
-            if ((pend >> r) & 1u) {
-                const uint32_t d = dig[r];
-                const uint32_t slot = atomicAdd(&L.tail[d], 1u);
-                if (slot - L.head[d] < depth) {
-                    L.buf[(d << lg_depth) + (slot & (depth - 1))] = key[r];
-                    pend &= ~(1u << r);
-                }
-            }
-        }
-        if (pend) L.more[parity] = 1;
-        __syncthreads();
-        for (uint32_t d = tid; d < (1u << lg); d += kPartBlock) {
-            const uint32_t head = L.head[d];
-            uint32_t have = L.tail[d] - head;
-            if (have > depth) {  // the overshoot of the keys that wait
-                have = depth;
-                L.tail[d] = head + depth;
-            }
-            const uint32_t n = have >> lg_line;
-            if (n) {
-                const uint32_t first = atomicAdd(&L.lines[parity], n);
-                for (uint32_t l = 0; l < n; ++l) {
-                    const uint32_t at = head + (l << lg_line);
-                    L.line[first + l] = (uint16_t)((d << lg_depth) + (at & (depth - 1)));
-                    L.at[first + l] = at;
-                    L.dig[first + l] = (uint16_t)d;
-                }
-                L.head[d] = head + (n << lg_line);
-            }
-        }
-        if (tid == 0) L.more[parity ^ 1u] = L.lines[parity ^ 1u] = 0;
-        __syncthreads();
-        const uint32_t nl = L.lines[parity];
-        for (uint32_t i = grp; i < nl; i += kPartBlock >> lg_line) {
-            const uint32_t at = L.at[i];
-            if (at < o.cap) o.base[(uint64_t)L.dig[i] * o.stride + at + sub] = L.buf[L.line[i] + sub];
-        }
-        const bool more = L.more[parity] != 0;
-        parity ^= 1u;
-        __syncthreads();
-        if (!more) break;
-    }
-}
-
-// The keys still in the rings, then the counts.
-__device__ __forceinline__ void part_end(PartLds &L, uint32_t lg, const PartOut &o) {
-    const uint32_t lg_depth = kLgBuf - lg, depth = 1u << lg_depth;
-    const uint32_t lg_line = lg_line_of(lg), sub = threadIdx.x & ((1u << lg_line) - 1), grp = threadIdx.x >> lg_line;
-    for (uint32_t d = grp; d < (1u << lg); d += kPartBlock >> lg_line) {
-        const uint32_t at = L.head[d] + sub, t = L.tail[d];
-        if (at < t && at < o.cap)
-            o.base[(uint64_t)d * o.stride + at] = L.buf[(d << lg_depth) + (at & (depth - 1))];
-        if (sub == 0) {
-            o.count[(uint64_t)d * o.count_stride] = t < o.cap ? t : o.cap;
-            if (t > o.cap) atomicOr(o.flags, kHashFlagPart);
-        }
-    }
 }
 
 // ---- generators -----------------------------------------------------------------
@@ -232,8 +120,8 @@ struct BitGens {
 template <class G>
 __global__ __launch_bounds__(kPartBlock) void hash_expand_kernel(const uint64_t *__restrict__ frontier, uint64_t F,
                                                                  G gens, uint32_t k, uint32_t tiles, uint32_t ranges,
-                                                                 uint32_t lg, PartOut o, uint64_t *next) {
-    __shared__ PartLds L;
+                                                                 uint32_t lg, PartOut<uint64_t> o, uint64_t *next) {
+    __shared__ PartLds<uint64_t> L;
     const uint32_t tid = threadIdx.x;
     // the next step's counters, not this one's: a plain store would reach
     // memory after other workgroups' atomics on the same line
@@ -261,7 +149,10 @@ __global__ __launch_bounds__(kPartBlock) void hash_expand_kernel(const uint64_t 
                 c[j] = gens.apply(s[j], g);
                 if (c[j] == s[j]) pend &= ~(1u << j);
             }
-            part_round(L, c, pend, 0, lg, o, parity);
+            uint32_t dig[kPartRows];
+#pragma unroll
+            for (int j = 0; j < kPartRows; ++j) dig[j] = key_hash(c[j]) >> (32 - lg);
+            part_round(L, c, dig, pend, lg, o, parity);
         }
     }
     part_end(L, lg, o);
@@ -273,8 +164,8 @@ __global__ __launch_bounds__(kPartBlock) void hash_expand_kernel(const uint64_t 
 __global__ __launch_bounds__(kPartBlock) void hash_split_kernel(const uint64_t *__restrict__ in,
                                                                 const uint32_t *__restrict__ in_count, uint32_t nsrc,
                                                                 uint32_t in_cap, uint32_t lg1, uint32_t lg2,
-                                                                PartOut o) {
-    __shared__ PartLds L;
+                                                                PartOut<uint64_t> o) {
+    __shared__ PartLds<uint64_t> L;
     constexpr uint32_t kWaves = kPartBlock / kWave;
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const uint32_t d = blockIdx.x;
@@ -307,7 +198,10 @@ __global__ __launch_bounds__(kPartBlock) void hash_split_kernel(const uint64_t *
             for (int j = 0; j < kPartRows; ++j) key[j] = 0;
         }
         if (!__syncthreads_or(any)) break;
-        part_round(L, key, pend, lg1, lg2, o, parity);
+        uint32_t dig[kPartRows];
+#pragma unroll
+        for (int j = 0; j < kPartRows; ++j) dig[j] = (key_hash(key[j]) << lg1) >> (32 - lg2);
+        part_round(L, key, dig, pend, lg2, o, parity);
     }
     part_end(L, lg2, o);
 }
@@ -688,15 +582,6 @@ uint32_t ceil_log2(uint64_t x) {
     return l;
 }
 
-// Keys a part has to hold when `mean` are expected: every state may come up
-// to k times, so the variance is up to k times that of a uniform draw; seven
-// deviations, and a few whole states' copies for parts that expect next to
-// nothing.
-uint32_t part_cap(double mean, uint32_t k) {
-    const double c = mean + 7.0 * std::sqrt((double)k * mean) + 4.0 * (double)k + 48.0;
-    return ((uint32_t)c + 16) / 16 * 16;
-}
-
 }  // namespace
 
 void launch_hash_sort_small(uint64_t *keys, const uint64_t *sizes, uint32_t layers, hipStream_t s) {
@@ -767,7 +652,8 @@ void with_gens(const HashGens &g, Fn &&fn) {
 void launch_hash_partition(const HashPlan &p, const HashGens &g, const HashLayer &cur, const HashBufs &b,
                            PipeWork &w) {
     if (w.prof) w.prof->begin(K_EXPAND);
-    PartOut o{b.part1, (uint64_t)p.blocks * p.cap1, p.cap1, b.count1, p.blocks, (uint32_t *)&b.counters[kHashFlags]};
+    PartOut<uint64_t> o{b.part1, (uint64_t)p.blocks * p.cap1, p.cap1, b.count1, p.blocks,
+                        (uint32_t *)&b.counters[kHashFlags], kHashFlagPart};
     with_gens(g, [&](auto gens) {
         hipLaunchKernelGGL((hash_expand_kernel<decltype(gens)>), dim3(p.blocks), dim3(kPartBlock), 0, w.stream,
                            cur.keys, cur.n, gens, g.k, p.tiles, p.ranges, p.lg1, o, b.next);
@@ -776,7 +662,7 @@ void launch_hash_partition(const HashPlan &p, const HashGens &g, const HashLayer
     if (w.prof) w.prof->end(K_EXPAND, 8.0 * (double)cur.n + 8.0 * (double)p.C, (double)p.C);
     if (p.lg2) {
         if (w.prof) w.prof->begin(K_SPLIT);
-        PartOut o2{b.part2, p.cap2, p.cap2, b.count2, 1, (uint32_t *)&b.counters[kHashFlags]};
+        PartOut<uint64_t> o2{b.part2, p.cap2, p.cap2, b.count2, 1, (uint32_t *)&b.counters[kHashFlags], kHashFlagPart};
         hipLaunchKernelGGL(hash_split_kernel, dim3(1u << p.lg1), dim3(kPartBlock), 0, w.stream, b.part1, b.count1,
                            p.blocks, p.cap1, p.lg1, p.lg2, o2);
         CG_HIP(hipGetLastError());

@@ -379,9 +379,12 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
     binary_ = binary;
     const uint64_t key0 = binary ? pack_bits_host(n, spec.start) : pack_host(n, spec.start);
     Progress pg;
-    const bool hashed = hash_layers(spec);
-    const bool finished = hashed && run_hashed(spec, res, key0, pg);
-    if (!finished) run_sorted(spec, res, key0, pg, hashed);
+    bool finished = rank_layers(spec) && run_ranked(spec, res, key0, pg);
+    if (!finished) {
+        const bool hashed = hash_layers(spec);
+        finished = hashed && run_hashed(spec, res, key0, pg);
+        if (!finished) run_sorted(spec, res, key0, pg, hashed);
+    }
 
     CG_HIP(hipEventRecord(ev1, stream_));
     CG_HIP(hipEventSynchronize(ev1));

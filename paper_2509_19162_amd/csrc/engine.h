@@ -30,7 +30,9 @@ JobSpec canonicalize(const cg_job_t &job, bool batch);
 
 // Whether a job's layers go by hash buckets (Engine::run_hashed).
 bool hash_layers(const JobSpec &spec);
-// Upper bound of the device bytes such a job makes an engine hold.
+// Whether they go over a rank bitmap (Engine::run_ranked, tried first).
+bool rank_layers(const JobSpec &spec);
+// Upper bound of the device bytes a job by hash buckets makes an engine hold.
 uint64_t hash_layers_bytes(const JobSpec &spec);
 
 double now_seconds();
@@ -49,6 +51,12 @@ public:
     // spec.max_layers entries). Throws Error on failure.
     void run(const JobSpec &spec, cg_result_t *res);
 
+    // Where a growth stands between layers: L_{d-1} has np states, L_d F.
+    struct Progress {
+        uint64_t np = 0, F = 1, total = 1, written = 0;
+        int layers = 1, status = CG_OK;
+        std::vector<uint64_t> off;  // keep_all: offsets of the layers in arena_
+    };
     PipeWork &work() { return w_; }
     hipStream_t stream() const { return stream_; }
     // Reads back one u64 counter and the kernel error flag (synchronises).
@@ -59,16 +67,16 @@ public:
     void release_buffers();
 
 private:
-    // Where a growth stands between layers: L_{d-1} has np states, L_d F.
-    struct Progress {
-        uint64_t np = 0, F = 1, total = 1, written = 0;
-        int layers = 1, status = CG_OK;
-        std::vector<uint64_t> off;  // keep_all: offsets of the layers in arena_
-    };
     // Layers by hash buckets (buckets.hip). True when the growth ended;
     // false when the sort path has to go on from `p`: L_{d-1} and L_d are
     // then sorted in lay_[0] and lay_[1] (keep_all: in arena_).
     bool run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p);
+    // Layers over a rank bitmap (rankbits.hip): permutations of up to 12
+    // entries. False when device memory is too short: `p` is then as at the
+    // start.
+    bool run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p);
+    bool take_layer(const JobSpec &spec, cg_result_t *res, uint64_t N, Progress &p);
+    void export_ranked(const JobSpec &spec, const uint64_t *sizes, int layers);
     void run_sorted(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p, bool resume);
     void hand_to_sort(const JobSpec &spec, const HashLayer &prev, const HashLayer &cur, const Progress &p);
     uint64_t *sorted_copy(const JobSpec &spec, const uint64_t *keys, uint64_t n, DevBuf &a, DevBuf &b);

@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 
+#include "bitmap.h"
 #include "engine.h"
 
 namespace cg {
@@ -36,19 +37,15 @@ constexpr double kExpectSlack = 1.15;
 
 // Sets closed under inverses (two reference layers are enough), unless the
 // caller asks for packed sorting or an environment tunable of the sort path
-// is set. Permutations of 12 entries stay with the sort of 32-bit ranks: S_12
-// pancake took 76 ms there and 97 ms by buckets of 64-bit keys; S_10 with
-// six random generators 1.7 ms against 1.1, S_16 LRX to 2^29 states 185
-// against 90, binary LRX cosets of n = 32 80 against 43.
+// is set. Permutations of up to 12 entries go over a rank bitmap instead, or
+// by sorting where memory is too short for that (S_12 pancake: 97 ms by
+// buckets of 64-bit keys, 76 by sorting 32-bit ranks, 28 over the bitmap).
+// Against the sort: S_16 LRX to 2^29 states 90 ms for 184, a multiset coset of
+// n = 14 9.1 for 28.6, binary LRX cosets of n = 32 44 for 82.
 bool hash_layers(const JobSpec &spec) {
     if (spec.k == 0 || !spec.inverse_closed || (spec.flags & (CG_PACKED_SORT | CG_BITMASK | CG_SMALL_JOB))) return false;
     if (std::getenv("CG_CHUNK_CANDIDATES") || std::getenv("CG_RANK_FULL")) return false;
-    if (spec.n == 12 && !spec.binary) {
-        uint32_t seen = 0;
-        for (int i = 0; i < 12; ++i) seen |= 1u << spec.start[i];
-        if (seen == 0xFFFu) return false;
-    }
-    return true;
+    return spec.binary || spec.n > 12 || !start_is_permutation(spec);
 }
 
 // Partitions and their counts at every frontier size up to the largest (the

@@ -58,7 +58,8 @@ enum KernelKind {
     K_SPLIT = 7,      // hash buckets: second partition
     K_BUCKET = 8,     // hash buckets: unique + set difference in LDS tables
     K_SMALL = 9,      // small layers in one workgroup
-    K_NUM = 10
+    K_STEP = 10,      // rank bitmap: expand + test + append
+    K_NUM = 11
 };
 const char *kernel_kind_name(int k);
 

@@ -1,0 +1,143 @@
+// Write-combining partition of one workgroup's keys, for gfx950.
+//
+// Every digit owns a ring of keys in LDS; whole lines (128 bytes, or 64 with
+// 1024 digits of 8-byte keys) go to the digit's own part of the output, so
+// no line of memory is written twice or in pieces, no position is shared
+// with another workgroup and no order is kept. A round takes R keys per
+// thread; a key whose ring is full waits for the round's flush and tries
+// again.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "device_util.h"
+
+namespace cg {
+
+constexpr int kPartBlock = 1024;             // threads of a partition workgroup (one per CU: LDS)
+constexpr uint32_t kPartBytes = 128u << 10;  // rings
+constexpr uint32_t kPartMaxLgDigits = 10;
+
+template <class K>
+struct PartLds {
+    static constexpr uint32_t kLgBuf = sizeof(K) == 4 ? 15 : 14;  // keys of all rings
+    static constexpr uint32_t kMaxLines = sizeof(K) == 4 ? 1024 : 2048;
+    static constexpr uint32_t kMaxDigits = sizeof(K) == 4 ? 512 : 1024;
+    static_assert((sizeof(K) << kLgBuf) == kPartBytes, "rings");
+    // keys per line written to memory
+    static __device__ __forceinline__ uint32_t lg_line(uint32_t lg) {
+        return sizeof(K) == 4 ? 5u : (lg > 9 ? 3u : 4u);
+    }
+    K buf[1u << kLgBuf];
+    uint32_t tail[kMaxDigits];   // keys taken in so far (may overshoot within a round)
+    uint32_t head[kMaxDigits];   // keys written out so far, this round's lines included
+    // the lines to write this round: first key in buf, position in the
+    // digit's part (past its end: dropped), digit
+    uint16_t line[kMaxLines];
+    uint16_t dig[kMaxLines];
+    uint32_t at[kMaxLines];
+    uint32_t lines[2];           // how many (by round parity)
+    uint32_t more[2];            // some key of the block waits (by round parity)
+};
+
+template <class K>
+struct PartOut {
+    K *base;            // digit d's part: base + d * stride, cap keys (a multiple of 32)
+    uint64_t stride;
+    uint32_t cap;
+    uint32_t *count;    // count[d * count_stride] = keys of digit d
+    uint32_t count_stride;
+    uint32_t *flags;    // gets `flag` when a part overran
+    uint32_t flag;
+};
+
+template <class K>
+__device__ __forceinline__ void part_begin(PartLds<K> &L, uint32_t digits) {
+    for (uint32_t i = threadIdx.x; i < digits; i += kPartBlock) L.tail[i] = L.head[i] = 0;
+    if (threadIdx.x < 2) L.more[threadIdx.x] = L.lines[threadIdx.x] = 0;
+    __syncthreads();
+}
+
+// One round: key[r] of digit dig[r] (below 2^lg) for the set bits r of
+// `pend`. Every thread of the block calls it the same number of times.
+template <class K, int R>
+__device__ __forceinline__ void part_round(PartLds<K> &L, const K (&key)[R], const uint32_t (&dig)[R], uint32_t pend,
+                                           uint32_t lg, const PartOut<K> &o, uint32_t &parity) {
+    const uint32_t lg_depth = PartLds<K>::kLgBuf - lg, depth = 1u << lg_depth, lg_line = PartLds<K>::lg_line(lg);
+    const uint32_t tid = threadIdx.x, sub = tid & ((1u << lg_line) - 1), grp = tid >> lg_line;
+    for (;;) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if ((pend >> r) & 1u) {
+                const uint32_t d = dig[r];
+                const uint32_t slot = atomicAdd(&L.tail[d], 1u);
+                if (slot - L.head[d] < depth) {
+                    L.buf[(d << lg_depth) + (slot & (depth - 1))] = key[r];
+                    pend &= ~(1u << r);
+                }
+            }
+        }
+        if (pend) L.more[parity] = 1;
+        __syncthreads();
+        for (uint32_t d = tid; d < (1u << lg); d += kPartBlock) {
+            const uint32_t head = L.head[d];
+            uint32_t have = L.tail[d] - head;
+            if (have > depth) {  // the overshoot of the keys that wait
+                have = depth;
+                L.tail[d] = head + depth;
+            }
+            const uint32_t n = have >> lg_line;
+            if (n) {
+                const uint32_t first = atomicAdd(&L.lines[parity], n);
+                for (uint32_t l = 0; l < n; ++l) {
+                    const uint32_t at = head + (l << lg_line);
+                    L.line[first + l] = (uint16_t)((d << lg_depth) + (at & (depth - 1)));
+                    L.at[first + l] = at;
+                    L.dig[first + l] = (uint16_t)d;
+                }
+                L.head[d] = head + (n << lg_line);
+            }
+        }
+        if (tid == 0) L.more[parity ^ 1u] = L.lines[parity ^ 1u] = 0;
+        __syncthreads();
+        const uint32_t nl = L.lines[parity];
+        for (uint32_t i = grp; i < nl; i += kPartBlock >> lg_line) {
+            const uint32_t at = L.at[i];
+            if (at < o.cap) o.base[(uint64_t)L.dig[i] * o.stride + at + sub] = L.buf[L.line[i] + sub];
+        }
+        const bool more = L.more[parity] != 0;
+        parity ^= 1u;
+        __syncthreads();
+        if (!more) break;
+    }
+}
+
+// The keys still in the rings, then the counts.
+template <class K>
+__device__ __forceinline__ void part_end(PartLds<K> &L, uint32_t lg, const PartOut<K> &o) {
+    const uint32_t lg_depth = PartLds<K>::kLgBuf - lg, depth = 1u << lg_depth;
+    const uint32_t lg_line = PartLds<K>::lg_line(lg);
+    const uint32_t sub = threadIdx.x & ((1u << lg_line) - 1), grp = threadIdx.x >> lg_line;
+    for (uint32_t d = grp; d < (1u << lg); d += kPartBlock >> lg_line) {
+        const uint32_t at = L.head[d] + sub, t = L.tail[d];
+        if (at < t && at < o.cap)
+            o.base[(uint64_t)d * o.stride + at] = L.buf[(d << lg_depth) + (at & (depth - 1))];
+        if (sub == 0) {
+            o.count[(uint64_t)d * o.count_stride] = t < o.cap ? t : o.cap;
+            if (t > o.cap) atomicOr(o.flags, o.flag);
+        }
+    }
+}
+
+// Keys a part has to hold when `mean` are expected: every state may come up
+// to k times, so the variance is up to k times that of a uniform draw; seven
+// deviations, and a few whole states' copies for parts that expect next to
+// nothing.
+inline uint32_t part_cap(double mean, uint32_t k) {
+    const double c = mean + 7.0 * __builtin_sqrt((double)k * mean) + 4.0 * (double)k + 48.0;
+    return ((uint32_t)c + 32) / 32 * 32;
+}
+
+}  // namespace cg

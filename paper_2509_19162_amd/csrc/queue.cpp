@@ -489,7 +489,7 @@ int cg_queue_submit(cg_queue_t *q, const cg_job_t *job, cg_result_t *res_slot, u
     if (r->big && r->spec.n >= 12 && !(r->spec.flags & CG_PACKED_SORT) && cg::bitmask_unsupported(r->spec).empty()) {
         r->spec.flags |= CG_BITMASK;
         r->bound = cg::job_bound(r->spec);
-    } else if (r->big && cg::hash_layers(r->spec)) {
+    } else if (r->big && !cg::rank_layers(r->spec) && cg::hash_layers(r->spec)) {
         // partitions and tables on top of what the sort path may still need
         r->bound = std::max(r->bound, cg::hash_layers_bytes(r->spec));
     }

@@ -309,7 +309,8 @@ uint32_t PipeWork::next_epoch() {
 const char *kernel_kind_name(int k) {
     static const char *names[K_NUM] = {"expand",      "digit_hist", "digit_scan", "sort_pass_expand",
                                        "sort_pass",   "dedup_compact", "aux",
-                                       "bucket_split", "bucket_dedup", "small_layers"};
+                                       "bucket_split", "bucket_dedup", "small_layers",
+                                       "bitmap_step"};
     return (k >= 0 && k < K_NUM) ? names[k] : "?";
 }
 
