@@ -495,7 +495,7 @@ double run_with(std::map<int, std::vector<Item>> &by_n, cg_result_t *results, co
         auto &all = kv.second;
         ClassChoice ch;
         ch.wg = n <= wg_max_n;
-        ch.block = n >= 10 ? 1024 : (n == 9 ? 512 : 256);  // the autotuner's usual picks on MI355X
+        ch.block = wg_block(n);
         ch.group_cap = group_cap_for(n);
         if (use_tuned) {
             auto f = c.tuned.find(n);

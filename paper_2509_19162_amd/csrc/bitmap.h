@@ -6,8 +6,8 @@
 // rank, test the visited bit, set the next-layer bit):
 //   * the small-job engine runs one whole job per workgroup inside one
 //     persistent launch; workgroups take jobs from a queue. Bitmaps live in
-//     LDS for n <= 8 and in a per-workgroup slot of device memory for
-//     n = 9, 10;
+//     LDS for n <= 9 and in a per-workgroup slot of device memory for
+//     n = 10;
 //   * the bitmask engine runs one large job over the whole device with
 //     three bitmaps (visited, current layer, next layer: 3 bits per state,
 //     the memory-saving encoding of the paper's section on growth
@@ -32,8 +32,12 @@ bool start_is_permutation(const JobSpec &spec);
 
 // Launch shape of the small-job engine.
 struct WgTuning {
-    int block = 256;  // threads per workgroup
+    int block = 1024;  // threads per workgroup
 };
+
+// Its default workgroup size for jobs of n entries: what a layer's states
+// keep busy (S_7 has 5040 in about 10 layers).
+inline int wg_block(int n) { return n >= 8 ? 1024 : (n == 7 ? 512 : 256); }
 
 struct WgItem {
     const JobSpec *spec;

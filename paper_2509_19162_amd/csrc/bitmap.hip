@@ -21,7 +21,7 @@
 // Device memory of cg_growth_batch_noalloc: every buffer its launch needs
 // beyond the caller's inputs and outputs (job table, generator table,
 // layer-size and outcome staging, the job-queue tickets, the per-workgroup
-// bitmap slots of n = 9, 10 jobs). Each GPU the library runs on holds its
+// bitmap slots of n = 10 jobs). Each GPU the library runs on holds its
 // own copy until the process ends. Host code never uses this name as an
 // address: it takes the device address once per device from
 // hipGetSymbolAddress (cg::noalloc_scratch).
@@ -50,12 +50,18 @@ uint64_t host_rank64(uint64_t key, int n) {
     return rank;
 }
 
-// Release this workgroup's writes to device memory, wait for all its
-// waves, then drop stale L1 lines: bitmap words change by L2 atomics.
+// Wait for all waves of the workgroup, then drop stale L1 lines: bitmap
+// words change by atomics in the L2. Only this workgroup touches them, so
+// nothing has to leave its own L2.
 __device__ __forceinline__ void wg_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+// OR into a word that only this workgroup uses: performed in LDS, or in the
+// nearest L2 (at device scope it would go to memory, 27 G/s for the chip).
+__device__ __forceinline__ void wg_or(uint32_t *p, uint32_t m) {
+    __hip_atomic_fetch_or(p, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
@@ -78,32 +84,133 @@ struct WgOutDev {
     uint64_t expanded;
 };
 
-constexpr uint32_t kWgLdsN = 8;
-constexpr uint32_t kWgLdsWords = (uint32_t)((factorial(kWgLdsN) + 31) / 32);  // 1260
+constexpr uint32_t kWgLdsN = 9;  // largest n whose bitmaps live in LDS
 constexpr int kWgMaxBlock = 1024;
+constexpr uint32_t kWgWaves = kWgMaxBlock / kWave;
+constexpr uint32_t kWgChunk = 16;  // bitmap words a wave lists at a time
+constexpr uint32_t wg_words(int n) { return (uint32_t)((factorial(n) + 31) / 32); }
+
+// ---- states of n <= 8 ------------------------------------------------------------
+// A state is eight bytes, entry i in byte i (of fewer than eight entries the
+// rest stay in place: S_n as a subgroup of S_8, ranks in S_8). A generator is
+// two byte permutes. The rank is that of the first four entries times 24 plus
+// the order among the last four: two table lookups, each at the 12-bit number
+// made of four 3-bit entries; the way back is two lookups and one byte
+// permute.
+struct Wg8Tables {
+    uint32_t from[2 * 1680];  // first four entries, the other four in order
+    uint32_t order[24];       // the 24 orders of four bytes, as selectors
+    uint16_t first[4096];     // rank of four entries in S_8, without the factor 24
+    uint8_t last[4096];       // order (0..23) among four entries
+};
+__device__ __forceinline__ uint32_t wg8_index(uint32_t x) {
+    return __builtin_amdgcn_udot4(x, 0x00400801u, (x >> 24) << 9, false);
+}
+__device__ __forceinline__ void wg8_build(Wg8Tables &t) {
+    for (uint32_t q = threadIdx.x; q < 1680u; q += blockDim.x) {
+        uint64_t left = 0x0706050403020100ull;
+        const uint32_t c[4] = {q / 210u, q / 30u % 7u, q / 5u % 6u, q % 5u};
+        uint32_t x = 0;
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t sh = 8u * c[i];
+            x |= (uint32_t)((left >> sh) & 255u) << (8 * i);
+            left = (left & ((1ull << sh) - 1ull)) | ((left >> 8) & ~((1ull << sh) - 1ull));
+        }
+        uint32_t o = 0;
+        for (int i = 0; i < 3; ++i) {
+            uint32_t less = 0;
+            for (int j = i + 1; j < 4; ++j) less += ((x >> (8 * j)) & 255u) < ((x >> (8 * i)) & 255u) ? 1u : 0u;
+            o = o * (uint32_t)(4 - i) + less;  // radices 4, 3, 2
+        }
+        t.from[2 * q] = x;
+        t.from[2 * q + 1] = (uint32_t)left;
+        t.first[wg8_index(x)] = (uint16_t)q;
+        t.last[wg8_index(x)] = (uint8_t)o;
+    }
+    for (uint32_t o = threadIdx.x; o < 24u; o += blockDim.x) {
+        uint32_t left = 0x03020100u, x = 0;
+        const uint32_t c[4] = {o / 6u, o / 2u % 3u, o % 2u, 0u};
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t sh = 8u * c[i], keep = (1u << sh) - 1u;
+            x |= ((left >> sh) & 255u) << (8 * i);
+            left = (left & keep) | ((left >> 8) & ~keep);
+        }
+        t.order[o] = x;
+    }
+}
+
+struct Wg8 {
+    const Wg8Tables &t;
+    const GenSel *sel;  // words 0 and 1: the byte selectors
+    struct State {
+        uint32_t lo, hi;
+    };
+    __device__ __forceinline__ State unrank(uint32_t r) const {
+        const uint32_t q = r / 24u, o = r - 24u * q;
+        return {t.from[2 * q], __builtin_amdgcn_perm(0u, t.from[2 * q + 1], t.order[o])};
+    }
+    __device__ __forceinline__ uint32_t neighbour(const State &s, uint32_t g) const {
+        const uint32_t lo = __builtin_amdgcn_perm(s.hi, s.lo, sel[g].sel[0]);
+        const uint32_t hi = __builtin_amdgcn_perm(s.hi, s.lo, sel[g].sel[1]);
+        return (uint32_t)t.first[wg8_index(lo)] * 24u + (uint32_t)t.last[wg8_index(hi)];
+    }
+};
 
 template <int N>
-__device__ __forceinline__ void wg_run(const WgJobDev &J, const GenSel *__restrict__ gtab, uint32_t *vis,
-                                       uint32_t *cur, uint32_t *nxt, uint64_t *__restrict__ sizes,
-                                       WgOutDev *__restrict__ out, GenSel *s_sel, uint32_t *s_acc) {
-    constexpr uint32_t W = (uint32_t)((factorial(N) + 31) / 32);
-    const uint32_t tid = threadIdx.x, nt = blockDim.x;
-    const int k = (int)J.k;
-    for (uint32_t i = tid; i < (uint32_t)k * 8u; i += nt) (&s_sel[0].sel[0])[i] = (&gtab[J.goff].sel[0])[i];
+struct WgN {
+    const GenSel *sel;
+    using State = Nibbles;
+    __device__ __forceinline__ State unrank(uint32_t r) const { return split_nibbles(perm_unrank_t<N>(r)); }
+    __device__ __forceinline__ uint32_t neighbour(const State &s, uint32_t g) const {
+        return perm_rank_t<N>(apply_gensel(s, sel[g]));
+    }
+};
+
+// One job. A layer's states are the set bits of `cur`; a wave lists the set
+// bits of 16 words at a time in LDS (`list`, its own 512 entries), so that
+// its lanes take one state each however the bits lie. Either every state of
+// the layer forms its neighbours, and those not seen are set in `nxt`; or,
+// when few states are left, every unseen state looks for a seen predecessor
+// (under the inverse generators, after the k generators in the codec's
+// table) and is set in `nxt` at the first (the wave owns its word: the bits
+// gather in `fresh`, 16 words of its own). `whole`: the bitmap holds no bits
+// of states outside S_n (then, and only then, unseen bits may be taken from
+// it). kGlobal: the bitmaps are in device memory.
+// Up to n = 9 the chain of a neighbour (two or three lookups, the test) times
+// the layers bounds it, so all lanes have to be busy: one growth of S_8 by
+// its Coxeter set is 94 us (29 layers; the call takes 160 us, and 440 when each
+// lane looped over a word's bits and computed ranks), 1024 growths of S_9 6.9 ms. At
+// n = 10 it is the reads and atomics at random addresses of 340 MB of slots:
+// 225 ms for 1365 growths, the same with one or two workgroups a CU.
+template <bool kGlobal, class C>
+__device__ __forceinline__ void wg_run(const WgJobDev &J, const C &codec, uint32_t W, uint64_t states, bool whole,
+                                       uint32_t *vis, uint32_t *cur, uint32_t *nxt, uint16_t *list, uint32_t *fresh,
+                                       uint64_t *__restrict__ sizes, WgOutDev *__restrict__ out, uint32_t *s_acc) {
+    const uint32_t tid = threadIdx.x, nt = blockDim.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const uint32_t waves = nt / kWave;
+    const uint32_t k = J.k;
+    auto barrier = [] {
+        if constexpr (kGlobal)
+            wg_barrier();
+        else
+            __syncthreads();
+    };
     for (uint32_t w = tid; w < W; w += nt) {
         vis[w] = 0u;
         cur[w] = 0u;
         nxt[w] = 0u;
     }
-    wg_barrier();
+    if (tid == 0) *s_acc = 0;
+    if (lane < kWgChunk) fresh[lane] = 0;
+    barrier();
     if (tid == 0) {
         const uint32_t r = J.start_rank;
         vis[r >> 5] = 1u << (r & 31u);
         cur[r >> 5] = 1u << (r & 31u);
         sizes[0] = 1;
     }
-    wg_barrier();
-    uint64_t F = 1, expanded = 0;
+    barrier();
+    uint64_t F = 1, before = 0, expanded = 0, seen = 1;
     uint32_t layers = 1;
     int status = CG_OK;
     for (;;) {
@@ -116,22 +223,64 @@ __device__ __forceinline__ void wg_run(const WgJobDev &J, const GenSel *__restri
             status = CG_TRUNCATED;
             break;
         }
-        // expand layer d: every set bit of cur, every generator
-        for (uint32_t w = tid; w < W; w += nt) {
-            uint32_t bits = cur[w];
-            while (bits) {
-                const uint32_t b = (uint32_t)__builtin_ctz(bits);
-                bits &= bits - 1u;
-                const Nibbles s = split_nibbles(perm_unrank_t<N>(w * 32u + b));
-                for (int g = 0; g < k; ++g) {
-                    const uint32_t q = perm_rank_t<N>(apply_gensel(s, s_sel[g]));
-                    const uint32_t m = 1u << (q & 31u);
-                    if (!(vis[q >> 5] & m)) atomicOr(&nxt[q >> 5], m);
+        const bool pull = whole && pull_is_less(states - seen, F, before, k);
+        for (uint32_t c = wave; c * kWgChunk < W; c += waves) {
+            const uint32_t w = c * kWgChunk + (lane >> 2);
+            uint32_t x = 0;
+            if (w < W) x = pull ? ~vis[w] : cur[w];
+            x = (x >> (8u * (lane & 3u))) & 255u;
+            uint32_t n = 0;
+#pragma unroll
+            for (uint32_t b = 0; b < 8; ++b) {
+                const bool on = (x >> b) & 1u;
+                const uint64_t m = __ballot(on);
+                if (on) list[n + mask_rank(m)] = (uint16_t)(lane << 3 | b);
+                n += (uint32_t)__popcll(m);
+            }
+            if (!n) continue;
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (uint32_t i = lane; i < n; i += kWave) {
+                const uint32_t r = c * (kWgChunk * 32u) + list[i];
+                const typename C::State s = codec.unrank(r);
+                if (!pull) {
+                    // bitmaps in memory: the words of four neighbours are
+                    // under way together
+                    constexpr uint32_t kAhead = kGlobal ? 4 : 1;
+                    for (uint32_t g0 = 0; g0 < k; g0 += kAhead) {
+                        uint32_t q[kAhead], v[kAhead];
+#pragma unroll
+                        for (uint32_t u = 0; u < kAhead; ++u) {
+                            q[u] = codec.neighbour(s, g0 + u < k ? g0 + u : k - 1);
+                            v[u] = vis[q[u] >> 5];
+                        }
+#pragma unroll
+                        for (uint32_t u = 0; u < kAhead; ++u) {
+                            const uint32_t m = 1u << (q[u] & 31u);
+                            if (!(v[u] & m)) wg_or(&nxt[q[u] >> 5], m);
+                        }
+                    }
+                } else {
+                    for (uint32_t g = k; g < 2 * k; ++g) {
+                        const uint32_t q = codec.neighbour(s, g);
+                        if ((vis[q >> 5] >> (q & 31u)) & 1u) {
+                            atomicOr(&fresh[list[i] >> 5], 1u << (r & 31u));
+                            break;
+                        }
+                    }
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (pull && lane < kWgChunk) {
+                const uint32_t x1 = fresh[lane];
+                if (x1) {
+                    nxt[c * kWgChunk + lane] = x1;
+                    fresh[lane] = 0;
                 }
             }
         }
-        if (tid == 0) *s_acc = 0;
-        wg_barrier();
+        barrier();
         // fold: visited |= next, count it, clear the expanded layer
         uint32_t cnt = 0;
         for (uint32_t w = tid; w < W; w += nt) {
@@ -143,8 +292,8 @@ __device__ __forceinline__ void wg_run(const WgJobDev &J, const GenSel *__restri
             cur[w] = 0u;
         }
         cnt = wave_sum(cnt);
-        if ((tid & (kWave - 1)) == 0 && cnt) atomicAdd(s_acc, cnt);
-        wg_barrier();
+        if (lane == 0 && cnt) atomicAdd(s_acc, cnt);
+        barrier();
         const uint32_t n1 = *s_acc;
         expanded += F;
         uint32_t *t = cur;
@@ -153,8 +302,11 @@ __device__ __forceinline__ void wg_run(const WgJobDev &J, const GenSel *__restri
         if (n1 == 0) break;
         if (tid == 0) sizes[layers] = n1;
         ++layers;
+        before = F;
         F = n1;
-        wg_barrier();  // every thread has read s_acc before it is reset
+        seen += n1;
+        barrier();  // every thread has read s_acc before it is reset
+        if (tid == 0) *s_acc = 0;
     }
     if (tid == 0) {
         out->status = status;
@@ -163,64 +315,75 @@ __device__ __forceinline__ void wg_run(const WgJobDev &J, const GenSel *__restri
     }
 }
 
-// One persistent launch for a whole batch: each workgroup takes the next
-// job from a queue (jobs are ordered by decreasing size) and runs it to
-// completion. Jobs with n >= 9 use the workgroup's slot of `gbits`
-// (3 * slot_words words, checked by the host to hold their bitmaps); only
-// workgroups below n_slot_blocks own a slot. Two queues: ticket[0] hands
-// out jobs [0, n_slot_jobs) to workgroups that own a slot, ticket[1] jobs
-// [n_slot_jobs, njobs) to every workgroup (the host puts a job with
-// n >= 9 there only when every workgroup owns a slot).
-__global__ __launch_bounds__(kWgMaxBlock) void wg_growth_kernel(const WgJobDev *__restrict__ jobs, uint32_t njobs,
-                                                                uint32_t n_slot_jobs, uint32_t n_slot_blocks,
-                                                                const GenSel *__restrict__ gtab,
-                                                                uint64_t *__restrict__ sizes,
-                                                                WgOutDev *__restrict__ outs, uint32_t *ticket,
-                                                                uint32_t *gbits, uint64_t slot_words) {
-    __shared__ uint32_t s_bits[3 * kWgLdsWords];
-    __shared__ GenSel s_sel[kBitmapMaxK];
+// The jobs of a launch, in order: n = 10 (bitmaps in device slots), n = 9
+// (bitmaps in LDS, one workgroup per CU), n <= 8 (LDS, two per CU).
+struct WgLaunch {
+    const WgJobDev *jobs;
+    uint32_t n10, n9, njobs;
+    uint32_t slot_blocks;  // workgroups that own a slot
+    const GenSel *gtab;
+    uint64_t *sizes;
+    WgOutDev *outs;
+    uint32_t *ticket;      // three queues
+    uint32_t *gbits;       // slots of 3 * slot_words words
+    uint64_t slot_words;
+};
+
+// A persistent launch: each workgroup takes the next job from a queue (jobs
+// are ordered by decreasing size within their range) and runs it to
+// completion. kNine: the jobs of n = 9, ticket[2]. Else ticket[0] hands the
+// jobs of n = 10 to the workgroups that own a slot, ticket[1] those of n <= 8
+// to every workgroup.
+template <bool kNine>
+__global__ __launch_bounds__(kWgMaxBlock) __attribute__((amdgpu_waves_per_eu(kNine ? 4 : 8))) void wg_growth_kernel(
+    WgLaunch a) {
+    struct Small {
+        uint32_t bits[3 * wg_words(8)];
+        Wg8Tables tables;
+    };
+    constexpr uint32_t kBytes = kNine ? 3 * 4 * wg_words(9) : (uint32_t)sizeof(Small);
+    __shared__ __align__(16) unsigned char s_area[kBytes];
+    __shared__ uint16_t s_list[kWgWaves][kWgChunk * 32];
+    __shared__ uint32_t s_fresh[kWgWaves][kWgChunk];
+    __shared__ GenSel s_sel[2 * kBitmapMaxK];
     __shared__ uint32_t s_acc, s_job;
-    const bool has_slot = gbits && blockIdx.x < n_slot_blocks;
-    uint32_t *slot = has_slot ? gbits + (uint64_t)blockIdx.x * 3ull * slot_words : nullptr;
-    for (uint32_t q = has_slot ? 0u : 1u; q < 2u; ++q) {
-    const uint32_t q_lo = q ? n_slot_jobs : 0u, q_hi = q ? njobs : n_slot_jobs;
-    for (;;) {
-        if (threadIdx.x == 0) s_job = atomicAdd(ticket + q, 1u);
-        __syncthreads();
-        const uint32_t t = s_job;
-        __syncthreads();
-        if (t >= q_hi - q_lo) break;
-        const uint32_t j = q_lo + t;
-        const WgJobDev J = jobs[j];
-        if (J.n > kWgLdsN && !slot) {
-            // a host bookkeeping error: report it instead of touching memory
-            if (threadIdx.x == 0) {
-                outs[j].status = CG_E_DEVICE;
-                outs[j].num_layers = 0;
-                outs[j].expanded = 0;
+    uint16_t *list = s_list[threadIdx.x / kWave];
+    uint32_t *fresh = s_fresh[threadIdx.x / kWave];
+    if constexpr (!kNine)
+        if (a.n10 + a.n9 < a.njobs) wg8_build(reinterpret_cast<Small *>(s_area)->tables);
+    const bool has_slot = !kNine && a.gbits && blockIdx.x < a.slot_blocks;
+    for (uint32_t q = kNine ? 2u : (has_slot ? 0u : 1u); q < (kNine ? 3u : 2u); ++q) {
+        const uint32_t lo = q == 0 ? 0u : (q == 2 ? a.n10 : a.n10 + a.n9);
+        const uint32_t hi = q == 0 ? a.n10 : (q == 2 ? a.n10 + a.n9 : a.njobs);
+        for (;;) {
+            if (threadIdx.x == 0) s_job = atomicAdd(a.ticket + q, 1u);
+            __syncthreads();
+            const uint32_t t = s_job;
+            __syncthreads();
+            if (t >= hi - lo) break;
+            const uint32_t j = lo + t;
+            const WgJobDev J = a.jobs[j];
+            for (uint32_t i = threadIdx.x; i < 2 * J.k * 8u; i += blockDim.x)
+                (&s_sel[0].sel[0])[i] = (&a.gtab[J.goff].sel[0])[i];
+            uint64_t *sz = a.sizes + J.sizes_off;
+            WgOutDev *out = a.outs + j;
+            if constexpr (kNine) {
+                constexpr uint32_t W = wg_words(9);
+                uint32_t *bits = reinterpret_cast<uint32_t *>(s_area);
+                wg_run<false>(J, WgN<9>{s_sel}, W, factorial(9), true, bits, bits + W, bits + 2 * W, list, fresh, sz, out,
+                              &s_acc);
+            } else if (q == 0) {
+                uint32_t *slot = a.gbits + (uint64_t)blockIdx.x * 3ull * a.slot_words;
+                wg_run<true>(J, WgN<10>{s_sel}, wg_words(10), factorial(10), true, slot, slot + a.slot_words,
+                             slot + 2 * a.slot_words, list, fresh, sz, out, &s_acc);
+            } else {
+                constexpr uint32_t W = wg_words(8);
+                Small &sm = *reinterpret_cast<Small *>(s_area);
+                wg_run<false>(J, Wg8{sm.tables, s_sel}, W, factorial(8), J.n == 8, sm.bits, sm.bits + W,
+                              sm.bits + 2 * W, list, fresh, sz, out, &s_acc);
             }
-            continue;
+            __syncthreads();
         }
-        uint64_t *sz = sizes + J.sizes_off;
-        uint32_t *l0 = s_bits, *l1 = s_bits + kWgLdsWords, *l2 = s_bits + 2 * kWgLdsWords;
-        switch (J.n) {
-            case 1: wg_run<1>(J, gtab, l0, l1, l2, sz, outs + j, s_sel, &s_acc); break;
-            case 2: wg_run<2>(J, gtab, l0, l1, l2, sz, outs + j, s_sel, &s_acc); break;
-            case 3: wg_run<3>(J, gtab, l0, l1, l2, sz, outs + j, s_sel, &s_acc); break;
-            case 4: wg_run<4>(J, gtab, l0, l1, l2, sz, outs + j, s_sel, &s_acc); break;
-            case 5: wg_run<5>(J, gtab, l0, l1, l2, sz, outs + j, s_sel, &s_acc); break;
-            case 6: wg_run<6>(J, gtab, l0, l1, l2, sz, outs + j, s_sel, &s_acc); break;
-            case 7: wg_run<7>(J, gtab, l0, l1, l2, sz, outs + j, s_sel, &s_acc); break;
-            case 8: wg_run<8>(J, gtab, l0, l1, l2, sz, outs + j, s_sel, &s_acc); break;
-            case 9:
-                wg_run<9>(J, gtab, slot, slot + slot_words, slot + 2 * slot_words, sz, outs + j, s_sel, &s_acc);
-                break;
-            default:
-                wg_run<10>(J, gtab, slot, slot + slot_words, slot + 2 * slot_words, sz, outs + j, s_sel, &s_acc);
-                break;
-        }
-        __syncthreads();
-    }
     }
 }
 
@@ -387,22 +550,41 @@ struct WgTables {
     std::vector<GenSel> gsel;
     uint64_t sizes_total = 0;     // layer-size entries of all jobs
     uint64_t slot_words = 0;      // words per bitmap of a device slot (0: no job needs one)
-    uint32_t n_slot_jobs = 0;     // slot_first: jobs [0, n_slot_jobs) have n >= 9
+    uint32_t n10 = 0, n9 = 0;     // jobs of n = 10 (first) and n = 9 (next)
     int n_max = 0;
 };
 
-// Largest jobs first (the queue then balances like longest-first); with
-// slot_first the jobs whose bitmaps need a device slot come before all
-// others. A job records at most min(max_layers, orbit) layer sizes: every
-// recorded layer holds at least one state of the orbit.
-WgTables wg_tables(const std::vector<WgItem> &items, bool slot_first) {
+// Selectors of generator g of a job, or of its inverse: up to n = 8 the two
+// byte selectors of the eight-byte states, else the nibble selectors.
+GenSel wg_gensel(const JobSpec &s, int g, bool inverse) {
+    const uint8_t *row = s.gens.data() + (size_t)g * s.n;
+    uint8_t r[16];
+    for (int i = 0; i < 16; ++i) r[i] = (uint8_t)i;
+    for (int i = 0; i < s.n; ++i) {
+        if (inverse)
+            r[row[i]] = (uint8_t)i;
+        else
+            r[i] = row[i];
+    }
+    if (s.n > 8) return make_gensel(s.n, r);
+    GenSel v{};
+    std::memcpy(&v.sel[0], r, 8);
+    return v;
+}
+
+// Jobs of n = 10 first, then n = 9, then the others; within these the largest
+// first (the queue then balances like longest-first). A job records at most
+// min(max_layers, orbit) layer sizes: every recorded layer holds at least
+// one state of the orbit.
+WgTables wg_tables(const std::vector<WgItem> &items) {
     const uint32_t nj = (uint32_t)items.size();
     WgTables T;
     T.order.resize(nj);
     for (uint32_t i = 0; i < nj; ++i) T.order[i] = i;
+    auto range = [](int n) { return n > (int)kWgLdsN ? 0 : (n == 9 ? 1 : 2); };
     std::stable_sort(T.order.begin(), T.order.end(), [&](uint32_t a, uint32_t b) {
         const JobSpec &x = *items[a].spec, &y = *items[b].spec;
-        if (slot_first && (x.n > (int)kWgLdsN) != (y.n > (int)kWgLdsN)) return x.n > (int)kWgLdsN;
+        if (range(x.n) != range(y.n)) return range(x.n) < range(y.n);
         const double cx = (double)factorial(x.n) * (x.k + 1), cy = (double)factorial(y.n) * (y.k + 1);
         return cx > cy;
     });
@@ -414,18 +596,23 @@ WgTables wg_tables(const std::vector<WgItem> &items, bool slot_first) {
         d.n = (uint32_t)s.n;
         d.k = (uint32_t)s.k;
         d.goff = (uint32_t)T.gsel.size();
+        // up to n = 8 the states are those of S_8 that fix the entries past n
+        const int m = std::max(s.n, 8);
         uint64_t key = 0;
-        for (int q = 0; q < s.n; ++q) key |= (uint64_t)s.start[q] << (4 * (s.n - 1 - q));
-        d.start_rank = (uint32_t)host_rank64(key, s.n);
+        for (int q = 0; q < m; ++q) key |= (uint64_t)(q < s.n ? s.start[q] : q) << (4 * (m - 1 - q));
+        d.start_rank = (uint32_t)host_rank64(key, m);
         d.max_layers = (uint32_t)s.max_layers;
         d.pad = 0;
         d.max_frontier = s.max_frontier;
         d.sizes_off = T.sizes_total;
         T.sizes_total += std::min<uint64_t>((uint64_t)s.max_layers, factorial(s.n));
-        for (int g = 0; g < s.k; ++g) T.gsel.push_back(make_gensel(s.n, s.gens.data() + (size_t)g * s.n));
+        // the generators, then their inverses
+        for (int g = 0; g < 2 * s.k; ++g) T.gsel.push_back(wg_gensel(s, g < s.k ? g : g - s.k, g >= s.k));
         if (s.n > (int)kWgLdsN) {
             T.slot_words = std::max<uint64_t>(T.slot_words, (factorial(s.n) + 31) / 32);
-            if (slot_first) T.n_slot_jobs = i + 1;
+            ++T.n10;
+        } else if (s.n == 9) {
+            ++T.n9;
         }
         T.n_max = std::max(T.n_max, s.n);
     }
@@ -458,20 +645,29 @@ void wg_results(std::vector<WgItem> &items, const WgTables &T, const uint64_t *h
 
 }  // namespace
 
-// Workgroups of a launch: every job its own, at most as many as are
-// resident at once.
-static uint32_t wg_grid(uint32_t n_jobs, int block) {
-    int occ = 0;
-    CG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, wg_growth_kernel, block, 0));
-    if (occ < 1) occ = 1;
-    return (uint32_t)std::min<uint64_t>(n_jobs, (uint64_t)device_cus() * (uint64_t)occ);
+// Workgroups of the two launches (n = 9; the others): every job its own, at
+// most as many as are resident at once.
+struct WgGrid {
+    uint32_t nine = 0, rest = 0;
+};
+static WgGrid wg_grid(const WgTables &T, int block) {
+    auto fit = [&](auto kernel, uint32_t jobs) {
+        int occ = 0;
+        CG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, block, 0));
+        return (uint32_t)std::min<uint64_t>(jobs, (uint64_t)device_cus() * (uint64_t)std::max(occ, 1));
+    };
+    WgGrid g;
+    if (T.n9) g.nine = fit(wg_growth_kernel<true>, T.n9);
+    const uint32_t others = (uint32_t)T.jobs.size() - T.n9;
+    if (others) g.rest = fit(wg_growth_kernel<false>, others);
+    return g;
 }
 
 uint64_t WgRunner::launch_bytes(const std::vector<WgItem> &items, const WgTuning &t) {
     if (items.empty()) return 0;
-    const WgTables T = wg_tables(items, true);
+    const WgTables T = wg_tables(items);
     const uint32_t nj = (uint32_t)items.size();
-    const uint64_t slots = T.slot_words ? std::min<uint64_t>(wg_grid(nj, t.block), T.n_slot_jobs) : 0;
+    const uint64_t slots = T.slot_words ? std::min<uint64_t>(wg_grid(T, t.block).rest, T.n10) : 0;
     // every buffer as DevBuf rounds it (64 KiB) with its growth slack
     auto r = [](uint64_t b) { return ((uint64_t)(1.5 * (double)b) + (64u << 10) - 1) / (64u << 10) * (64u << 10); };
     return r(sizeof(WgJobDev) * nj) + r(sizeof(GenSel) * T.gsel.size()) + r(sizeof(uint64_t) * T.sizes_total) +
@@ -497,11 +693,10 @@ double WgRunner::run(std::vector<WgItem> &items, const WgTuning &t, double t_sub
     if (t.block < 64 || t.block > kWgMaxBlock || t.block % kWave) throw Error(CG_E_INVAL, "bad workgroup size");
     // jobs that need a device slot first: only as many workgroups as there
     // are such jobs own one
-    const WgTables T = wg_tables(items, true);
+    const WgTables T = wg_tables(items);
     const uint64_t sizes_total = T.sizes_total, slot_words = T.slot_words;
-    const uint32_t grid = wg_grid(nj, t.block);
-    const uint32_t n_slot_jobs = T.n_slot_jobs;
-    const uint32_t n_slot_blocks = slot_words ? std::min(grid, n_slot_jobs) : 0u;
+    const WgGrid grid = wg_grid(T, t.block);
+    const uint32_t n_slot_blocks = slot_words ? std::min(grid.rest, T.n10) : 0u;
 
     jobs_.ensure(sizeof(WgJobDev) * nj, 1.25);
     gsel_.ensure(sizeof(GenSel) * T.gsel.size(), 1.25);
@@ -513,53 +708,58 @@ double WgRunner::run(std::vector<WgItem> &items, const WgTuning &t, double t_sub
     CG_HIP(hipMemcpyAsync(gsel_.p, T.gsel.data(), sizeof(GenSel) * T.gsel.size(), hipMemcpyHostToDevice, stream_));
 
     uint32_t *gbits = slot_words ? ws_.as<uint32_t>() : nullptr;
-    const std::vector<uint64_t> key = {(uint64_t)(uintptr_t)jobs_.p, nj, (uint64_t)(uintptr_t)gsel_.p,
-                                       (uint64_t)(uintptr_t)sizes_.p, (uint64_t)(uintptr_t)outs_.p,
-                                       (uint64_t)(uintptr_t)ticket_.p, (uint64_t)(uintptr_t)gbits, slot_words,
-                                       grid, (uint64_t)t.block};
+    WgLaunch args{jobs_.as<const WgJobDev>(), T.n10, T.n9, nj, n_slot_blocks, gsel_.as<const GenSel>(),
+                  sizes_.as<uint64_t>(), outs_.as<WgOutDev>(), ticket_.as<uint32_t>(), gbits, slot_words};
+    const std::vector<uint64_t> key = {(uint64_t)(uintptr_t)jobs_.p,   nj,
+                                       (uint64_t)(uintptr_t)gsel_.p,   (uint64_t)(uintptr_t)sizes_.p,
+                                       (uint64_t)(uintptr_t)outs_.p,   (uint64_t)(uintptr_t)ticket_.p,
+                                       (uint64_t)(uintptr_t)gbits,     slot_words,
+                                       T.n10,                          T.n9,
+                                       grid.nine,                      grid.rest,
+                                       (uint64_t)t.block};
     auto enqueue = [&]() {
-        hipLaunchKernelGGL(clear_u32_kernel, dim3(1), dim3(64), 0, stream_, ticket_.as<uint32_t>(), 2u);
-        hipLaunchKernelGGL(wg_growth_kernel, dim3(grid), dim3(t.block), 0, stream_, jobs_.as<const WgJobDev>(), nj,
-                           n_slot_jobs, n_slot_blocks, gsel_.as<const GenSel>(), sizes_.as<uint64_t>(),
-                           outs_.as<WgOutDev>(), ticket_.as<uint32_t>(), gbits, slot_words);
+        hipLaunchKernelGGL(clear_u32_kernel, dim3(1), dim3(64), 0, stream_, ticket_.as<uint32_t>(), 3u);
+        if (grid.nine)
+            hipLaunchKernelGGL(wg_growth_kernel<true>, dim3(grid.nine), dim3(t.block), 0, stream_, args);
+        if (grid.rest)
+            hipLaunchKernelGGL(wg_growth_kernel<false>, dim3(grid.rest), dim3(t.block), 0, stream_, args);
     };
     if (key != graph_key_) {
         // the graph is built node by node (no stream capture): a queue
-        // reset followed by the persistent kernel
+        // reset, then the persistent kernels side by side
         if (exec_) (void)hipGraphExecDestroy(exec_);
         if (graph_) (void)hipGraphDestroy(graph_);
         exec_ = nullptr;
         graph_ = nullptr;
         graph_key_.clear();
         uint32_t *tk = ticket_.as<uint32_t>();
-        uint32_t two = 2;
-        void *clear_args[] = {&tk, &two};
-        const WgJobDev *a_jobs = jobs_.as<const WgJobDev>();
-        uint32_t a_nj = nj, a_slot_jobs = n_slot_jobs, a_slot_blocks = n_slot_blocks;
-        const GenSel *a_gsel = gsel_.as<const GenSel>();
-        uint64_t *a_sizes = sizes_.as<uint64_t>();
-        WgOutDev *a_outs = outs_.as<WgOutDev>();
-        uint32_t *a_gbits = gbits;
-        uint64_t a_slot = slot_words;
-        void *wg_args[] = {&a_jobs, &a_nj, &a_slot_jobs, &a_slot_blocks, &a_gsel, &a_sizes, &a_outs, &tk, &a_gbits,
-                           &a_slot};
-        hipKernelNodeParams p0{}, p1{};
-        p0.func = reinterpret_cast<void *>(clear_u32_kernel);
-        p0.gridDim = dim3(1);
-        p0.blockDim = dim3(64);
-        p0.sharedMemBytes = 0;
-        p0.kernelParams = clear_args;
-        p0.extra = nullptr;
-        p1.func = reinterpret_cast<void *>(wg_growth_kernel);
-        p1.gridDim = dim3(grid);
-        p1.blockDim = dim3(t.block);
-        p1.sharedMemBytes = 0;
-        p1.kernelParams = wg_args;
-        p1.extra = nullptr;
+        uint32_t three = 3;
+        void *clear_args[] = {&tk, &three};
+        void *wg_args[] = {&args};
+        auto node = [](void *func, uint32_t grid_x, int block, void **kernel_args) {
+            hipKernelNodeParams p{};
+            p.func = func;
+            p.gridDim = dim3(grid_x);
+            p.blockDim = dim3(block);
+            p.sharedMemBytes = 0;
+            p.kernelParams = kernel_args;
+            p.extra = nullptr;
+            return p;
+        };
         hipGraphNode_t n0 = nullptr, n1 = nullptr;
         bool ok = hipGraphCreate(&graph_, 0) == hipSuccess;
+        const hipKernelNodeParams p0 = node(reinterpret_cast<void *>(clear_u32_kernel), 1, 64, clear_args);
         ok = ok && hipGraphAddKernelNode(&n0, graph_, nullptr, 0, &p0) == hipSuccess;
-        ok = ok && hipGraphAddKernelNode(&n1, graph_, &n0, 1, &p1) == hipSuccess;
+        if (grid.nine) {
+            const hipKernelNodeParams p =
+                node(reinterpret_cast<void *>(wg_growth_kernel<true>), grid.nine, t.block, wg_args);
+            ok = ok && hipGraphAddKernelNode(&n1, graph_, &n0, 1, &p) == hipSuccess;
+        }
+        if (grid.rest) {
+            const hipKernelNodeParams p =
+                node(reinterpret_cast<void *>(wg_growth_kernel<false>), grid.rest, t.block, wg_args);
+            ok = ok && hipGraphAddKernelNode(&n1, graph_, &n0, 1, &p) == hipSuccess;
+        }
         ok = ok && hipGraphInstantiate(&exec_, graph_, nullptr, nullptr, 0) == hipSuccess;
         if (ok) {
             graph_key_ = key;
@@ -623,11 +823,11 @@ namespace {
 
 constexpr size_t na_align(size_t x) { return (x + 255) & ~(size_t)255; }
 // layout of the scratch array
-constexpr size_t kNaOffTicket = 0;  // two uint32 queue tickets
+constexpr size_t kNaOffTicket = 0;  // three uint32 queue tickets
 constexpr size_t kNaOffOuts = 256;
 constexpr size_t kNaOffJobs = na_align(kNaOffOuts + sizeof(WgOutDev) * kNoAllocMaxJobs);
 constexpr size_t kNaOffGsel = na_align(kNaOffJobs + sizeof(WgJobDev) * kNoAllocMaxJobs);
-constexpr size_t kNaOffSizes = na_align(kNaOffGsel + sizeof(GenSel) * kNoAllocMaxGens);
+constexpr size_t kNaOffSizes = na_align(kNaOffGsel + sizeof(GenSel) * 2 * kNoAllocMaxGens);
 constexpr size_t kNaOffSlots = na_align(kNaOffSizes + sizeof(uint64_t) * kNoAllocMaxSizes);
 // one n = 10 slot: three bitmaps of 10!/32 words, rounded up to 64 words
 constexpr size_t kNaSlot10 = 3 * (((factorial(10) + 31) / 32 + 63) / 64 * 64) * sizeof(uint32_t);
@@ -689,8 +889,8 @@ void run_batch_noalloc(int n_jobs, const cg_job_t *jobs, cg_result_t *results, h
     }
     for (size_t j = 0; j < specs.size(); ++j) items.push_back({&specs[j], &results[idx[j]]});
     if (items.empty()) return;
-    const WgTables T = wg_tables(items, true);
-    if (T.gsel.size() > kNoAllocMaxGens)
+    const WgTables T = wg_tables(items);
+    if (T.gsel.size() > 2 * kNoAllocMaxGens)  // with their inverses
         throw Error(CG_E_INVAL, "cg_growth_batch_noalloc takes at most 32768 distinct generators in all");
     if (T.sizes_total > kNoAllocMaxSizes)
         throw Error(CG_E_INVAL, "cg_growth_batch_noalloc records at most 2^21 layer sizes in all "
@@ -709,27 +909,28 @@ void run_batch_noalloc(int n_jobs, const cg_job_t *jobs, cg_result_t *results, h
     uint32_t *gbits = T.slot_words ? reinterpret_cast<uint32_t *>(base + kNaOffSlots) : nullptr;
 
     // the launch shape of cg_growth_batch for the batch's largest n
-    const int block = T.n_max >= 10 ? 1024 : (T.n_max == 9 ? 512 : 256);
-    const uint32_t grid = wg_grid(nj, block);
+    const int block = wg_block(T.n_max);
+    const WgGrid grid = wg_grid(T, block);
     // workgroups that own a slot: as many as the slot area holds, at most
     // one per job that needs one
     uint32_t n_slot_blocks = 0;
     if (gbits) {
         const uint64_t slot_bytes = 3 * T.slot_words * sizeof(uint32_t);
         const uint64_t fit = (kNoAllocScratchBytes - kNaOffSlots) / slot_bytes;
-        n_slot_blocks = (uint32_t)std::min<uint64_t>({fit, (uint64_t)grid, (uint64_t)T.n_slot_jobs});
+        n_slot_blocks = (uint32_t)std::min<uint64_t>({fit, (uint64_t)grid.rest, (uint64_t)T.n10});
         if (n_slot_blocks < 1 || kNaOffSlots + (uint64_t)n_slot_blocks * slot_bytes > kNoAllocScratchBytes)
             throw Error(CG_E_DEVICE, "no-allocation slot layout");
     }
     CG_HIP(hipMemcpyAsync(djobs, T.jobs.data(), sizeof(WgJobDev) * nj, hipMemcpyHostToDevice, stream));
     CG_HIP(hipMemcpyAsync(dgsel, T.gsel.data(), sizeof(GenSel) * T.gsel.size(), hipMemcpyHostToDevice, stream));
     // the array keeps the last call's contents: the tickets start at zero
-    hipLaunchKernelGGL(clear_u32_kernel, dim3(1), dim3(64), 0, stream, ticket, 2u);
+    hipLaunchKernelGGL(clear_u32_kernel, dim3(1), dim3(64), 0, stream, ticket, 3u);
     CG_HIP(hipGetLastError());
     const double t_admit = now_seconds();
-    hipLaunchKernelGGL(wg_growth_kernel, dim3(grid), dim3(block), 0, stream, (const WgJobDev *)djobs, nj,
-                       T.n_slot_jobs, n_slot_blocks, (const GenSel *)dgsel, dsizes, outs, ticket, gbits,
-                       T.slot_words);
+    const WgLaunch args{djobs, T.n10, T.n9, nj, n_slot_blocks, dgsel, dsizes, outs, ticket, gbits, T.slot_words};
+    if (grid.nine) hipLaunchKernelGGL(wg_growth_kernel<true>, dim3(grid.nine), dim3(block), 0, stream, args);
+    CG_HIP(hipGetLastError());
+    if (grid.rest) hipLaunchKernelGGL(wg_growth_kernel<false>, dim3(grid.rest), dim3(block), 0, stream, args);
     CG_HIP(hipGetLastError());
     std::vector<uint64_t> hsz(T.sizes_total);
     std::vector<WgOutDev> ho(nj);

@@ -44,6 +44,18 @@ struct GenSel {
 };
 GenSel make_gensel(int n, const uint8_t *g);
 
+// A layer step over bitmaps, from layer d (F states; `before`: layer d-1) or
+// from the side of the unseen states: whether those make fewer tests than the
+// layer has neighbours. An unseen state of the next layer stops after about
+// three tests, the others take all k; listing and unranking one costs about
+// four. The next layer is taken to grow 0.7 times as much as the last one.
+__host__ __device__ inline bool pull_is_less(uint64_t unseen, uint64_t F, uint64_t before, uint64_t k) {
+    const double U = (double)unseen, f = (double)F;
+    const double grown = before ? 0.7 * f * f / (double)before : f;
+    const double next = grown < U ? grown : U;
+    return 3.0 * next + (double)k * (U - next) + 4.0 * U < f * (double)k;
+}
+
 // ---------------------------------------------------------------------------
 // Per-kernel HIP-event profiling (CG_PROFILE).
 // ---------------------------------------------------------------------------

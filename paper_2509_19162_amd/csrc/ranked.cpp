@@ -20,16 +20,6 @@ constexpr uint64_t kRbLargeCandidates = 1u << 20;
 // States a chain of steps may add where the layer array grows on demand.
 constexpr uint64_t kRbChainStates = 1u << 24;
 
-// Whether the unseen states make fewer tests than the frontier has
-// neighbours. Those of the next layer stop after about three, the others
-// take all k; one state costs about four tests to enumerate. The next layer
-// is taken to grow 0.7 times as much as the last one.
-bool pull_is_less(uint64_t unseen, const Engine::Progress &p, uint32_t k) {
-    const double U = (double)unseen, F = (double)p.F;
-    const double next = std::min(U, p.np ? 0.7 * F * F / (double)p.np : F);
-    return 3.0 * next + (double)k * (U - next) + 4.0 * U < F * (double)k;
-}
-
 }  // namespace
 
 bool rank_layers(const JobSpec &spec) {
@@ -168,7 +158,7 @@ bool Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
             // steps, as long as they are expected to stay small, whose sizes
             // are read back together
             bool large = large_ok && C >= kRbLargeCandidates;
-            const bool pull = large && pull_is_less(orbit - p.total, p, k);
+            const bool pull = large && pull_is_less(orbit - p.total, p.F, p.np, k);
             RbPlan plan;
             uint32_t chain = 1;
             uint64_t most = p.F, sum = std::min(orbit, C);
