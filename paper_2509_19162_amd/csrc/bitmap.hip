@@ -434,6 +434,70 @@ __global__ __launch_bounds__(kBmBlock) void bm_expand_kernel(const uint32_t *__r
     }
 }
 
+// The step from the other side, late in a growth: every unseen state looks
+// for a seen predecessor (its images under the inverse generators) and is in
+// the next layer iff there is one. No atomics: a state's bit is set by the
+// wave that owns its word. A wave lists the unseen bits of 16 words at a
+// time in LDS, so that its lanes take one state each. Bound by the tests at
+// random addresses (53 G/s in 780 MB), of which there are fewer: S_13 by two
+// random generators and their inverses 794 -> 617 ms. Sets of even
+// permutations reach half of S_n, the other half stays unseen, and the rule
+// stays with the expansion.
+template <int N>
+__global__ __launch_bounds__(kBmBlock) void bm_pull_kernel(const uint32_t *__restrict__ vis,
+                                                           uint32_t *__restrict__ nxt, uint32_t *snxt, uint64_t W,
+                                                           const GenSel *__restrict__ ginv, int k) {
+    using R = RankOf<N>;
+    constexpr uint32_t kWords = 16, kWaves = kBmBlock / kWave;
+    __shared__ GenSel s_sel[kBitmapMaxK];
+    __shared__ uint16_t s_list[kWaves][kWords * 32];
+    __shared__ uint32_t s_new[kWaves][kWords];
+    for (int i = threadIdx.x; i < k * 8; i += kBmBlock) (&s_sel[0].sel[0])[i] = (&ginv[0].sel[0])[i];
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    uint16_t *list = s_list[wave];
+    uint32_t *fresh = s_new[wave];
+    const uint64_t pieces = (W + kWords - 1) / kWords;
+    for (uint64_t c = (uint64_t)blockIdx.x * kWaves + wave; c < pieces; c += (uint64_t)gridDim.x * kWaves) {
+        const uint64_t w = c * kWords + (lane >> 2);
+        uint32_t x = w < W ? ~vis[w] : 0u;
+        if (lane < kWords) fresh[lane] = 0;
+        x = (x >> (8u * (lane & 3u))) & 255u;
+        uint32_t n = 0;
+#pragma unroll
+        for (uint32_t b = 0; b < 8; ++b) {
+            const bool on = (x >> b) & 1u;
+            const uint64_t m = __ballot(on);
+            if (on) list[n + mask_rank(m)] = (uint16_t)(lane << 3 | b);
+            n += (uint32_t)__popcll(m);
+        }
+        if (!n) continue;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (uint32_t i = lane; i < n; i += kWave) {
+            const uint32_t bit = list[i];
+            const R r = (R)(c * (kWords * 32)) + (R)bit;
+            if ((uint64_t)r >= factorial(N)) continue;  // past the last rank, in the last word
+            const Nibbles s = split_nibbles(perm_unrank_t<N, R>(r));
+            for (int g = 0; g < k; ++g) {
+                const uint64_t q = (uint64_t)perm_rank_t<N, R>(apply_gensel(s, s_sel[g]));
+                if ((vis[q >> 5] >> (uint32_t)(q & 31u)) & 1u) {
+                    atomicOr(&fresh[bit >> 5], 1u << (bit & 31u));
+                    break;
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t f = lane < kWords ? fresh[lane] : 0u;
+        if (f) {
+            nxt[c * kWords + lane] = f;
+            const uint64_t qc = (c * kWords) / kChunkWords;
+            atomicOr(&snxt[qc >> 5], 1u << (uint32_t)(qc & 31u));
+        }
+    }
+}
+
 // visited |= next (counted), and the expanded layer is cleared, over the
 // chunks that either touches.
 __global__ __launch_bounds__(kBmBlock) void bm_fold_kernel(uint32_t *__restrict__ vis, uint32_t *__restrict__ cur,
@@ -980,8 +1044,14 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     scur.ensure(sw * 4);
     snxt.ensure(sw * 4);
     cnt.ensure(64);
-    std::vector<GenSel> hs(std::max(1, k));
-    for (int g = 0; g < k; ++g) hs[g] = make_gensel(n, spec.gens.data() + (size_t)g * n);
+    std::vector<GenSel> hs(std::max(1, 2 * k));  // the generators, then their inverses
+    for (int g = 0; g < k; ++g) {
+        const uint8_t *row = spec.gens.data() + (size_t)g * n;
+        uint8_t inv[16] = {0};
+        for (int i = 0; i < n; ++i) inv[row[i]] = (uint8_t)i;
+        hs[g] = make_gensel(n, row);
+        hs[k + g] = make_gensel(n, inv);
+    }
     gsel.ensure(sizeof(GenSel) * hs.size());
     CG_HIP(hipMemcpyAsync(gsel.p, hs.data(), sizeof(GenSel) * hs.size(), hipMemcpyHostToDevice, s));
     CG_HIP(hipMemsetAsync(vis.p, 0, W * 4, s));
@@ -1004,8 +1074,11 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     CG_HIP(hipHostMalloc((void **)&host_cnt, sizeof(uint64_t), hipHostMallocDefault));
     uint32_t *pc = cur.as<uint32_t>(), *pn = nxt.as<uint32_t>(), *sc = scur.as<uint32_t>(),
              *sn = snxt.as<uint32_t>();
-    uint64_t F = 1;
+    uint64_t F = 1, before = 0, seen = 1;
     int layers = 1, status = CG_OK;
+    // every step from the unseen side goes over the whole bitmap: not for
+    // layers whose neighbours are fewer than its words
+    const uint32_t grid_all = (uint32_t)std::min<uint64_t>((W + 63) / 64, (uint64_t)device_cus() * 32);
     try {
         for (;;) {
             if (k == 0) break;
@@ -1017,9 +1090,15 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
                 status = CG_TRUNCATED;
                 break;
             }
+            const bool pull = F * (uint64_t)k >= W && pull_is_less(S - seen, F, before, (uint64_t)k);
             with_bm_n(n, [&](auto NN) {
-                hipLaunchKernelGGL(bm_expand_kernel<decltype(NN)::value>, dim3(grid), dim3(kBmBlock), 0, s, pc, sc,
-                                   vis.as<const uint32_t>(), pn, sn, W, nchunks, gsel.as<const GenSel>(), k);
+                if (pull)
+                    hipLaunchKernelGGL(bm_pull_kernel<decltype(NN)::value>, dim3(grid_all), dim3(kBmBlock), 0, s,
+                                       vis.as<const uint32_t>(), pn, sn, W, gsel.as<const GenSel>() + k, k);
+                else
+                    hipLaunchKernelGGL(bm_expand_kernel<decltype(NN)::value>, dim3(grid), dim3(kBmBlock), 0, s,
+                                       pc, sc, vis.as<const uint32_t>(), pn, sn, W, nchunks, gsel.as<const GenSel>(),
+                                       k);
             });
             CG_HIP(hipGetLastError());
             hipLaunchKernelGGL(bm_fold_kernel, dim3(grid), dim3(kBmBlock), 0, s, vis.as<uint32_t>(), pc, sc, pn, sn,
@@ -1040,7 +1119,9 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
             std::swap(sc, sn);
             if (N == 0) break;
             sizes[layers++] = N;
+            before = F;
             F = N;
+            seen += N;
         }
     } catch (...) {
         (void)hipStreamSynchronize(s);

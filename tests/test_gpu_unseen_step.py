@@ -1,0 +1,40 @@
+"""The bitmask engine's step from the side of the unseen states: sizes against
+the CPU oracle, the default engine and the closed form of the bubble-sort
+growth (Mahonian numbers). Bitmaps whose last word is whole (n >= 8) and not,
+directed sets, starts, and sets that reach a part of S_n only (the unseen
+states never run out). Tolerance: none (exact integers)."""
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2509_19162_amd import api  # noqa: E402
+from paper_2509_19162_amd import inputs as I  # noqa: E402
+
+
+@pytest.mark.parametrize("n", [4, 7, 9, 10])
+@pytest.mark.parametrize("fam", ["all_transpositions", "reversals", "pancake", "star"])
+def test_families(n, fam, oracle_c):
+    gens = I.family(fam, n)
+    assert api.growth_ex(n, gens, max_layers=512, bitmask=True).sizes == oracle_c.growth(n, gens, max_layers=512)[0]
+
+
+@pytest.mark.parametrize("n", [5, 8, 10, 11])
+@pytest.mark.parametrize("m,directed", [(2, True), (3, False), (5, True)])
+def test_random_sets_starts_and_rules(n, m, directed):
+    r = I.rng_for(n, seed=61 + m)
+    gens = I.random_perms_with_inverses(n, m, r)
+    gens = gens[:m] if directed else gens
+    start = [int(x) for x in r.permutation(n)]
+    for kw in (dict(max_layers=512), dict(max_layers=7), dict(max_layers=512, max_frontier=10**5)):
+        got = api.growth_ex(n, gens, start=start, allow_directed=directed, bitmask=True, **kw)
+        ref = api.growth_ex(n, gens, start=start, allow_directed=directed, packed_sort=True, **kw)
+        assert (got.status, got.sizes, got.states_expanded, got.candidates) == (
+            ref.status, ref.sizes, ref.states_expanded, ref.candidates)
+
+
+def test_mahonian_12():
+    row = [1]
+    for m in range(2, 13):
+        row = [sum(row[max(0, j - m + 1) : j + 1]) for j in range(len(row) + m - 1)]
+    assert api.growth_ex(12, I.family("coxeter", 12), max_layers=512, bitmask=True).sizes == row
