@@ -50,20 +50,6 @@ uint64_t host_rank64(uint64_t key, int n) {
     return rank;
 }
 
-// Wait for all waves of the workgroup, then drop stale L1 lines: bitmap
-// words change by atomics in the L2. Only this workgroup touches them, so
-// nothing has to leave its own L2.
-__device__ __forceinline__ void wg_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-}
-// OR into a word that only this workgroup uses: performed in LDS, or in the
-// nearest L2 (at device scope it would go to memory, 27 G/s for the chip).
-__device__ __forceinline__ void wg_or(uint32_t *p, uint32_t m) {
-    __hip_atomic_fetch_or(p, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
@@ -89,6 +75,15 @@ constexpr int kWgMaxBlock = 1024;
 constexpr uint32_t kWgWaves = kWgMaxBlock / kWave;
 constexpr uint32_t kWgChunk = 16;  // bitmap words a wave lists at a time
 constexpr uint32_t wg_words(int n) { return (uint32_t)((factorial(n) + 31) / 32); }
+// n = 10: the bitmap in parts of 2^20 bits.
+constexpr uint32_t kWgLgPart = 20, kWgParts = 4;
+constexpr uint32_t kWgPartWords = 1u << (kWgLgPart - 5);
+static_assert((uint64_t)kWgParts << kWgLgPart >= factorial(10), "parts cover the bitmap");
+// Words of a slot: three bitmaps and the lists of neighbours (their length
+// is divided among the waves and parts).
+constexpr uint64_t kWgSlotBits = (wg_words(10) + 63) / 64 * 64;
+constexpr uint64_t kWgListWords = 512u << 10;
+constexpr uint64_t kWgListWordsNoAlloc = 64u << 10;
 
 // ---- states of n <= 8 ------------------------------------------------------------
 // A state is eight bytes, entry i in byte i (of fewer than eight entries the
@@ -158,43 +153,110 @@ struct Wg8 {
 
 template <int N>
 struct WgN {
-    const GenSel *sel;
+    const GenSel *sel;  // in device memory
     using State = Nibbles;
     __device__ __forceinline__ State unrank(uint32_t r) const { return split_nibbles(perm_unrank_t<N>(r)); }
     __device__ __forceinline__ uint32_t neighbour(const State &s, uint32_t g) const {
-        return perm_rank_t<N>(apply_gensel(s, sel[g]));
+        return perm_rank_t<N>(apply_gensel(s, uniform_gensel(sel, g)));
     }
 };
 
-// One job. A layer's states are the set bits of `cur`; a wave lists the set
-// bits of 16 words at a time in LDS (`list`, its own 512 entries), so that
-// its lanes take one state each however the bits lie. Either every state of
-// the layer forms its neighbours, and those not seen are set in `nxt`; or,
-// when few states are left, every unseen state looks for a seen predecessor
-// (under the inverse generators, after the k generators in the codec's
-// table) and is set in `nxt` at the first (the wave owns its word: the bits
-// gather in `fresh`, 16 words of its own). `whole`: the bitmap holds no bits
-// of states outside S_n (then, and only then, unseen bits may be taken from
-// it). kGlobal: the bitmaps are in device memory.
-// Up to n = 9 the chain of a neighbour (two or three lookups, the test) times
-// the layers bounds it, so all lanes have to be busy: one growth of S_8 by
-// its Coxeter set is 94 us (29 layers; the call takes 160 us, and 440 when each
-// lane looped over a word's bits and computed ranks), 1024 growths of S_9 6.9 ms. At
-// n = 10 it is the reads and atomics at random addresses of 340 MB of slots:
-// 225 ms for 1365 growths, the same with one or two workgroups a CU.
-template <bool kGlobal, class C>
+// The set bits of 16 words (16 c ..) in `list`: bit numbers from the first
+// word on. Returns how many.
+__device__ __forceinline__ uint32_t wg_list(const uint32_t *words, bool unset, uint32_t c, uint32_t W, uint16_t *list) {
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t w = c * kWgChunk + (lane >> 2);
+    uint32_t x = 0;
+    if (w < W) x = unset ? ~words[w] : words[w];
+    x = (x >> (8u * (lane & 3u))) & 255u;
+    uint32_t n = 0;
+#pragma unroll
+    for (uint32_t b = 0; b < 8; ++b) {
+        const bool on = (x >> b) & 1u;
+        const uint64_t m = __ballot(on);
+        if (on) list[n + mask_rank(m)] = (uint16_t)(lane << 3 | b);
+        n += (uint32_t)__popcll(m);
+    }
+    return n;
+}
+__device__ __forceinline__ void wg_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+// The unseen states of chunk c that have a seen predecessor (under the
+// inverse generators, after the k generators in the codec's table): their
+// bits in `fresh`, 16 words of the wave's own, zero before.
+template <class C>
+__device__ __forceinline__ void wg_pull(const C &codec, uint32_t k, const uint32_t *vis, uint32_t c, uint32_t W,
+                                        uint16_t *list, uint32_t *fresh) {
+    const uint32_t n = wg_list(vis, true, c, W, list);
+    wg_wave_sync();
+    for (uint32_t i = threadIdx.x & (kWave - 1); i < n; i += kWave) {
+        const uint32_t bit = list[i];
+        const typename C::State s = codec.unrank(c * (kWgChunk * 32u) + bit);
+        for (uint32_t g = k; g < 2 * k; ++g) {
+            const uint32_t q = codec.neighbour(s, g);
+            if ((vis[q >> 5] >> (q & 31u)) & 1u) {
+                atomicOr(&fresh[bit >> 5], 1u << (bit & 31u));
+                break;
+            }
+        }
+    }
+    wg_wave_sync();
+}
+
+// What a growth keeps between its layers, and the stop rules.
+struct WgLayers {
+    uint64_t F = 1, before = 0, expanded = 0, seen = 1;
+    uint32_t layers = 1;
+    int status = CG_OK;
+    __device__ __forceinline__ bool done(const WgJobDev &J) {
+        if (J.k == 0) return true;
+        if ((J.max_frontier && F > J.max_frontier) || layers >= J.max_layers) {
+            status = CG_TRUNCATED;
+            return true;
+        }
+        return false;
+    }
+    // the next layer has n1 states; false: none
+    __device__ __forceinline__ bool next(uint32_t n1, uint64_t *sizes) {
+        expanded += F;
+        if (n1 == 0) return false;
+        if (threadIdx.x == 0) sizes[layers] = n1;
+        ++layers;
+        before = F;
+        F = n1;
+        seen += n1;
+        return true;
+    }
+    __device__ __forceinline__ void store(WgOutDev *out) const {
+        if (threadIdx.x == 0) {
+            out->status = status;
+            out->num_layers = (int32_t)layers;
+            out->expanded = expanded;
+        }
+    }
+};
+
+// One job with its bitmaps in LDS. A layer's states are the set bits of
+// `cur`; a wave lists those of 16 words at a time, so that its lanes take
+// one state each however the bits lie. Either every state of the layer forms
+// its neighbours, and those not seen are set in `nxt`; or, when few states
+// are left, every unseen state looks for a seen predecessor and is set in
+// `nxt` at the first (the wave owns its word). `whole`: the bitmap holds no
+// bits of states outside S_n (then, and only then, unseen bits may be taken
+// from it).
+// The chain of a neighbour (two or three lookups, the test) times the layers
+// bounds it, so all lanes have to be busy: one growth of S_8 by its Coxeter
+// set is 94 us (29 layers; the call takes 160 us, and 440 when each lane
+// looped over a word's bits and computed ranks), 1024 growths of S_9 6.9 ms.
+template <class C>
 __device__ __forceinline__ void wg_run(const WgJobDev &J, const C &codec, uint32_t W, uint64_t states, bool whole,
                                        uint32_t *vis, uint32_t *cur, uint32_t *nxt, uint16_t *list, uint32_t *fresh,
                                        uint64_t *__restrict__ sizes, WgOutDev *__restrict__ out, uint32_t *s_acc) {
     const uint32_t tid = threadIdx.x, nt = blockDim.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const uint32_t waves = nt / kWave;
     const uint32_t k = J.k;
-    auto barrier = [] {
-        if constexpr (kGlobal)
-            wg_barrier();
-        else
-            __syncthreads();
-    };
     for (uint32_t w = tid; w < W; w += nt) {
         vis[w] = 0u;
         cur[w] = 0u;
@@ -202,85 +264,42 @@ __device__ __forceinline__ void wg_run(const WgJobDev &J, const C &codec, uint32
     }
     if (tid == 0) *s_acc = 0;
     if (lane < kWgChunk) fresh[lane] = 0;
-    barrier();
+    __syncthreads();
     if (tid == 0) {
         const uint32_t r = J.start_rank;
         vis[r >> 5] = 1u << (r & 31u);
         cur[r >> 5] = 1u << (r & 31u);
         sizes[0] = 1;
     }
-    barrier();
-    uint64_t F = 1, before = 0, expanded = 0, seen = 1;
-    uint32_t layers = 1;
-    int status = CG_OK;
-    for (;;) {
-        if (k == 0) break;
-        if (J.max_frontier && F > J.max_frontier) {
-            status = CG_TRUNCATED;
-            break;
-        }
-        if (layers >= J.max_layers) {
-            status = CG_TRUNCATED;
-            break;
-        }
-        const bool pull = whole && pull_is_less(states - seen, F, before, k);
+    __syncthreads();
+    WgLayers L;
+    while (!L.done(J)) {
+        const bool pull = whole && pull_is_less(states - L.seen, L.F, L.before, k);
         for (uint32_t c = wave; c * kWgChunk < W; c += waves) {
-            const uint32_t w = c * kWgChunk + (lane >> 2);
-            uint32_t x = 0;
-            if (w < W) x = pull ? ~vis[w] : cur[w];
-            x = (x >> (8u * (lane & 3u))) & 255u;
-            uint32_t n = 0;
-#pragma unroll
-            for (uint32_t b = 0; b < 8; ++b) {
-                const bool on = (x >> b) & 1u;
-                const uint64_t m = __ballot(on);
-                if (on) list[n + mask_rank(m)] = (uint16_t)(lane << 3 | b);
-                n += (uint32_t)__popcll(m);
+            if (pull) {
+                wg_pull(codec, k, vis, c, W, list, fresh);
+                if (lane < kWgChunk) {
+                    const uint32_t x = fresh[lane];
+                    if (x) {
+                        nxt[c * kWgChunk + lane] = x;
+                        fresh[lane] = 0;
+                    }
+                }
+                continue;
             }
+            const uint32_t n = wg_list(cur, false, c, W, list);
             if (!n) continue;
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            wg_wave_sync();
             for (uint32_t i = lane; i < n; i += kWave) {
-                const uint32_t r = c * (kWgChunk * 32u) + list[i];
-                const typename C::State s = codec.unrank(r);
-                if (!pull) {
-                    // bitmaps in memory: the words of four neighbours are
-                    // under way together
-                    constexpr uint32_t kAhead = kGlobal ? 4 : 1;
-                    for (uint32_t g0 = 0; g0 < k; g0 += kAhead) {
-                        uint32_t q[kAhead], v[kAhead];
-#pragma unroll
-                        for (uint32_t u = 0; u < kAhead; ++u) {
-                            q[u] = codec.neighbour(s, g0 + u < k ? g0 + u : k - 1);
-                            v[u] = vis[q[u] >> 5];
-                        }
-#pragma unroll
-                        for (uint32_t u = 0; u < kAhead; ++u) {
-                            const uint32_t m = 1u << (q[u] & 31u);
-                            if (!(v[u] & m)) wg_or(&nxt[q[u] >> 5], m);
-                        }
-                    }
-                } else {
-                    for (uint32_t g = k; g < 2 * k; ++g) {
-                        const uint32_t q = codec.neighbour(s, g);
-                        if ((vis[q >> 5] >> (q & 31u)) & 1u) {
-                            atomicOr(&fresh[list[i] >> 5], 1u << (r & 31u));
-                            break;
-                        }
-                    }
+                const typename C::State s = codec.unrank(c * (kWgChunk * 32u) + list[i]);
+                for (uint32_t g = 0; g < k; ++g) {
+                    const uint32_t q = codec.neighbour(s, g), m = 1u << (q & 31u);
+                    if (!(vis[q >> 5] & m)) atomicOr(&nxt[q >> 5], m);
                 }
             }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            if (pull && lane < kWgChunk) {
-                const uint32_t x1 = fresh[lane];
-                if (x1) {
-                    nxt[c * kWgChunk + lane] = x1;
-                    fresh[lane] = 0;
-                }
-            }
+            wg_wave_sync();
         }
-        barrier();
+        __syncthreads();
         // fold: visited |= next, count it, clear the expanded layer
         uint32_t cnt = 0;
         for (uint32_t w = tid; w < W; w += nt) {
@@ -293,26 +312,197 @@ __device__ __forceinline__ void wg_run(const WgJobDev &J, const C &codec, uint32
         }
         cnt = wave_sum(cnt);
         if (lane == 0 && cnt) atomicAdd(s_acc, cnt);
-        barrier();
+        __syncthreads();
         const uint32_t n1 = *s_acc;
-        expanded += F;
         uint32_t *t = cur;
         cur = nxt;
         nxt = t;
-        if (n1 == 0) break;
-        if (tid == 0) sizes[layers] = n1;
-        ++layers;
-        before = F;
-        F = n1;
-        seen += n1;
-        barrier();  // every thread has read s_acc before it is reset
+        if (!L.next(n1, sizes)) break;
+        __syncthreads();  // every thread has read s_acc before it is reset
         if (tid == 0) *s_acc = 0;
     }
-    if (tid == 0) {
-        out->status = status;
-        out->num_layers = (int32_t)layers;
-        out->expanded = expanded;
+    L.store(out);
+}
+
+// One job of n = 10: its bitmaps (454 KB each) lie in device memory, where
+// tests and ORs at random addresses run at 53 and 27 G/s for the whole chip.
+// So neighbours are not tested one by one: each wave appends them to four
+// lists of its own, one per part of the bitmap, in order (16-lane pieces of
+// whole lines); then, part by part, the workgroup ORs its lists into a part
+// in LDS, takes away what was seen and writes the next layer's words. A list
+// that is full ends the round of its wave; the others end theirs likewise,
+// the lists are applied and the waves go on where they were. Late in a growth
+// the unseen states look for a seen predecessor in the bitmap in memory; such
+// a test weighs four neighbours here.
+// A batch of 4096 jobs (1365 of n = 10, four or more generators): this launch
+// 86 ms, 222 ms with tests and ORs in the bitmaps in memory; bound by the
+// instructions that form the neighbours' ranks.
+constexpr uint32_t kWgSpan = 8;                            // words listed at a time
+constexpr uint32_t kWgQueue = kWgSpan * 32 + kWave;        // states a wave holds
+template <class C>
+__device__ __forceinline__ void wg_run_parts(const WgJobDev &J, const C &codec, uint32_t *vis, uint32_t *cur,
+                                             uint32_t *nxt, uint32_t *lists, uint32_t cap, uint32_t *part,
+                                             uint32_t *queue, uint32_t *fresh, uint64_t *__restrict__ sizes,
+                                             WgOutDev *__restrict__ out, uint32_t *s_acc, uint32_t *s_more) {
+    constexpr uint32_t W = wg_words(10), kSpans = kWave / kWgSpan;
+    static_assert(W % 4 == 0, "bitmaps of whole uint4");
+    const uint32_t tid = threadIdx.x, nt = blockDim.x, lane = tid & (kWave - 1);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave)), waves = nt / kWave;
+    const uint32_t k = (uint32_t)__builtin_amdgcn_readfirstlane((int)J.k);
+    uint32_t *const mine = lists + (uint64_t)wave * kWgParts * cap;
+    for (uint32_t w = tid; w < W; w += nt) {
+        vis[w] = 0u;
+        cur[w] = 0u;
     }
+    for (uint32_t w = tid; w < kWgPartWords; w += nt) part[w] = 0u;
+    if (tid == 0) *s_acc = *s_more = 0;
+    if (lane < kWgChunk) fresh[lane] = 0;
+    __syncthreads();
+    if (tid == 0) {
+        const uint32_t r = J.start_rank;
+        vis[r >> 5] = 1u << (r & 31u);
+        cur[r >> 5] = 1u << (r & 31u);
+        sizes[0] = 1;
+    }
+    __syncthreads();
+    WgLayers L;
+    while (!L.done(J)) {
+        uint32_t cnt = 0;
+        if (pull_is_less(factorial(10) - L.seen, L.F, L.before, k, 4.0)) {
+            for (uint32_t c = wave; c * kWgChunk < W; c += waves) {
+                wg_pull(codec, k, vis, c, W, (uint16_t *)queue, fresh);
+                if (lane < kWgChunk && c * kWgChunk + lane < W) {
+                    nxt[c * kWgChunk + lane] = fresh[lane];
+                    fresh[lane] = 0;
+                }
+            }
+            __syncthreads();
+            for (uint32_t w = tid; w < W; w += nt) {
+                const uint32_t x = nxt[w];
+                if (x) {
+                    vis[w] |= x;
+                    cnt += (uint32_t)__popc(x);
+                }
+            }
+        } else {
+            // where the wave is: its span of the 64 words of which a lane
+            // holds one, the states in its queue, and the next generator
+            uint32_t block = wave, span = kSpans, held = 0, g = 0, x = 0;
+            uint64_t some = 0;  // lanes with states left
+            for (bool first = true;; first = false) {
+                uint32_t fill[kWgParts] = {0, 0, 0, 0};
+                bool full = false;
+                while (!full) {
+                    if (held < kWave && g == 0) {
+                        if (span == kSpans) {
+                            if (block * kWave < W) {
+                                const uint32_t w = block * kWave + lane;
+                                x = w < W ? cur[w] : 0u;
+                                some = __ballot(x != 0);
+                                block += waves;
+                                span = 0;
+                                continue;
+                            }
+                        } else {
+                            if ((some >> (kWgSpan * span)) & ((1u << kWgSpan) - 1u)) {
+                                // four bits of a word per lane
+                                const uint32_t from = span * kWgSpan + lane / 8u;
+                                const uint32_t y = __shfl(x, (int)from, kWave) >> (4u * (lane & 7u));
+                                const uint32_t r0 = ((block - waves) * kWave + from) * 32u + 4u * (lane & 7u);
+#pragma unroll
+                                for (uint32_t b = 0; b < 4; ++b) {
+                                    const bool on = (y >> b) & 1u;
+                                    const uint64_t m = __ballot(on);
+                                    if (on) queue[held + mask_rank(m)] = r0 + b;
+                                    held += (uint32_t)__popcll(m);
+                                }
+                                wg_wave_sync();
+                            }
+                            ++span;
+                            continue;
+                        }
+                        if (held == 0) break;
+                    }
+                    const uint32_t take = held < kWave ? held : (uint32_t)kWave;
+                    const bool on = lane < take;
+                    const uint64_t in = __ballot(on);
+                    const typename C::State s = codec.unrank(queue[held - take + (on ? lane : 0u)]);
+                    for (; g < k; ++g) {
+                        if (max(max(fill[0], fill[1]), max(fill[2], fill[3])) + kWave > cap) {
+                            full = true;
+                            break;
+                        }
+                        const uint32_t q = codec.neighbour(s, g), d = q >> kWgLgPart;
+                        const uint64_t b0 = __ballot(d & 1u), b1 = __ballot(d & 2u);
+                        const uint64_t m[kWgParts] = {in & ~b1 & ~b0, in & ~b1 & b0, in & b1 & ~b0, in & b1 & b0};
+                        uint32_t at = 0;
+#pragma unroll
+                        for (uint32_t p = 0; p < kWgParts; ++p) {
+                            const uint32_t pos = __builtin_amdgcn_mbcnt_hi(
+                                (uint32_t)(m[p] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[p], fill[p]));
+                            at = d == p ? p * cap + pos : at;
+                            fill[p] += (uint32_t)__popcll(m[p]);
+                        }
+                        if (on) mine[at] = q & ((1u << kWgLgPart) - 1u);
+                    }
+                    if (!full) {
+                        held -= take;
+                        g = 0;
+                    }
+                }
+                if (full && lane == 0) *s_more = 1;
+                __syncthreads();
+                const bool more = *s_more != 0;
+#pragma unroll
+                for (uint32_t p = 0; p < kWgParts; ++p) {
+                    const uint32_t *const in = mine + (uint64_t)p * cap;
+                    for (uint32_t i = 4u * lane; i < fill[p]; i += 4u * kWave) {
+                        const uint4 v = *reinterpret_cast<const uint4 *>(in + i);
+                        const uint32_t q[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                        for (uint32_t j = 0; j < 4; ++j)
+                            if (i + j < fill[p]) atomicOr(&part[q[j] >> 5], 1u << (q[j] & 31u));
+                    }
+                    __syncthreads();
+                    if (tid == 0) *s_more = 0;  // every thread has read it
+                    constexpr uint32_t kAll = kWgPartWords / 4;
+                    const uint32_t n4 = min(kAll, W / 4 - p * kAll);
+                    uint4 *const pt = reinterpret_cast<uint4 *>(part);
+                    uint4 *const vs = reinterpret_cast<uint4 *>(vis) + p * kAll;
+                    uint4 *const nx = reinterpret_cast<uint4 *>(nxt) + p * kAll;
+                    for (uint32_t i = tid; i < n4; i += nt) {
+                        uint4 f = pt[i];
+                        const bool any = (f.x | f.y | f.z | f.w) != 0;
+                        if (any) {
+                            uint4 v = vs[i];
+                            f = make_uint4(f.x & ~v.x, f.y & ~v.y, f.z & ~v.z, f.w & ~v.w);
+                            cnt += (uint32_t)(__popc(f.x) + __popc(f.y) + __popc(f.z) + __popc(f.w));
+                            pt[i] = make_uint4(0, 0, 0, 0);
+                            vs[i] = make_uint4(v.x | f.x, v.y | f.y, v.z | f.z, v.w | f.w);
+                            if (!first) {
+                                v = nx[i];
+                                f = make_uint4(v.x | f.x, v.y | f.y, v.z | f.z, v.w | f.w);
+                            }
+                        }
+                        if (first || any) nx[i] = f;
+                    }
+                    __syncthreads();
+                }
+                if (!more) break;
+            }
+        }
+        cnt = wave_sum(cnt);
+        if (lane == 0 && cnt) atomicAdd(s_acc, cnt);
+        __syncthreads();
+        const uint32_t n1 = *s_acc;
+        uint32_t *t = cur;
+        cur = nxt;
+        nxt = t;
+        if (!L.next(n1, sizes)) break;
+        __syncthreads();  // every thread has read s_acc before it is reset
+        if (tid == 0) *s_acc = 0;
+    }
+    L.store(out);
 }
 
 // The jobs of a launch, in order: n = 10 (bitmaps in device slots), n = 9
@@ -325,62 +515,69 @@ struct WgLaunch {
     uint64_t *sizes;
     WgOutDev *outs;
     uint32_t *ticket;      // three queues
-    uint32_t *gbits;       // slots of 3 * slot_words words
+    uint32_t *gbits;       // slots of slot_words words
     uint64_t slot_words;
 };
 
 // A persistent launch: each workgroup takes the next job from a queue (jobs
 // are ordered by decreasing size within their range) and runs it to
-// completion. kNine: the jobs of n = 9, ticket[2]. Else ticket[0] hands the
-// jobs of n = 10 to the workgroups that own a slot, ticket[1] those of n <= 8
-// to every workgroup.
-template <bool kNine>
-__global__ __launch_bounds__(kWgMaxBlock) __attribute__((amdgpu_waves_per_eu(kNine ? 4 : 8))) void wg_growth_kernel(
+// completion. ticket[0] hands the jobs of n = 10 to the workgroups that own a
+// slot, ticket[1] those of n = 9, ticket[2] the others. kBig: the launch with
+// the LDS of a whole CU, which takes from all three; else from the last only.
+template <bool kBig>
+__global__ __launch_bounds__(kWgMaxBlock) __attribute__((amdgpu_waves_per_eu(kBig ? 4 : 8))) void wg_growth_kernel(
     WgLaunch a) {
     struct Small {
         uint32_t bits[3 * wg_words(8)];
         Wg8Tables tables;
+        GenSel sel[2 * kBitmapMaxK];
     };
-    constexpr uint32_t kBytes = kNine ? 3 * 4 * wg_words(9) : (uint32_t)sizeof(Small);
+    constexpr uint32_t kBytes = kBig ? 3 * 4 * wg_words(9) : (uint32_t)sizeof(Small);
+    static_assert(kBytes >= sizeof(Small) && (!kBig || kBytes >= 4 * kWgPartWords), "one area for every range");
     __shared__ __align__(16) unsigned char s_area[kBytes];
-    __shared__ uint16_t s_list[kWgWaves][kWgChunk * 32];
+    __shared__ __align__(16) uint32_t s_list[kWgWaves][kBig ? kWgQueue : kWgChunk * 16];
     __shared__ uint32_t s_fresh[kWgWaves][kWgChunk];
-    __shared__ GenSel s_sel[2 * kBitmapMaxK];
-    __shared__ uint32_t s_acc, s_job;
-    uint16_t *list = s_list[threadIdx.x / kWave];
-    uint32_t *fresh = s_fresh[threadIdx.x / kWave];
-    if constexpr (!kNine)
-        if (a.n10 + a.n9 < a.njobs) wg8_build(reinterpret_cast<Small *>(s_area)->tables);
-    const bool has_slot = !kNine && a.gbits && blockIdx.x < a.slot_blocks;
-    for (uint32_t q = kNine ? 2u : (has_slot ? 0u : 1u); q < (kNine ? 3u : 2u); ++q) {
-        const uint32_t lo = q == 0 ? 0u : (q == 2 ? a.n10 : a.n10 + a.n9);
-        const uint32_t hi = q == 0 ? a.n10 : (q == 2 ? a.n10 + a.n9 : a.njobs);
+    __shared__ uint32_t s_acc, s_more, s_job;
+    const uint32_t wave = threadIdx.x / kWave;
+    uint32_t *const queue = s_list[wave], *const fresh = s_fresh[wave];
+    uint16_t *const list = reinterpret_cast<uint16_t *>(queue);
+    Small &sm = *reinterpret_cast<Small *>(s_area);
+    bool built = false;
+    const bool has_slot = kBig && a.gbits && blockIdx.x < a.slot_blocks;
+    for (uint32_t q = kBig ? (has_slot ? 0u : 1u) : 2u; q < 3u; ++q) {
+        const uint32_t lo = q == 0 ? 0u : (q == 1 ? a.n10 : a.n10 + a.n9);
+        const uint32_t hi = q == 0 ? a.n10 : (q == 1 ? a.n10 + a.n9 : a.njobs);
         for (;;) {
             if (threadIdx.x == 0) s_job = atomicAdd(a.ticket + q, 1u);
             __syncthreads();
-            const uint32_t t = s_job;
+            const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_job);
             __syncthreads();
             if (t >= hi - lo) break;
             const uint32_t j = lo + t;
             const WgJobDev J = a.jobs[j];
-            for (uint32_t i = threadIdx.x; i < 2 * J.k * 8u; i += blockDim.x)
-                (&s_sel[0].sel[0])[i] = (&a.gtab[J.goff].sel[0])[i];
+            const GenSel *gens = a.gtab + (uint32_t)__builtin_amdgcn_readfirstlane((int)J.goff);
             uint64_t *sz = a.sizes + J.sizes_off;
             WgOutDev *out = a.outs + j;
-            if constexpr (kNine) {
-                constexpr uint32_t W = wg_words(9);
-                uint32_t *bits = reinterpret_cast<uint32_t *>(s_area);
-                wg_run<false>(J, WgN<9>{s_sel}, W, factorial(9), true, bits, bits + W, bits + 2 * W, list, fresh, sz, out,
-                              &s_acc);
-            } else if (q == 0) {
-                uint32_t *slot = a.gbits + (uint64_t)blockIdx.x * 3ull * a.slot_words;
-                wg_run<true>(J, WgN<10>{s_sel}, wg_words(10), factorial(10), true, slot, slot + a.slot_words,
-                             slot + 2 * a.slot_words, list, fresh, sz, out, &s_acc);
-            } else {
+            if (q == 2) {
                 constexpr uint32_t W = wg_words(8);
-                Small &sm = *reinterpret_cast<Small *>(s_area);
-                wg_run<false>(J, Wg8{sm.tables, s_sel}, W, factorial(8), J.n == 8, sm.bits, sm.bits + W,
-                              sm.bits + 2 * W, list, fresh, sz, out, &s_acc);
+                if (!built) wg8_build(sm.tables);
+                built = true;
+                for (uint32_t i = threadIdx.x; i < 2 * J.k * 8u; i += blockDim.x)
+                    (&sm.sel[0].sel[0])[i] = (&gens[0].sel[0])[i];
+                wg_run(J, Wg8{sm.tables, sm.sel}, W, factorial(8), J.n == 8, sm.bits, sm.bits + W, sm.bits + 2 * W, list,
+                       fresh, sz, out, &s_acc);
+            } else if constexpr (kBig) {
+                uint32_t *bits = reinterpret_cast<uint32_t *>(s_area);
+                if (q == 1) {
+                    constexpr uint32_t W = wg_words(9);
+                    wg_run(J, WgN<9>{gens}, W, factorial(9), true, bits, bits + W, bits + 2 * W, list, fresh, sz, out,
+                           &s_acc);
+                } else {
+                    uint32_t *slot = a.gbits + (uint64_t)blockIdx.x * a.slot_words;
+                    const uint32_t cap = (uint32_t)(a.slot_words - 3 * kWgSlotBits) / (kWgParts * (blockDim.x / kWave));
+                    wg_run_parts(J, WgN<10>{gens}, slot, slot + kWgSlotBits, slot + 2 * kWgSlotBits,
+                                 slot + 3 * kWgSlotBits, cap & ~3u, bits, queue, fresh, sz, out, &s_acc, &s_more);
+                }
             }
             __syncthreads();
         }
@@ -613,7 +810,6 @@ struct WgTables {
     std::vector<WgJobDev> jobs;
     std::vector<GenSel> gsel;
     uint64_t sizes_total = 0;     // layer-size entries of all jobs
-    uint64_t slot_words = 0;      // words per bitmap of a device slot (0: no job needs one)
     uint32_t n10 = 0, n9 = 0;     // jobs of n = 10 (first) and n = 9 (next)
     int n_max = 0;
 };
@@ -672,16 +868,11 @@ WgTables wg_tables(const std::vector<WgItem> &items) {
         T.sizes_total += std::min<uint64_t>((uint64_t)s.max_layers, factorial(s.n));
         // the generators, then their inverses
         for (int g = 0; g < 2 * s.k; ++g) T.gsel.push_back(wg_gensel(s, g < s.k ? g : g - s.k, g >= s.k));
-        if (s.n > (int)kWgLdsN) {
-            T.slot_words = std::max<uint64_t>(T.slot_words, (factorial(s.n) + 31) / 32);
-            ++T.n10;
-        } else if (s.n == 9) {
-            ++T.n9;
-        }
+        T.n10 += s.n > (int)kWgLdsN;
+        T.n9 += s.n == 9;
         T.n_max = std::max(T.n_max, s.n);
     }
     if (T.gsel.empty()) T.gsel.push_back(GenSel{});
-    T.slot_words = (T.slot_words + 63) / 64 * 64;
     return T;
 }
 
@@ -709,33 +900,35 @@ void wg_results(std::vector<WgItem> &items, const WgTables &T, const uint64_t *h
 
 }  // namespace
 
-// Workgroups of the two launches (n = 9; the others): every job its own, at
-// most as many as are resident at once.
+// Workgroups of the two launches: every job its own, at most as many as are
+// resident at once. The one for n <= 8 is there for the CUs that the other
+// leaves free; when it leaves none, it runs those jobs as well, at its end.
 struct WgGrid {
-    uint32_t nine = 0, rest = 0;
+    uint32_t big = 0, small = 0;
 };
 static WgGrid wg_grid(const WgTables &T, int block) {
-    auto fit = [&](auto kernel, uint32_t jobs) {
-        int occ = 0;
-        CG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, block, 0));
-        return (uint32_t)std::min<uint64_t>(jobs, (uint64_t)device_cus() * (uint64_t)std::max(occ, 1));
-    };
+    const uint32_t cus = (uint32_t)device_cus();
+    const uint32_t bigs = T.n10 + T.n9, others = (uint32_t)T.jobs.size() - bigs;
     WgGrid g;
-    if (T.n9) g.nine = fit(wg_growth_kernel<true>, T.n9);
-    const uint32_t others = (uint32_t)T.jobs.size() - T.n9;
-    if (others) g.rest = fit(wg_growth_kernel<false>, others);
+    g.big = std::min(bigs, cus);  // the LDS of a whole CU
+    if (others && g.big < cus) {
+        int occ = 0;
+        CG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, wg_growth_kernel<false>, block, 0));
+        g.small = (uint32_t)std::min<uint64_t>(others, (uint64_t)cus * (uint64_t)std::max(occ, 1));
+    }
     return g;
 }
+constexpr uint64_t kWgSlotWords = 3 * kWgSlotBits + kWgListWords;
 
 uint64_t WgRunner::launch_bytes(const std::vector<WgItem> &items, const WgTuning &t) {
     if (items.empty()) return 0;
     const WgTables T = wg_tables(items);
     const uint32_t nj = (uint32_t)items.size();
-    const uint64_t slots = T.slot_words ? std::min<uint64_t>(wg_grid(T, t.block).rest, T.n10) : 0;
+    const uint64_t slots = std::min(wg_grid(T, t.block).big, T.n10);
     // every buffer as DevBuf rounds it (64 KiB) with its growth slack
     auto r = [](uint64_t b) { return ((uint64_t)(1.5 * (double)b) + (64u << 10) - 1) / (64u << 10) * (64u << 10); };
     return r(sizeof(WgJobDev) * nj) + r(sizeof(GenSel) * T.gsel.size()) + r(sizeof(uint64_t) * T.sizes_total) +
-           r(sizeof(WgOutDev) * nj) + r(256) + r(slots * 3 * T.slot_words * sizeof(uint32_t));
+           r(sizeof(WgOutDev) * nj) + r(256) + r(slots * kWgSlotWords * sizeof(uint32_t));
 }
 
 uint64_t WgRunner::device_bytes() const {
@@ -758,35 +951,33 @@ double WgRunner::run(std::vector<WgItem> &items, const WgTuning &t, double t_sub
     // jobs that need a device slot first: only as many workgroups as there
     // are such jobs own one
     const WgTables T = wg_tables(items);
-    const uint64_t sizes_total = T.sizes_total, slot_words = T.slot_words;
+    const uint64_t sizes_total = T.sizes_total;
     const WgGrid grid = wg_grid(T, t.block);
-    const uint32_t n_slot_blocks = slot_words ? std::min(grid.rest, T.n10) : 0u;
+    const uint32_t n_slot_blocks = std::min(grid.big, T.n10);
 
     jobs_.ensure(sizeof(WgJobDev) * nj, 1.25);
     gsel_.ensure(sizeof(GenSel) * T.gsel.size(), 1.25);
     sizes_.ensure(sizeof(uint64_t) * sizes_total, 1.25);
     outs_.ensure(sizeof(WgOutDev) * nj, 1.25);
     ticket_.ensure(256);
-    if (slot_words) ws_.ensure((size_t)n_slot_blocks * 3 * slot_words * sizeof(uint32_t));
+    if (n_slot_blocks) ws_.ensure((size_t)n_slot_blocks * kWgSlotWords * sizeof(uint32_t));
     CG_HIP(hipMemcpyAsync(jobs_.p, T.jobs.data(), sizeof(WgJobDev) * nj, hipMemcpyHostToDevice, stream_));
     CG_HIP(hipMemcpyAsync(gsel_.p, T.gsel.data(), sizeof(GenSel) * T.gsel.size(), hipMemcpyHostToDevice, stream_));
 
-    uint32_t *gbits = slot_words ? ws_.as<uint32_t>() : nullptr;
+    uint32_t *gbits = n_slot_blocks ? ws_.as<uint32_t>() : nullptr;
     WgLaunch args{jobs_.as<const WgJobDev>(), T.n10, T.n9, nj, n_slot_blocks, gsel_.as<const GenSel>(),
-                  sizes_.as<uint64_t>(), outs_.as<WgOutDev>(), ticket_.as<uint32_t>(), gbits, slot_words};
+                  sizes_.as<uint64_t>(), outs_.as<WgOutDev>(), ticket_.as<uint32_t>(), gbits, kWgSlotWords};
     const std::vector<uint64_t> key = {(uint64_t)(uintptr_t)jobs_.p,   nj,
                                        (uint64_t)(uintptr_t)gsel_.p,   (uint64_t)(uintptr_t)sizes_.p,
                                        (uint64_t)(uintptr_t)outs_.p,   (uint64_t)(uintptr_t)ticket_.p,
-                                       (uint64_t)(uintptr_t)gbits,     slot_words,
+                                       (uint64_t)(uintptr_t)gbits,     (uint64_t)t.block,
                                        T.n10,                          T.n9,
-                                       grid.nine,                      grid.rest,
-                                       (uint64_t)t.block};
+                                       grid.big,                       grid.small};
     auto enqueue = [&]() {
         hipLaunchKernelGGL(clear_u32_kernel, dim3(1), dim3(64), 0, stream_, ticket_.as<uint32_t>(), 3u);
-        if (grid.nine)
-            hipLaunchKernelGGL(wg_growth_kernel<true>, dim3(grid.nine), dim3(t.block), 0, stream_, args);
-        if (grid.rest)
-            hipLaunchKernelGGL(wg_growth_kernel<false>, dim3(grid.rest), dim3(t.block), 0, stream_, args);
+        if (grid.big) hipLaunchKernelGGL(wg_growth_kernel<true>, dim3(grid.big), dim3(t.block), 0, stream_, args);
+        if (grid.small)
+            hipLaunchKernelGGL(wg_growth_kernel<false>, dim3(grid.small), dim3(t.block), 0, stream_, args);
     };
     if (key != graph_key_) {
         // the graph is built node by node (no stream capture): a queue
@@ -814,14 +1005,14 @@ double WgRunner::run(std::vector<WgItem> &items, const WgTuning &t, double t_sub
         bool ok = hipGraphCreate(&graph_, 0) == hipSuccess;
         const hipKernelNodeParams p0 = node(reinterpret_cast<void *>(clear_u32_kernel), 1, 64, clear_args);
         ok = ok && hipGraphAddKernelNode(&n0, graph_, nullptr, 0, &p0) == hipSuccess;
-        if (grid.nine) {
+        if (grid.big) {
             const hipKernelNodeParams p =
-                node(reinterpret_cast<void *>(wg_growth_kernel<true>), grid.nine, t.block, wg_args);
+                node(reinterpret_cast<void *>(wg_growth_kernel<true>), grid.big, t.block, wg_args);
             ok = ok && hipGraphAddKernelNode(&n1, graph_, &n0, 1, &p) == hipSuccess;
         }
-        if (grid.rest) {
+        if (grid.small) {
             const hipKernelNodeParams p =
-                node(reinterpret_cast<void *>(wg_growth_kernel<false>), grid.rest, t.block, wg_args);
+                node(reinterpret_cast<void *>(wg_growth_kernel<false>), grid.small, t.block, wg_args);
             ok = ok && hipGraphAddKernelNode(&n1, graph_, &n0, 1, &p) == hipSuccess;
         }
         ok = ok && hipGraphInstantiate(&exec_, graph_, nullptr, nullptr, 0) == hipSuccess;
@@ -893,8 +1084,9 @@ constexpr size_t kNaOffJobs = na_align(kNaOffOuts + sizeof(WgOutDev) * kNoAllocM
 constexpr size_t kNaOffGsel = na_align(kNaOffJobs + sizeof(WgJobDev) * kNoAllocMaxJobs);
 constexpr size_t kNaOffSizes = na_align(kNaOffGsel + sizeof(GenSel) * 2 * kNoAllocMaxGens);
 constexpr size_t kNaOffSlots = na_align(kNaOffSizes + sizeof(uint64_t) * kNoAllocMaxSizes);
-// one n = 10 slot: three bitmaps of 10!/32 words, rounded up to 64 words
-constexpr size_t kNaSlot10 = 3 * (((factorial(10) + 31) / 32 + 63) / 64 * 64) * sizeof(uint32_t);
+// one n = 10 slot: shorter lists than with memory of its own, for more slots
+constexpr size_t kNaSlotWords = 3 * kWgSlotBits + kWgListWordsNoAlloc;
+constexpr size_t kNaSlot10 = kNaSlotWords * sizeof(uint32_t);
 static_assert(kNaOffSlots + 16 * kNaSlot10 <= kNoAllocScratchBytes, "room for at least 16 slots of n = 10");
 
 constexpr int kNaMaxDevices = 64;
@@ -970,7 +1162,7 @@ void run_batch_noalloc(int n_jobs, const cg_job_t *jobs, cg_result_t *results, h
     WgJobDev *djobs = reinterpret_cast<WgJobDev *>(base + kNaOffJobs);
     GenSel *dgsel = reinterpret_cast<GenSel *>(base + kNaOffGsel);
     uint64_t *dsizes = reinterpret_cast<uint64_t *>(base + kNaOffSizes);
-    uint32_t *gbits = T.slot_words ? reinterpret_cast<uint32_t *>(base + kNaOffSlots) : nullptr;
+    uint32_t *gbits = T.n10 ? reinterpret_cast<uint32_t *>(base + kNaOffSlots) : nullptr;
 
     // the launch shape of cg_growth_batch for the batch's largest n
     const int block = wg_block(T.n_max);
@@ -979,10 +1171,9 @@ void run_batch_noalloc(int n_jobs, const cg_job_t *jobs, cg_result_t *results, h
     // one per job that needs one
     uint32_t n_slot_blocks = 0;
     if (gbits) {
-        const uint64_t slot_bytes = 3 * T.slot_words * sizeof(uint32_t);
-        const uint64_t fit = (kNoAllocScratchBytes - kNaOffSlots) / slot_bytes;
-        n_slot_blocks = (uint32_t)std::min<uint64_t>({fit, (uint64_t)grid.rest, (uint64_t)T.n10});
-        if (n_slot_blocks < 1 || kNaOffSlots + (uint64_t)n_slot_blocks * slot_bytes > kNoAllocScratchBytes)
+        const uint64_t fit = (kNoAllocScratchBytes - kNaOffSlots) / kNaSlot10;
+        n_slot_blocks = (uint32_t)std::min<uint64_t>({fit, (uint64_t)grid.big, (uint64_t)T.n10});
+        if (n_slot_blocks < 1 || kNaOffSlots + (uint64_t)n_slot_blocks * kNaSlot10 > kNoAllocScratchBytes)
             throw Error(CG_E_DEVICE, "no-allocation slot layout");
     }
     CG_HIP(hipMemcpyAsync(djobs, T.jobs.data(), sizeof(WgJobDev) * nj, hipMemcpyHostToDevice, stream));
@@ -991,10 +1182,10 @@ void run_batch_noalloc(int n_jobs, const cg_job_t *jobs, cg_result_t *results, h
     hipLaunchKernelGGL(clear_u32_kernel, dim3(1), dim3(64), 0, stream, ticket, 3u);
     CG_HIP(hipGetLastError());
     const double t_admit = now_seconds();
-    const WgLaunch args{djobs, T.n10, T.n9, nj, n_slot_blocks, dgsel, dsizes, outs, ticket, gbits, T.slot_words};
-    if (grid.nine) hipLaunchKernelGGL(wg_growth_kernel<true>, dim3(grid.nine), dim3(block), 0, stream, args);
+    const WgLaunch args{djobs, T.n10, T.n9, nj, n_slot_blocks, dgsel, dsizes, outs, ticket, gbits, kNaSlotWords};
+    if (grid.big) hipLaunchKernelGGL(wg_growth_kernel<true>, dim3(grid.big), dim3(block), 0, stream, args);
     CG_HIP(hipGetLastError());
-    if (grid.rest) hipLaunchKernelGGL(wg_growth_kernel<false>, dim3(grid.rest), dim3(block), 0, stream, args);
+    if (grid.small) hipLaunchKernelGGL(wg_growth_kernel<false>, dim3(grid.small), dim3(block), 0, stream, args);
     CG_HIP(hipGetLastError());
     std::vector<uint64_t> hsz(T.sizes_total);
     std::vector<WgOutDev> ho(nj);

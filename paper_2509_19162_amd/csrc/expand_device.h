@@ -27,6 +27,16 @@ __device__ __forceinline__ Nibbles split_nibbles(uint64_t key) {
     return r;
 }
 
+// Generator g of a table, the same for a whole wave, by scalar loads.
+__device__ __forceinline__ GenSel uniform_gensel(const GenSel *table, uint32_t g) {
+    const uint32_t __attribute__((address_space(4))) *p =
+        (const uint32_t __attribute__((address_space(4))) *)(uintptr_t)&table[g].sel[0];
+    GenSel v;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v.sel[i] = p[i];
+    return v;
+}
+
 // Key of s.g for the generator whose selectors are `g` (make_gensel).
 __device__ __forceinline__ uint64_t apply_gensel(const Nibbles &s, const GenSel &g) {
     const uint32_t ye0 = __builtin_amdgcn_perm(s.e1, s.e0, g.sel[0]) |

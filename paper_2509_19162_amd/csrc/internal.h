@@ -49,11 +49,13 @@ GenSel make_gensel(int n, const uint8_t *g);
 // layer has neighbours. An unseen state of the next layer stops after about
 // three tests, the others take all k; listing and unranking one costs about
 // four. The next layer is taken to grow 0.7 times as much as the last one.
-__host__ __device__ inline bool pull_is_less(uint64_t unseen, uint64_t F, uint64_t before, uint64_t k) {
+// `weight`: what a test costs, in neighbours.
+__host__ __device__ inline bool pull_is_less(uint64_t unseen, uint64_t F, uint64_t before, uint64_t k,
+                                             double weight = 1.0) {
     const double U = (double)unseen, f = (double)F;
     const double grown = before ? 0.7 * f * f / (double)before : f;
     const double next = grown < U ? grown : U;
-    return 3.0 * next + (double)k * (U - next) + 4.0 * U < f * (double)k;
+    return weight * (3.0 * next + (double)k * (U - next)) + 4.0 * U < f * (double)k;
 }
 
 // ---------------------------------------------------------------------------

@@ -54,17 +54,6 @@ __device__ __forceinline__ uint64_t rb_uniform(uint64_t x) {
     return (uint64_t)hi << 32 | lo;
 }
 
-// Read-only and the same in every lane: through the constant address space,
-// by scalar loads.
-__device__ __forceinline__ GenSel rb_gen(const GenSel *sel, uint32_t g) {
-    const uint32_t __attribute__((address_space(4))) *p =
-        (const uint32_t __attribute__((address_space(4))) *)(uintptr_t)&sel[g].sel[0];
-    GenSel v;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v.sel[i] = p[i];
-    return v;
-}
-
 // ---- bit numbers ---------------------------------------------------------------
 // The scramble spreads the layers (whose ranks crowd: few inversions, common
 // leading entries) evenly over the segments, and the neighbours of one
@@ -163,7 +152,7 @@ __global__ __launch_bounds__(kRbBlock) __attribute__((amdgpu_waves_per_eu(8))) v
 #pragma unroll
             for (int j = 0; j < kRbRows; ++j) {
                 const uint32_t g = q * kRbRows + j < a.k ? q * kRbRows + j : a.k - 1;
-                t[j] = apply_gensel(s, rb_gen(a.sel, g));
+                t[j] = apply_gensel(s, uniform_gensel(a.sel, g));
                 r[j] = RbBits<N>::of_key(t[j]);
                 fresh[j] = in && q * kRbRows + j < a.k;
                 word[j] = fresh[j] ? a.seen[r[j] >> 5] : ~0u;
@@ -246,7 +235,7 @@ __global__ __launch_bounds__(kPartBlock) void rb_part_kernel(const uint64_t *__r
             for (int h = 0; h < kRbPartGens; ++h) {
                 const uint32_t g = p * kRbPartGens + h;
                 if (g < k) pend |= in << (h * kRbPartStates);
-                const GenSel G = rb_gen(sel, g < k ? g : k - 1);
+                const GenSel G = uniform_gensel(sel, g < k ? g : k - 1);
 #pragma unroll
                 for (int j = 0; j < kRbPartStates; ++j) {
                     const uint32_t r = RbBits<N>::of_key(apply_gensel(s[j], G));
@@ -384,7 +373,7 @@ __global__ __launch_bounds__(kRbBlock) __attribute__((amdgpu_waves_per_eu(8))) v
                 key = perm_unrank_t<N>(RbBits<N>::to_rank((w0 << 5) + bit));
                 const Nibbles s = split_nibbles(key);
                 for (uint32_t g = 0; g < a.k && !hit; ++g) {
-                    const uint32_t r = RbBits<N>::of_key(apply_gensel(s, rb_gen(inv, g)));
+                    const uint32_t r = RbBits<N>::of_key(apply_gensel(s, uniform_gensel(inv, g)));
                     hit = (seen[r >> 5] >> (r & 31u)) & 1u;
                 }
                 if (hit) atomicOr(&s_new[bit >> 5], 1u << (bit & 31u));

@@ -48,3 +48,14 @@ def test_batches_mix_the_ranges(oracle_c):
         for got in (api.growth_batch(jobs, max_layers=512), api.growth_batch_noalloc(jobs, max_layers=512)):
             for (n, g), r in zip(jobs, got):
                 assert r.sizes == oracle_c.growth(n, g, max_layers=512)[0]
+
+
+@pytest.mark.parametrize("fam", ["coxeter", "all_transpositions", "reversals"])
+def test_ten_entries_many_rounds(fam):
+    """n = 10 with crowded neighbours (adjacent swaps: most lie in one part of
+    the bitmap) and with many generators (lists fill up within a state)."""
+    gens = I.family(fam, 10)
+    ref = api.growth_ex(10, gens, max_layers=512, packed_sort=True)
+    for r in (api.growth_ex(10, gens, max_layers=512, small_job=True),
+              api.growth_batch_noalloc([(10, gens)], max_layers=512)[0]):
+        assert r.sizes == ref.sizes and r.status == ref.status
