@@ -78,8 +78,11 @@ extern "C" {
                                     section on growth benchmarks). n <= 14,
                                     start state a permutation, no layer
                                     export; n! * 3/8 bytes of device memory
-                                    (32.7 GB at n = 14). Exact; directed
-                                    sets allowed with CG_ALLOW_DIRECTED.     */
+                                    (32.7 GB at n = 14), and for n = 11..13
+                                    lists of a large layer's neighbours where
+                                    they fit (1.5 GB at n = 13). Exact;
+                                    directed sets allowed with
+                                    CG_ALLOW_DIRECTED.                       */
 #define CG_SMALL_JOB 0x40u       /* run the whole job inside one workgroup
                                     (n <= 10, start a permutation, no layer
                                     export): one launch, rank-space bitmaps

@@ -93,6 +93,8 @@ void *noalloc_scratch(int dev);
 // The bitmask engine: whole-device growth of one job (n <= 14, start a
 // permutation). Fills res like Engine::run. Layers are not exported.
 void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s);
+// Device bytes it may take beyond its bitmaps (lists of neighbours).
+uint64_t bitmask_list_bytes(const JobSpec &spec);
 
 // Why a job cannot use the bitmask engine ("" when it can).
 std::string bitmask_unsupported(const JobSpec &spec);

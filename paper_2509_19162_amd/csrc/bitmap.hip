@@ -16,6 +16,7 @@
 #include "device_util.h"
 #include "expand_device.h"
 #include "internal.h"
+#include "partition_device.h"
 #include "perm_rank.h"
 
 // Device memory of cg_growth_batch_noalloc: every buffer its launch needs
@@ -600,9 +601,11 @@ __global__ __launch_bounds__(kBmBlock) void bm_expand_kernel(const uint32_t *__r
                                                              const uint32_t *__restrict__ scur,
                                                              const uint32_t *__restrict__ vis, uint32_t *nxt,
                                                              uint32_t *snxt, uint64_t W, uint64_t nchunks,
-                                                             const GenSel *__restrict__ gsel, int k) {
+                                                             const GenSel *__restrict__ gsel, int k,
+                                                             const uint32_t *go) {
     using R = RankOf<N>;
     __shared__ GenSel s_sel[kBitmapMaxK];
+    if (go && !*go) return;  // the lists held everything
     for (int i = threadIdx.x; i < k * 8; i += kBmBlock) (&s_sel[0].sel[0])[i] = (&gsel[0].sel[0])[i];
     __syncthreads();
     for (uint64_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
@@ -630,6 +633,226 @@ __global__ __launch_bounds__(kBmBlock) void bm_expand_kernel(const uint32_t *__r
         }
     }
 }
+
+// ---- large layers through lists --------------------------------------------------
+// A test at a random address of the bitmaps costs 19 ps of the whole chip's
+// time (53 G/s), the atomic of a new state 37. For n = 11..13 a large layer
+// goes through lists instead: a piece of its neighbours is split by segment
+// of the bitmap (bm_part_kernel: 512 digits, each the segments digit,
+// digit + 512, ..., so that crowded ranks spread), then a workgroup per
+// segment ORs its words into LDS, takes away what was seen and adds the rest
+// to the next layer (bm_apply_kernel). The workgroups of one digit run side
+// by side on one XCD: its words, read by each of them, come from that L2.
+// States next to each other share their first entries, and so do their
+// neighbours under one generator: hundreds of words of one digit at a time,
+// so the workgroups share the digits' parts (with parts of their own, of
+// 2000 words, one in ten overran).
+// OR may be repeated, so a piece whose lists overran goes through
+// bm_expand_kernel as if nothing had happened.
+// S_13 by two random generators and their inverses: 617 -> 260 ms, of which
+// the split takes 60% (8.9 ps a neighbour: ranks, ring slots and barriers)
+// and the ORs 30% (4.4).
+constexpr uint32_t kBmLgDigits = 9;
+constexpr uint32_t kBmPartBlocks = 256;
+constexpr uint32_t kBmSets = 2;  // cursors of a digit: workgroups take turns
+constexpr uint32_t kBmCursors = (kBmSets * PartShared<uint32_t>::kStep) << kBmLgDigits;
+template <int N>
+struct BmSeg {
+    static constexpr uint32_t kLg = N >= 12 ? 20 : 17;  // bits of a segment
+    static constexpr uint32_t kSegs = (uint32_t)((factorial(N) + (1ull << kLg) - 1) >> kLg);
+    static constexpr uint32_t kSubs = (kSegs + (1u << kBmLgDigits) - 1) >> kBmLgDigits;  // per digit
+    static_assert((uint64_t)kSubs << kLg <= 1ull << 32, "words of 32 bits");
+};
+constexpr uint32_t kBmSpan = 4, kBmTake = 2 * kWave;  // words listed at a time; states a wave takes
+
+// Piece `piece` of `pieces` of the layer: every pieces-th block of 64 words.
+// A round forms eight neighbours per thread, of two states and four
+// generators; a wave queues states so that its rounds are full.
+template <int N>
+__global__ __launch_bounds__(kPartBlock) void bm_part_kernel(const uint32_t *__restrict__ cur, uint64_t W,
+                                                             uint32_t piece, uint32_t pieces,
+                                                             const GenSel *__restrict__ sel, uint32_t k,
+                                                             PartShared<uint32_t> o) {
+    using R = RankOf<N>;
+    constexpr uint32_t kWaves = kPartBlock / kWave, kLg = BmSeg<N>::kLg, kSpans = kWave / kBmSpan;
+    constexpr uint32_t kQueue = kBmTake + kBmSpan * 32;
+    __shared__ PartLds<uint32_t> L;
+    __shared__ uint32_t s_queue[kWaves][kQueue];
+    __shared__ uint32_t s_any[2];
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    uint32_t *const queue = s_queue[wave];
+    if (threadIdx.x < 2) s_any[threadIdx.x] = 0;
+    part_begin(L, 1u << kBmLgDigits);
+    o.base += (uint64_t)(blockIdx.x / 8u % kBmSets) * o.cap;
+    o.cursor += (blockIdx.x / 8u % kBmSets) * (kBmCursors / kBmSets);
+    // block of 64 words number i of this wave
+    const uint32_t id = blockIdx.x * kWaves + wave, stride = gridDim.x * kWaves;
+    auto word_of = [&](uint32_t i) { return ((uint64_t)((uint64_t)i * stride + id) * pieces + piece) * kWave; };
+    uint32_t parity = 0, turn = 0, i = 0, span = kSpans, held = 0, x = 0;
+    uint64_t some = 0;
+    for (;;) {
+        while (held < kBmTake) {
+            if (span == kSpans) {
+                const uint64_t w0 = word_of(i);
+                if (w0 >= W) break;
+                x = w0 + lane < W ? cur[w0 + lane] : 0u;
+                some = __ballot(x != 0);
+                span = 0;
+                ++i;
+                continue;
+            }
+            if ((some >> (kBmSpan * span)) & ((1u << kBmSpan) - 1u)) {
+                // two bits of a word per lane
+                const uint32_t from = span * kBmSpan + lane / 16u;
+                const uint32_t y = __shfl(x, (int)from, kWave) >> (2u * (lane & 15u));
+                const uint32_t r0 = ((i - 1) * kWave + from) * 32u + 2u * (lane & 15u);
+#pragma unroll
+                for (uint32_t b = 0; b < 2; ++b) {
+                    const bool on = (y >> b) & 1u;
+                    const uint64_t m = __ballot(on);
+                    if (on) queue[held + mask_rank(m)] = r0 + b;
+                    held += (uint32_t)__popcll(m);
+                }
+                wg_wave_sync();
+            }
+            ++span;
+        }
+        if (held && lane == 0) s_any[turn] = 1;
+        __syncthreads();
+        if (!s_any[turn]) break;
+        turn ^= 1u;
+        if (threadIdx.x == 0) s_any[turn] = 0;  // read before the last barrier
+        const uint32_t take = held < kBmTake ? held : kBmTake;
+        held -= take;
+        Nibbles s[2];
+        uint32_t in = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < 2; ++j) {
+            const uint32_t at = j * kWave + lane;
+            const bool on = at < take;
+            const uint32_t e = queue[on ? held + at : 0];
+            const uint64_t r = on ? word_of(e >> 11) * 32u + (e & 2047u) : 0ull;
+            s[j] = split_nibbles(perm_unrank_t<N, R>((R)r));
+            if (on) in |= 1u << j;
+        }
+        for (uint32_t g0 = 0; g0 < k; g0 += 4) {
+            uint32_t v[8], dig[8], pend = 0;
+#pragma unroll
+            for (uint32_t h = 0; h < 4; ++h) {
+                const uint32_t g = g0 + h < k ? g0 + h : k - 1;
+                if (g0 + h < k) pend |= in << (2 * h);
+                const GenSel G = uniform_gensel(sel, g);
+#pragma unroll
+                for (uint32_t j = 0; j < 2; ++j) {
+                    const R q = perm_rank_t<N, R>(apply_gensel(s[j], G));
+                    const uint32_t seg = (uint32_t)(q >> kLg);
+                    dig[2 * h + j] = seg & ((1u << kBmLgDigits) - 1u);
+                    v[2 * h + j] = (seg >> kBmLgDigits) << kLg | ((uint32_t)q & ((1u << kLg) - 1u));
+                }
+            }
+            part_round(L, v, dig, pend, kBmLgDigits, o, parity);
+        }
+    }
+    part_end(L, kBmLgDigits, o);
+}
+
+template <int N>
+__global__ __launch_bounds__(kPartBlock) void bm_apply_kernel(const uint32_t *__restrict__ in,
+                                                              const uint32_t *__restrict__ cursor, uint32_t cap,
+                                                              const uint32_t *__restrict__ vis,
+                                                              uint32_t *__restrict__ nxt, uint32_t *snxt, uint64_t W,
+                                                              uint32_t *overrun) {
+    constexpr uint32_t kLg = BmSeg<N>::kLg, kSubs = BmSeg<N>::kSubs, kWords = 1u << (kLg - 5);
+    constexpr uint32_t kRows = 4;  // loads of a lane under way
+    static_assert(kWords % kChunkWords == 0 && kChunkWords % 256 == 0, "whole summary bits, a wave in one");
+    __shared__ __align__(16) uint32_t s_bits[kWords];
+    __shared__ uint32_t s_sum;
+    // blocks go to the XCDs in turn
+    const uint32_t xcd = blockIdx.x % 8u, at = blockIdx.x / 8u;
+    const uint32_t digit = at / kSubs * 8u + xcd, sub = at % kSubs, seg = sub << kBmLgDigits | digit;
+    if (seg >= BmSeg<N>::kSegs) return;
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
+    uint4 *const bits4 = reinterpret_cast<uint4 *>(s_bits);
+    for (uint32_t w = tid; w < kWords / 4; w += kPartBlock) bits4[w] = make_uint4(0, 0, 0, 0);
+    if (tid == 0) s_sum = 0;
+    __syncthreads();
+    for (uint32_t set = 0; set < kBmSets; ++set) {
+        const uint32_t given = cursor[set * (kBmCursors / kBmSets) + digit * PartShared<uint32_t>::kStep];
+        const uint32_t n = min(given, cap) / 4;
+        if (given > cap && tid == 0) *overrun = 1;
+        const uint4 *const p = reinterpret_cast<const uint4 *>(in + ((uint64_t)digit * kBmSets + set) * cap);
+        for (uint32_t b = tid; b < n; b += kRows * kPartBlock) {
+            uint4 q[kRows];
+#pragma unroll
+            for (uint32_t j = 0; j < kRows; ++j)
+                q[j] = b + j * kPartBlock < n ? p[b + j * kPartBlock] : make_uint4(~0u, ~0u, ~0u, ~0u);
+#pragma unroll
+            for (uint32_t j = 0; j < kRows; ++j) {
+                const uint32_t x[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
+#pragma unroll
+                for (uint32_t u = 0; u < 4; ++u)
+                    if (x[u] >> kLg == sub) {  // not of a place that holds no word
+                        const uint32_t y = x[u] & ((1u << kLg) - 1u);
+                        atomicOr(&s_bits[y >> 5], 1u << (y & 31u));
+                    }
+            }
+        }
+    }
+    __syncthreads();
+    const uint64_t w0 = (uint64_t)seg * kWords;
+    const uint32_t n4 = (uint32_t)(min((uint64_t)kWords, W - w0) / 4);
+    static_assert(factorial(N) % 128 == 0, "bitmaps of whole uint4");
+    const uint4 *const v4 = reinterpret_cast<const uint4 *>(vis + w0);
+    uint4 *const x4 = reinterpret_cast<uint4 *>(nxt + w0);
+    for (uint32_t i = tid; i < kWords / 4; i += kPartBlock) {
+        const uint4 f = bits4[i];
+        bool some = false;
+        if (i < n4 && (f.x | f.y | f.z | f.w)) {
+            const uint4 v = v4[i], x = x4[i];
+            const uint4 y = make_uint4(x.x | (f.x & ~v.x), x.y | (f.y & ~v.y), x.z | (f.z & ~v.z), x.w | (f.w & ~v.w));
+            some = y.x != x.x || y.y != x.y || y.z != x.z || y.w != x.w;
+            if (some) x4[i] = y;
+        }
+        if (__ballot(some) && lane == 0) atomicOr(&s_sum, 1u << (4 * i / kChunkWords));
+    }
+    __syncthreads();
+    const uint64_t c = w0 / kChunkWords;
+    if (tid == 0 && s_sum) atomicOr(&snxt[c >> 5], s_sum << (uint32_t)(c & 31u));
+}
+
+// Lists of a layer step: `pieces` launches of at most `per_piece` neighbours.
+struct BmLists {
+    uint64_t per_piece = 0;  // 0: n has none
+    uint32_t cap = 0;        // words of a part (one of kBmSets) of a digit
+    uint64_t words() const { return (uint64_t)kBmSets * cap << kBmLgDigits; }
+};
+BmLists bm_lists(int n, uint32_t k) {
+    BmLists l;
+    auto set = [&](auto NN) {
+        constexpr int N = decltype(NN)::value;
+        // about a sixteenth of the states, 1 GiB of words at most
+        l.per_piece = std::min<uint64_t>(1ull << 28, std::max<uint64_t>(1ull << 24, factorial(N) / 16));
+        const double share = (double)BmSeg<N>::kSubs / (double)BmSeg<N>::kSegs;  // of the fullest digit
+        // (workgroups end a part in the middle of a line)
+        l.cap = part_cap(1.3 * (double)l.per_piece * share / kBmSets + 32.0 * kBmPartBlocks / kBmSets, k);
+    };
+    if (n == 11) set(std::integral_constant<int, 11>{});
+    if (n == 12) set(std::integral_constant<int, 12>{});
+    if (n == 13) set(std::integral_constant<int, 13>{});
+    return l;
+}
+template <class F>
+void with_bm_lists_n(int n, F &&f) {
+    switch (n) {
+        case 11: f(std::integral_constant<int, 11>{}); break;
+        case 12: f(std::integral_constant<int, 12>{}); break;
+        default: f(std::integral_constant<int, 13>{}); break;
+    }
+}
+// From this many neighbours on a layer goes through lists: below, clearing
+// and writing back every segment (0.3 ms at n = 13) is more than the tests.
+constexpr uint64_t kBmListsMin = 1ull << 23;
 
 // The step from the other side, late in a growth: every unseen state looks
 // for a seen predecessor (its images under the inverse generators) and is in
@@ -736,7 +959,7 @@ __global__ void bm_seed_kernel(uint32_t *vis, uint32_t *cur, uint32_t *scur, uin
     cur[w] = m;
     const uint64_t c = w / kChunkWords;
     scur[c >> 5] = 1u << (uint32_t)(c & 31u);
-    *count = 0;
+    count[0] = count[1] = 0;  // and the lists' flag
 }
 
 __global__ void bm_clear_kernel(uint32_t *a, uint64_t na, unsigned long long *count) {
@@ -1209,6 +1432,13 @@ std::string bitmask_unsupported(const JobSpec &spec) {
     return "";
 }
 
+uint64_t bitmask_list_bytes(const JobSpec &spec) {
+    const uint64_t k = (uint64_t)spec.k;
+    if (spec.max_frontier && spec.max_frontier < kBmListsMin / std::max<uint64_t>(1, k)) return 0;
+    const BmLists l = bm_lists(spec.n, spec.k);
+    return l.per_piece ? (l.words() + kBmCursors) * sizeof(uint32_t) : 0;
+}
+
 void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     const std::string why = bitmask_unsupported(spec);
     if (!why.empty()) throw Error(CG_E_INVAL, why);
@@ -1227,8 +1457,8 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     const uint64_t W = (S + 31) / 32;
     const uint64_t nchunks = (W + kChunkWords - 1) / kChunkWords;
     const uint64_t sw = (nchunks + 31) / 32;
-    DevBuf vis, cur, nxt, scur, snxt, gsel, cnt;
-    for (DevBuf *b : {&vis, &cur, &nxt, &scur, &snxt, &gsel, &cnt}) b->stream = s;
+    DevBuf vis, cur, nxt, scur, snxt, gsel, cnt, lists, list_cnt;
+    for (DevBuf *b : {&vis, &cur, &nxt, &scur, &snxt, &gsel, &cnt, &lists, &list_cnt}) b->stream = s;
     vis.ensure(W * 4);
     cur.ensure(W * 4);
     nxt.ensure(W * 4);
@@ -1262,7 +1492,7 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     CG_HIP(hipEventRecord(e0, s));
     const uint32_t grid = (uint32_t)std::min<uint64_t>(nchunks, (uint64_t)device_cus() * 16);
     uint64_t *host_cnt = nullptr;
-    CG_HIP(hipHostMalloc((void **)&host_cnt, sizeof(uint64_t), hipHostMallocDefault));
+    CG_HIP(hipHostMalloc((void **)&host_cnt, 2 * sizeof(uint64_t), hipHostMallocDefault));
     uint32_t *pc = cur.as<uint32_t>(), *pn = nxt.as<uint32_t>(), *sc = scur.as<uint32_t>(),
              *sn = snxt.as<uint32_t>();
     uint64_t F = 1, before = 0, seen = 1;
@@ -1270,6 +1500,23 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     // every step from the unseen side goes over the whole bitmap: not for
     // layers whose neighbours are fewer than its words
     const uint32_t grid_all = (uint32_t)std::min<uint64_t>((W + 63) / 64, (uint64_t)device_cus() * 32);
+    BmLists L = bm_lists(n, (uint32_t)k);
+    uint64_t lists_from = kBmListsMin;
+    // the lists are there from the first large layer on, if memory allows
+    auto room_for_lists = [&]() {
+        if (!lists.p) {
+            try {
+                lists.ensure(L.words() * 4);
+                list_cnt.ensure(kBmCursors * sizeof(uint32_t));
+            } catch (const Error &e) {
+                if (e.code != CG_E_NOMEM) throw;
+                lists.release();
+                L.per_piece = 0;
+                return false;
+            }
+        }
+        return true;
+    };
     try {
         for (;;) {
             if (k == 0) break;
@@ -1281,7 +1528,31 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
                 status = CG_TRUNCATED;
                 break;
             }
-            const bool pull = F * (uint64_t)k >= W && pull_is_less(S - seen, F, before, (uint64_t)k);
+            const bool large = L.per_piece && F * (uint64_t)k >= lists_from;
+            // (a test costs two and a half neighbours that go through lists)
+            const bool pull =
+                F * (uint64_t)k >= W && pull_is_less(S - seen, F, before, (uint64_t)k, large ? 2.5 : 1.0);
+            bool by_lists = large && !pull && room_for_lists();
+            if (by_lists) {
+                const uint32_t pieces = (uint32_t)((F * (uint64_t)k + L.per_piece - 1) / L.per_piece);
+                uint32_t *const flag = cnt.as<uint32_t>() + 2;  // after the layer's count
+                const PartShared<uint32_t> o{lists.as<uint32_t>(), (uint64_t)kBmSets * L.cap, L.cap,
+                                             list_cnt.as<uint32_t>()};
+                with_bm_lists_n(n, [&](auto NN) {
+                    constexpr int N = decltype(NN)::value;
+                    for (uint32_t p = 0; p < pieces; ++p) {
+                        hipLaunchKernelGGL(bm_clear_kernel, dim3(kBmCursors / 256), dim3(256), 0, s,
+                                           list_cnt.as<uint32_t>(), (uint64_t)kBmCursors,
+                                           (unsigned long long *)nullptr);
+                        hipLaunchKernelGGL(bm_part_kernel<N>, dim3(kBmPartBlocks), dim3(kPartBlock), 0, s, pc, W, p,
+                                           pieces, gsel.as<const GenSel>(), (uint32_t)k, o);
+                        hipLaunchKernelGGL(bm_apply_kernel<N>, dim3(BmSeg<N>::kSubs << kBmLgDigits), dim3(kPartBlock),
+                                           0, s, lists.as<const uint32_t>(), list_cnt.as<const uint32_t>(), L.cap,
+                                           vis.as<const uint32_t>(), pn, sn, W, flag);
+                    }
+                });
+                CG_HIP(hipGetLastError());
+            }
             with_bm_n(n, [&](auto NN) {
                 if (pull)
                     hipLaunchKernelGGL(bm_pull_kernel<decltype(NN)::value>, dim3(grid_all), dim3(kBmBlock), 0, s,
@@ -1289,7 +1560,7 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
                 else
                     hipLaunchKernelGGL(bm_expand_kernel<decltype(NN)::value>, dim3(grid), dim3(kBmBlock), 0, s,
                                        pc, sc, vis.as<const uint32_t>(), pn, sn, W, nchunks, gsel.as<const GenSel>(),
-                                       k);
+                                       k, by_lists ? cnt.as<const uint32_t>() + 2 : (const uint32_t *)nullptr);
             });
             CG_HIP(hipGetLastError());
             hipLaunchKernelGGL(bm_fold_kernel, dim3(grid), dim3(kBmBlock), 0, s, vis.as<uint32_t>(), pc, sc, pn, sn,
@@ -1299,11 +1570,14 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
             hipLaunchKernelGGL(bm_clear_kernel, dim3((uint32_t)std::min<uint64_t>((sw + 255) / 256, 4096)),
                                dim3(256), 0, s, sc, sw, (unsigned long long *)nullptr);
             CG_HIP(hipGetLastError());
-            CG_HIP(hipMemcpyAsync(host_cnt, cnt.p, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-            hipLaunchKernelGGL(bm_clear_kernel, dim3(1), dim3(64), 0, s, (uint32_t *)nullptr, 0ull,
+            CG_HIP(hipMemcpyAsync(host_cnt, cnt.p, 2 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+            hipLaunchKernelGGL(bm_clear_kernel, dim3(1), dim3(64), 0, s, cnt.as<uint32_t>() + 2, 1ull,
                                cnt.as<unsigned long long>());
             CG_HIP(hipStreamSynchronize(s));
-            const uint64_t N = *host_cnt;
+            const uint64_t N = host_cnt[0];
+            // an orbit in few segments overruns every time: wait for layers
+            // four times as large
+            if (by_lists && (uint32_t)host_cnt[1]) lists_from = 4 * F * (uint64_t)k;
             res->states_expanded += F;
             res->candidates += F * (uint64_t)k;
             std::swap(pc, pn);
@@ -1328,7 +1602,7 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     (void)hipHostFree(host_cnt);
-    for (DevBuf *b : {&vis, &cur, &nxt, &scur, &snxt, &gsel, &cnt}) b->release();
+    for (DevBuf *b : {&vis, &cur, &nxt, &scur, &snxt, &gsel, &cnt, &lists, &list_cnt}) b->release();
     res->device_ms = ms;
     res->status = status;
     res->num_layers = layers;

@@ -51,6 +51,23 @@ struct PartOut {
     uint32_t count_stride;
     uint32_t *flags;    // gets `flag` when a part overran
     uint32_t flag;
+    // where `keys` more of digit d go, of which `head` were written so far
+    __device__ __forceinline__ uint32_t place(uint32_t, uint32_t head, uint32_t) const { return head; }
+};
+
+// Parts that several workgroups fill, a line at a time: for keys that come
+// in lumps (many of one digit to one workgroup), which even out over the
+// workgroups only. Unused places of a workgroup's last line hold all ones.
+template <class K>
+struct PartShared {
+    K *base;            // digit d's part: base + d * stride, cap keys (a multiple of 32)
+    uint64_t stride;
+    uint32_t cap;
+    uint32_t *cursor;   // cursor[d * kStep]: places given away (past cap: overrun)
+    static constexpr uint32_t kStep = 16;  // a line of memory each
+    __device__ __forceinline__ uint32_t place(uint32_t d, uint32_t, uint32_t keys) const {
+        return atomicAdd(&cursor[d * kStep], keys);
+    }
 };
 
 template <class K>
@@ -62,9 +79,9 @@ __device__ __forceinline__ void part_begin(PartLds<K> &L, uint32_t digits) {
 
 // One round: key[r] of digit dig[r] (below 2^lg) for the set bits r of
 // `pend`. Every thread of the block calls it the same number of times.
-template <class K, int R>
+template <class K, int R, class Out>
 __device__ __forceinline__ void part_round(PartLds<K> &L, const K (&key)[R], const uint32_t (&dig)[R], uint32_t pend,
-                                           uint32_t lg, const PartOut<K> &o, uint32_t &parity) {
+                                           uint32_t lg, const Out &o, uint32_t &parity) {
     const uint32_t lg_depth = PartLds<K>::kLgBuf - lg, depth = 1u << lg_depth, lg_line = PartLds<K>::lg_line(lg);
     const uint32_t tid = threadIdx.x, sub = tid & ((1u << lg_line) - 1), grp = tid >> lg_line;
     for (;;) {
@@ -91,10 +108,11 @@ __device__ __forceinline__ void part_round(PartLds<K> &L, const K (&key)[R], con
             const uint32_t n = have >> lg_line;
             if (n) {
                 const uint32_t first = atomicAdd(&L.lines[parity], n);
+                const uint32_t to = o.place(d, head, n << lg_line);
                 for (uint32_t l = 0; l < n; ++l) {
-                    const uint32_t at = head + (l << lg_line);
-                    L.line[first + l] = (uint16_t)((d << lg_depth) + (at & (depth - 1)));
-                    L.at[first + l] = at;
+                    const uint32_t at = l << lg_line;
+                    L.line[first + l] = (uint16_t)((d << lg_depth) + ((head + at) & (depth - 1)));
+                    L.at[first + l] = to + at;
                     L.dig[first + l] = (uint16_t)d;
                 }
                 L.head[d] = head + (n << lg_line);
@@ -128,6 +146,24 @@ __device__ __forceinline__ void part_end(PartLds<K> &L, uint32_t lg, const PartO
             o.count[(uint64_t)d * o.count_stride] = t < o.cap ? t : o.cap;
             if (t > o.cap) atomicOr(o.flags, o.flag);
         }
+    }
+}
+
+// Shared parts: the keys still in the rings, as a line each.
+template <class K>
+__device__ __forceinline__ void part_end(PartLds<K> &L, uint32_t lg, const PartShared<K> &o) {
+    const uint32_t lg_depth = PartLds<K>::kLgBuf - lg, depth = 1u << lg_depth;
+    const uint32_t lg_line = PartLds<K>::lg_line(lg), line = 1u << lg_line;
+    for (uint32_t d = threadIdx.x; d < (1u << lg); d += kPartBlock)
+        if (L.tail[d] != L.head[d]) L.at[d] = o.place(d, 0, line);
+    __syncthreads();
+    const uint32_t sub = threadIdx.x & (line - 1), grp = threadIdx.x >> lg_line;
+    for (uint32_t d = grp; d < (1u << lg); d += kPartBlock >> lg_line) {
+        const uint32_t from = L.head[d] + sub, t = L.tail[d];
+        if (t == L.head[d]) continue;
+        const uint32_t to = L.at[d];
+        if (to < o.cap)
+            o.base[(uint64_t)d * o.stride + to + sub] = from < t ? L.buf[(d << lg_depth) + (from & (depth - 1))] : (K)~(K)0;
     }
 }
 

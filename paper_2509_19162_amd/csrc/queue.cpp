@@ -60,13 +60,14 @@ uint64_t factorial_u64(int n) {
 // states and an expanded one at most min(orbit, max_frontier), so the
 // candidates of one step are at most k * F. Buffers may grow with 50%
 // slack; 64 MiB covers the fixed ones. Bitmask engine: its three bitmaps
-// and their summaries, exactly.
+// and their summaries, and the lists of its large layers.
 uint64_t job_bound(const JobSpec &s) {
     const double k = (double)std::max(1, s.k);
     const double orbit = (double)s.orbit_bound;
     if (s.flags & CG_BITMASK) {
         const double words = std::ceil((double)factorial_u64(s.n) / 32.0);
-        return (uint64_t)(12.0 * words + 8.0 * std::ceil(words / 1024.0 / 32.0)) + (64ull << 20);
+        return (uint64_t)(12.0 * words + 8.0 * std::ceil(words / 1024.0 / 32.0)) + bitmask_list_bytes(s) +
+               (64ull << 20);
     }
     double F = orbit;
     if (s.max_frontier) F = std::min(F, (double)s.max_frontier);

@@ -1,4 +1,5 @@
-"""The bitmask engine's step from the side of the unseen states: sizes against
+"""The bitmask engine's large layers (through lists of neighbours split by
+segment, n = 11..13) and its step from the side of the unseen states: sizes against
 the CPU oracle, the default engine and the closed form of the bubble-sort
 growth (Mahonian numbers). Bitmaps whose last word is whole (n >= 8) and not,
 directed sets, starts, and sets that reach a part of S_n only (the unseen
@@ -38,3 +39,14 @@ def test_mahonian_12():
     for m in range(2, 13):
         row = [sum(row[max(0, j - m + 1) : j + 1]) for j in range(len(row) + m - 1)]
     assert api.growth_ex(12, I.family("coxeter", 12), max_layers=512, bitmask=True).sizes == row
+
+
+@pytest.mark.parametrize("n,m", [(12, 4), (13, 4), (13, 8)])
+def test_orbit_in_few_segments(n, m):
+    """Generators that fix the first entries: the orbit is a small range of
+    ranks, its lists overrun and the layer is expanded directly."""
+    small = I.random_perms_with_inverses(11, m // 2, I.rng_for(11, seed=71 + m))
+    gens = [list(range(n - 11)) + [n - 11 + int(x) for x in g] for g in small]
+    exp = api.growth_ex(11, small, max_layers=512)
+    got = api.growth_ex(n, gens, max_layers=512, bitmask=True)
+    assert (got.sizes, got.states_expanded, got.candidates) == (exp.sizes, exp.states_expanded, exp.candidates)
