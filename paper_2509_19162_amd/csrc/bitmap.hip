@@ -158,7 +158,7 @@ struct WgN {
     using State = Nibbles;
     __device__ __forceinline__ State unrank(uint32_t r) const { return split_nibbles(perm_unrank_t<N>(r)); }
     __device__ __forceinline__ uint32_t neighbour(const State &s, uint32_t g) const {
-        return perm_rank_t<N>(apply_gensel(s, uniform_gensel(sel, g)));
+        return nibbles_rank_t<N>(apply_gensel_nibbles(s, uniform_gensel(sel, g)));
     }
 };
 
@@ -618,7 +618,7 @@ __global__ __launch_bounds__(kBmBlock) void bm_expand_kernel(const uint32_t *__r
                 bits &= bits - 1u;
                 const Nibbles s = split_nibbles(perm_unrank_t<N, R>((R)(w * 32u + b)));
                 for (int g = 0; g < k; ++g) {
-                    const uint64_t q = (uint64_t)perm_rank_t<N, R>(apply_gensel(s, s_sel[g]));
+                    const uint64_t q = (uint64_t)nibbles_rank_t<N, R>(apply_gensel_nibbles(s, s_sel[g]));
                     const uint64_t qw = q >> 5;
                     const uint32_t m = 1u << (uint32_t)(q & 31u);
                     if (vis[qw] & m) continue;
@@ -745,7 +745,7 @@ __global__ __launch_bounds__(kPartBlock) void bm_part_kernel(const uint32_t *__r
                 const GenSel G = uniform_gensel(sel, g);
 #pragma unroll
                 for (uint32_t j = 0; j < 2; ++j) {
-                    const R q = perm_rank_t<N, R>(apply_gensel(s[j], G));
+                    const R q = nibbles_rank_t<N, R>(apply_gensel_nibbles(s[j], G));
                     const uint32_t seg = (uint32_t)(q >> kLg);
                     dig[2 * h + j] = seg & ((1u << kBmLgDigits) - 1u);
                     v[2 * h + j] = (seg >> kBmLgDigits) << kLg | ((uint32_t)q & ((1u << kLg) - 1u));
@@ -900,7 +900,7 @@ __global__ __launch_bounds__(kBmBlock) void bm_pull_kernel(const uint32_t *__res
             if ((uint64_t)r >= factorial(N)) continue;  // past the last rank, in the last word
             const Nibbles s = split_nibbles(perm_unrank_t<N, R>(r));
             for (int g = 0; g < k; ++g) {
-                const uint64_t q = (uint64_t)perm_rank_t<N, R>(apply_gensel(s, s_sel[g]));
+                const uint64_t q = (uint64_t)nibbles_rank_t<N, R>(apply_gensel_nibbles(s, s_sel[g]));
                 if ((vis[q >> 5] >> (uint32_t)(q & 31u)) & 1u) {
                     atomicOr(&fresh[bit >> 5], 1u << (bit & 31u));
                     break;

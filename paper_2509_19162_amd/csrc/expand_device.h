@@ -8,6 +8,7 @@
 #include <cstdint>
 
 #include "internal.h"
+#include "perm_rank.h"
 
 namespace cg {
 
@@ -37,23 +38,36 @@ __device__ __forceinline__ GenSel uniform_gensel(const GenSel *table, uint32_t g
     return v;
 }
 
-// Key of s.g for the generator whose selectors are `g` (make_gensel).
+// s.g for the generator whose selectors are `g` (make_gensel).
+__device__ __forceinline__ Nibbles apply_gensel_nibbles(const Nibbles &s, const GenSel &g) {
+    Nibbles y;
+    y.e0 = __builtin_amdgcn_perm(s.e1, s.e0, g.sel[0]) | __builtin_amdgcn_perm(s.o1, s.o0, g.sel[1]);
+    y.e1 = __builtin_amdgcn_perm(s.e1, s.e0, g.sel[2]) | __builtin_amdgcn_perm(s.o1, s.o0, g.sel[3]);
+    y.o0 = __builtin_amdgcn_perm(s.e1, s.e0, g.sel[4]) | __builtin_amdgcn_perm(s.o1, s.o0, g.sel[5]);
+    y.o1 = __builtin_amdgcn_perm(s.e1, s.e0, g.sel[6]) | __builtin_amdgcn_perm(s.o1, s.o0, g.sel[7]);
+    return y;
+}
+__device__ __forceinline__ uint64_t join_nibbles(const Nibbles &y) {
+    return (uint64_t)(y.e1 | (y.o1 << 4)) << 32 | (y.e0 | (y.o0 << 4));
+}
+
+// Key of s.g.
 __device__ __forceinline__ uint64_t apply_gensel(const Nibbles &s, const GenSel &g) {
-    const uint32_t ye0 = __builtin_amdgcn_perm(s.e1, s.e0, g.sel[0]) |
-                         __builtin_amdgcn_perm(s.o1, s.o0, g.sel[1]);
-    const uint32_t ye1 = __builtin_amdgcn_perm(s.e1, s.e0, g.sel[2]) |
-                         __builtin_amdgcn_perm(s.o1, s.o0, g.sel[3]);
-    const uint32_t yo0 = __builtin_amdgcn_perm(s.e1, s.e0, g.sel[4]) |
-                         __builtin_amdgcn_perm(s.o1, s.o0, g.sel[5]);
-    const uint32_t yo1 = __builtin_amdgcn_perm(s.e1, s.e0, g.sel[6]) |
-                         __builtin_amdgcn_perm(s.o1, s.o0, g.sel[7]);
-    const uint32_t lo = ye0 | (yo0 << 4);
-    const uint32_t hi = ye1 | (yo1 << 4);
-    return ((uint64_t)hi << 32) | lo;
+    return join_nibbles(apply_gensel_nibbles(s, g));
 }
 
 __device__ __forceinline__ uint64_t apply_gensel(uint64_t key, const GenSel &g) {
     return apply_gensel(split_nibbles(key), g);
+}
+
+// Rank of a split state: its entries are read from their bytes.
+template <int N, class R = uint32_t>
+__device__ __forceinline__ R nibbles_rank_t(const Nibbles &y) {
+    return perm_rank_of<N, R>([&](int i) {
+        const int q = N - 1 - i;  // nibble of the key
+        const uint32_t w = q & 1 ? (q < 8 ? y.o0 : y.o1) : (q < 8 ? y.e0 : y.e1);
+        return (w >> (8 * (q / 2 % 4))) & 255u;
+    });
 }
 
 }  // namespace cg

@@ -82,8 +82,9 @@ constexpr uint32_t rank_lo_radix() {
 // The same with n fixed at compile time: the loops unroll, shifts become
 // constants and the divisions of the unrank become multiplications. R is
 // the rank type: uint32_t up to n = 12, uint64_t beyond (16! < 2^45).
-template <int N, class R = uint32_t>
-__host__ __device__ __forceinline__ R perm_rank_t(uint64_t key) {
+// `entry(i)`: entry i of the permutation.
+template <int N, class R, class E>
+__host__ __device__ __forceinline__ R perm_rank_of(E entry) {
     // c_i = number of values below s[i] not used before position i: the
     // popcount of the low s[i] bits of the still-unused set. The first
     // position has c_0 = s[0]; the last always has c = 0.
@@ -102,18 +103,18 @@ __host__ __device__ __forceinline__ R perm_rank_t(uint64_t key) {
         static_assert(kLoRadix < (1u << 24), "low part of the rank in 24 bits");
         static_assert(sizeof(R) == 8 || N <= 12, "32-bit ranks up to n = 12");
         uint32_t unused = (1u << N) - 1u;
-        const uint32_t v0 = (uint32_t)(key >> (4 * (N - 1))) & 15u;
+        const uint32_t v0 = entry(0);
         uint32_t hi = v0, lo = 0;
-        unused ^= 1u << v0;
+        unused += ~0u << v0;  // takes the bit away: one shift-and-add
 #pragma unroll
         for (int i = 1; i < N - 1; ++i) {
-            const uint32_t v = (uint32_t)(key >> (4 * (N - 1 - i))) & 15u;
+            const uint32_t v = entry(i);
             const uint32_t c = (uint32_t)__builtin_popcount(low_bits(unused, v));
             if (i <= kHi)
                 hi = mad24<uint32_t>(hi, (uint32_t)(N - i), c);
             else
                 lo = mad24<uint32_t>(lo, (uint32_t)(N - i), c);
-            unused ^= 1u << v;
+            unused += ~0u << v;
         }
         // the last position's digit is 0 (radix 1)
         if constexpr (sizeof(R) == 4)
@@ -121,6 +122,10 @@ __host__ __device__ __forceinline__ R perm_rank_t(uint64_t key) {
         else
             return (uint64_t)hi * (uint64_t)kLoRadix + (uint64_t)lo;
     }
+}
+template <int N, class R = uint32_t>
+__host__ __device__ __forceinline__ R perm_rank_t(uint64_t key) {
+    return perm_rank_of<N, R>([&](int i) { return (uint32_t)(key >> (4 * (N - 1 - i))) & 15u; });
 }
 
 // The inverse with n fixed at compile time (n <= 16). The unused values,

@@ -479,7 +479,7 @@ __global__ __launch_bounds__(kBlock) void expand_rank_hist_kernel(
                     if (kGuard && f >= hi) continue;
                     R r;
                     if constexpr (!Incr) {
-                        r = perm_rank_t<N, R>(apply_gensel(st[j], gsel[g]));
+                        r = nibbles_rank_t<N, R>(apply_gensel_nibbles(st[j], gsel[g]));
                     } else if constexpr (M <= N - 2) {
                         r = rank_prefix_from<N, M>(sk[j], gsh + (uint32_t)g * N) + suf[j][M - 2];
                     } else {

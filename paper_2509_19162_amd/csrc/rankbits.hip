@@ -91,6 +91,7 @@ struct RbBits {
         return x ^ (x >> kShift);
     }
     static __device__ __forceinline__ uint32_t of_key(uint64_t key) { return of_rank(perm_rank_t<N>(key)); }
+    static __device__ __forceinline__ uint32_t of_state(const Nibbles &y) { return of_rank(nibbles_rank_t<N>(y)); }
     // bits of a segment: 512 segments
     static constexpr int kLgSeg = B - (int)kRbLgDigits;
 };
@@ -152,8 +153,9 @@ __global__ __launch_bounds__(kRbBlock) __attribute__((amdgpu_waves_per_eu(8))) v
 #pragma unroll
             for (int j = 0; j < kRbRows; ++j) {
                 const uint32_t g = q * kRbRows + j < a.k ? q * kRbRows + j : a.k - 1;
-                t[j] = apply_gensel(s, uniform_gensel(a.sel, g));
-                r[j] = RbBits<N>::of_key(t[j]);
+                const Nibbles y = apply_gensel_nibbles(s, uniform_gensel(a.sel, g));
+                t[j] = join_nibbles(y);
+                r[j] = RbBits<N>::of_state(y);
                 fresh[j] = in && q * kRbRows + j < a.k;
                 word[j] = fresh[j] ? a.seen[r[j] >> 5] : ~0u;
             }
@@ -238,7 +240,7 @@ __global__ __launch_bounds__(kPartBlock) void rb_part_kernel(const uint64_t *__r
                 const GenSel G = uniform_gensel(sel, g < k ? g : k - 1);
 #pragma unroll
                 for (int j = 0; j < kRbPartStates; ++j) {
-                    const uint32_t r = RbBits<N>::of_key(apply_gensel(s[j], G));
+                    const uint32_t r = RbBits<N>::of_state(apply_gensel_nibbles(s[j], G));
                     x[h * kRbPartStates + j] = r & ((1u << RbBits<N>::kLgSeg) - 1u);
                     dig[h * kRbPartStates + j] = r >> RbBits<N>::kLgSeg;
                 }
@@ -373,7 +375,7 @@ __global__ __launch_bounds__(kRbBlock) __attribute__((amdgpu_waves_per_eu(8))) v
                 key = perm_unrank_t<N>(RbBits<N>::to_rank((w0 << 5) + bit));
                 const Nibbles s = split_nibbles(key);
                 for (uint32_t g = 0; g < a.k && !hit; ++g) {
-                    const uint32_t r = RbBits<N>::of_key(apply_gensel(s, uniform_gensel(inv, g)));
+                    const uint32_t r = RbBits<N>::of_state(apply_gensel_nibbles(s, uniform_gensel(inv, g)));
                     hit = (seen[r >> 5] >> (r & 31u)) & 1u;
                 }
                 if (hit) atomicOr(&s_new[bit >> 5], 1u << (bit & 31u));
