@@ -69,7 +69,8 @@ public:
 
 private:
     hipStream_t stream_;
-    DevBuf jobs_, gsel_, sizes_, outs_, ws_, ticket_;
+    DevBuf jobs_, gsel_, outs_, ws_, ticket_;  // outs_: outcomes, then layer sizes
+    HostKit kit_;                              // read-back
     hipGraphExec_t exec_ = nullptr;
     hipGraph_t graph_ = nullptr;
     std::vector<uint64_t> graph_key_;

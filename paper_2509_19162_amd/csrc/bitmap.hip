@@ -1015,14 +1015,15 @@ bool wg_eligible(const JobSpec &spec) {
 // WgRunner
 // ---------------------------------------------------------------------------
 WgRunner::WgRunner(hipStream_t s) : stream_(s) {
-    for (DevBuf *b : {&jobs_, &gsel_, &sizes_, &outs_, &ws_, &ticket_}) b->stream = s;
+    for (DevBuf *b : {&jobs_, &gsel_, &outs_, &ws_, &ticket_}) b->stream = s;
 }
 
 WgRunner::~WgRunner() {
     if (exec_) (void)hipGraphExecDestroy(exec_);
     if (graph_) (void)hipGraphDestroy(graph_);
-    (void)hipStreamSynchronize(stream_);
-    for (DevBuf *b : {&jobs_, &gsel_, &sizes_, &outs_, &ws_, &ticket_}) b->release();
+    const bool idle = hipStreamSynchronize(stream_) == hipSuccess;
+    for (DevBuf *b : {&jobs_, &gsel_, &outs_, &ws_, &ticket_}) b->release();
+    give_kit(kit_, idle);
 }
 
 namespace {
@@ -1150,12 +1151,12 @@ uint64_t WgRunner::launch_bytes(const std::vector<WgItem> &items, const WgTuning
     const uint64_t slots = std::min(wg_grid(T, t.block).big, T.n10);
     // every buffer as DevBuf rounds it (64 KiB) with its growth slack
     auto r = [](uint64_t b) { return ((uint64_t)(1.5 * (double)b) + (64u << 10) - 1) / (64u << 10) * (64u << 10); };
-    return r(sizeof(WgJobDev) * nj) + r(sizeof(GenSel) * T.gsel.size()) + r(sizeof(uint64_t) * T.sizes_total) +
-           r(sizeof(WgOutDev) * nj) + r(256) + r(slots * kWgSlotWords * sizeof(uint32_t));
+    return r(sizeof(WgJobDev) * nj) + r(sizeof(GenSel) * T.gsel.size()) +
+           r(sizeof(WgOutDev) * nj + sizeof(uint64_t) * T.sizes_total) + r(256) + r(slots * kWgSlotWords * sizeof(uint32_t));
 }
 
 uint64_t WgRunner::device_bytes() const {
-    return jobs_.bytes + gsel_.bytes + sizes_.bytes + outs_.bytes + ws_.bytes + ticket_.bytes;
+    return jobs_.bytes + gsel_.bytes + outs_.bytes + ws_.bytes + ticket_.bytes;
 }
 
 void WgRunner::release() {
@@ -1164,7 +1165,8 @@ void WgRunner::release() {
     exec_ = nullptr;
     graph_ = nullptr;
     graph_key_.clear();
-    for (DevBuf *b : {&jobs_, &gsel_, &sizes_, &outs_, &ws_, &ticket_}) b->release();
+    for (DevBuf *b : {&jobs_, &gsel_, &outs_, &ws_, &ticket_}) b->release();
+    give_kit(kit_, hipStreamSynchronize(stream_) == hipSuccess);
 }
 
 double WgRunner::run(std::vector<WgItem> &items, const WgTuning &t, double t_submit) {
@@ -1180,8 +1182,10 @@ double WgRunner::run(std::vector<WgItem> &items, const WgTuning &t, double t_sub
 
     jobs_.ensure(sizeof(WgJobDev) * nj, 1.25);
     gsel_.ensure(sizeof(GenSel) * T.gsel.size(), 1.25);
-    sizes_.ensure(sizeof(uint64_t) * sizes_total, 1.25);
-    outs_.ensure(sizeof(WgOutDev) * nj, 1.25);
+    static_assert(sizeof(WgOutDev) % sizeof(uint64_t) == 0, "sizes follow the outcomes");
+    const size_t outs_bytes = sizeof(WgOutDev) * nj, back = outs_bytes + sizeof(uint64_t) * sizes_total;
+    outs_.ensure(back, 1.25);
+    uint64_t *const d_sizes = reinterpret_cast<uint64_t *>(outs_.as<char>() + outs_bytes);
     ticket_.ensure(256);
     if (n_slot_blocks) ws_.ensure((size_t)n_slot_blocks * kWgSlotWords * sizeof(uint32_t));
     CG_HIP(hipMemcpyAsync(jobs_.p, T.jobs.data(), sizeof(WgJobDev) * nj, hipMemcpyHostToDevice, stream_));
@@ -1189,9 +1193,9 @@ double WgRunner::run(std::vector<WgItem> &items, const WgTuning &t, double t_sub
 
     uint32_t *gbits = n_slot_blocks ? ws_.as<uint32_t>() : nullptr;
     WgLaunch args{jobs_.as<const WgJobDev>(), T.n10, T.n9, nj, n_slot_blocks, gsel_.as<const GenSel>(),
-                  sizes_.as<uint64_t>(), outs_.as<WgOutDev>(), ticket_.as<uint32_t>(), gbits, kWgSlotWords};
+                  d_sizes, outs_.as<WgOutDev>(), ticket_.as<uint32_t>(), gbits, kWgSlotWords};
     const std::vector<uint64_t> key = {(uint64_t)(uintptr_t)jobs_.p,   nj,
-                                       (uint64_t)(uintptr_t)gsel_.p,   (uint64_t)(uintptr_t)sizes_.p,
+                                       (uint64_t)(uintptr_t)gsel_.p,   (uint64_t)(uintptr_t)d_sizes,
                                        (uint64_t)(uintptr_t)outs_.p,   (uint64_t)(uintptr_t)ticket_.p,
                                        (uint64_t)(uintptr_t)gbits,     (uint64_t)t.block,
                                        T.n10,                          T.n9,
@@ -1263,17 +1267,29 @@ double WgRunner::run(std::vector<WgItem> &items, const WgTuning &t, double t_sub
         CG_HIP(hipGetLastError());
     }
     CG_HIP(hipEventRecord(e1, stream_));
-    std::vector<uint64_t> hsz(sizes_total);
-    std::vector<WgOutDev> ho(nj);
-    CG_HIP(hipMemcpyAsync(hsz.data(), sizes_.p, sizeof(uint64_t) * sizes_total, hipMemcpyDeviceToHost, stream_));
-    CG_HIP(hipMemcpyAsync(ho.data(), outs_.p, sizeof(WgOutDev) * nj, hipMemcpyDeviceToHost, stream_));
+    // one copy, into pinned memory where that is kept (large batches: their
+    // sizes take milliseconds either way)
+    std::vector<uint64_t> pageable;
+    const char *h;
+    if (back <= kMaxKitBytes) {
+        if (kit_.bytes < back) {
+            give_kit(kit_, true);
+            kit_ = take_kit(back, false);
+        }
+        h = static_cast<const char *>(kit_.host);
+    } else {
+        pageable.resize(back / sizeof(uint64_t));
+        h = reinterpret_cast<const char *>(pageable.data());
+    }
+    CG_HIP(hipMemcpyAsync(const_cast<char *>(h), outs_.p, back, hipMemcpyDeviceToHost, stream_));
     CG_HIP(hipStreamSynchronize(stream_));
     float ms = 0;
     CG_HIP(hipEventElapsedTime(&ms, e0, e1));
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     const double t_done = now_seconds();
-    wg_results(items, T, hsz.data(), ho.data(), ms, t_submit, t_admit, t_done);
+    wg_results(items, T, reinterpret_cast<const uint64_t *>(h + outs_bytes), reinterpret_cast<const WgOutDev *>(h), ms,
+               t_submit, t_admit, t_done);
     return ms;
 }
 
@@ -1491,8 +1507,8 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     CG_HIP(hipEventCreate(&e1));
     CG_HIP(hipEventRecord(e0, s));
     const uint32_t grid = (uint32_t)std::min<uint64_t>(nchunks, (uint64_t)device_cus() * 16);
-    uint64_t *host_cnt = nullptr;
-    CG_HIP(hipHostMalloc((void **)&host_cnt, 2 * sizeof(uint64_t), hipHostMallocDefault));
+    HostKit kit = take_kit(2 * sizeof(uint64_t), false);
+    uint64_t *const host_cnt = static_cast<uint64_t *>(kit.host);
     uint32_t *pc = cur.as<uint32_t>(), *pn = nxt.as<uint32_t>(), *sc = scur.as<uint32_t>(),
              *sn = snxt.as<uint32_t>();
     uint64_t F = 1, before = 0, seen = 1;
@@ -1589,8 +1605,7 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
             seen += N;
         }
     } catch (...) {
-        (void)hipStreamSynchronize(s);
-        (void)hipHostFree(host_cnt);
+        give_kit(kit, hipStreamSynchronize(s) == hipSuccess);
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         throw;
@@ -1601,7 +1616,7 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     CG_HIP(hipEventElapsedTime(&ms, e0, e1));
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    (void)hipHostFree(host_cnt);
+    give_kit(kit, true);
     for (DevBuf *b : {&vis, &cur, &nxt, &scur, &snxt, &gsel, &cnt, &lists, &list_cnt}) b->release();
     res->device_ms = ms;
     res->status = status;

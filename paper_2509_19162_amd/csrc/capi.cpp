@@ -70,6 +70,7 @@ void cg_release_cached_memory(void) {
     guarded([&]() -> int {
         cg::release_batch_buffers();
         cg::release_cached_device_memory();
+        cg::release_kits();
         return CG_OK;
     });
 }

@@ -115,28 +115,21 @@ JobSpec canonicalize(const cg_job_t &job, bool batch) {
 }
 
 Engine::Engine(hipStream_t user_stream) {
-    if (user_stream) {
-        stream_ = user_stream;
-    } else {
-        CG_HIP(hipStreamCreateWithFlags(&stream_, hipStreamNonBlocking));
-        own_stream_ = true;
-    }
-    w_.init(stream_);
+    kit_ = take_kit(kHostSmallBytes, user_stream == nullptr);
+    stream_ = user_stream ? user_stream : kit_.stream;
+    host_small_ = static_cast<uint64_t *>(kit_.host);
+    w_.attach(stream_);
     for (DevBuf *b : buffers()) b->stream = stream_;
     prof_.stream = stream_;
-    CG_HIP(hipHostMalloc((void **)&host_small_, kHostSmallBytes, hipHostMallocDefault));
 }
 
 Engine::~Engine() {
     delete wg_;
-    if (host_small_) (void)hipHostFree(host_small_);
     // buffers go back to the device cache while their stream still exists
     for (DevBuf *b : buffers()) b->release();
     for (DevBuf *b : w_.buffers()) b->release();
-    if (own_stream_) {
-        (void)hipStreamSynchronize(stream_);
-        (void)hipStreamDestroy(stream_);
-    }
+    // (copies from or to the kit may be under way after an error)
+    give_kit(kit_, hipStreamSynchronize(stream_) == hipSuccess);
 }
 
 std::vector<DevBuf *> Engine::buffers() {
@@ -407,6 +400,7 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
 // The layer loop by sorting, from layer 0 or (resume) from where the hash
 // buckets stopped.
 void Engine::run_sorted(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &pg, bool resume) {
+    if (!w_.ready()) w_.init(stream_);
     const int n = spec.n, k = spec.k;
     const bool keep_all = (spec.flags & CG_KEEP_ALL_LAYERS) != 0;
     // A set not closed under inverses can reach any earlier layer, so the

@@ -92,7 +92,6 @@ private:
                          uint64_t *dst, uint64_t out_cap, uint64_t room, int in);
 
     hipStream_t stream_ = nullptr;
-    bool own_stream_ = false;
     PipeWork w_;
     Profiler prof_;
     DevBuf gsel_, cand0_, cand1_, lay_[3], arena_, stage_, chunk_hist_, vis_[2];
@@ -103,7 +102,8 @@ private:
     DevBuf part_[2], part_cnt_[2], tab_[3], small_[3], hctr_, ssz_, order_[2];
     class WgRunner *wg_ = nullptr;  // small-job engine (created on first use)
     static constexpr size_t kHostSmallBytes = 16384;
-    uint64_t *host_small_ = nullptr;  // pinned: counters read back, inputs uploaded
+    HostKit kit_;
+    uint64_t *host_small_ = nullptr;  // of the kit: counters read back, inputs uploaded
 };
 
 void fill_kstats(const Profiler &p, cg_result_t *res);

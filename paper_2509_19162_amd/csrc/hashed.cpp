@@ -69,6 +69,7 @@ uint64_t hash_layers_bytes(const JobSpec &spec) {
 
 // keys[0..n) sorted, in a or b (each n keys); keys is left as it is.
 uint64_t *Engine::sorted_copy(const JobSpec &spec, const uint64_t *keys, uint64_t n, DevBuf &a, DevBuf &b) {
+    if (!w_.ready()) w_.init(stream_);
     a.ensure(std::max<uint64_t>(n, 1) * 8);
     b.ensure(std::max<uint64_t>(n, 1) * 8);
     CG_HIP(hipMemcpyAsync(a.p, keys, n * 8, hipMemcpyDeviceToDevice, stream_));

@@ -145,6 +145,24 @@ void memory_stats(cg_memory_stats_t *out, bool reset_peak);
 // Frees the device arena (hipFree) when no buffer uses it
 // (cg_release_cached_memory).
 void release_cached_device_memory();
+
+// What a single call needs besides device memory: pinned host memory and,
+// where the caller brings no stream, a stream. Making and destroying them
+// took half of a small growth (S_7: 100 of 190 us), so idle ones are kept,
+// at most kMaxIdleKits of at most kMaxKitBytes each in a process, until
+// release_kits(). A kit has one owner at a time, and goes back only when no
+// work that uses it is under way.
+struct HostKit {
+    int dev = -1;
+    hipStream_t stream = nullptr;
+    void *host = nullptr;
+    size_t bytes = 0;
+};
+constexpr size_t kMaxIdleKits = 16;
+constexpr size_t kMaxKitBytes = 4u << 20;
+HostKit take_kit(size_t bytes, bool with_stream);  // of the current device
+void give_kit(HostKit &k, bool idle);              // not idle (an error): destroyed
+void release_kits();
 // Makes [p, p + bytes) the current device's arena (p == nullptr: back to an
 // arena the library reserves itself). Throws CG_E_BUSY while buffers live
 // in the current arena.
@@ -175,7 +193,9 @@ struct PipeWork {
     std::vector<DevBuf *> buffers() {
         return {&hist, &base, &small, &status, &bounds, &tile_cnt, &tile_off, &kill, &tcnt, &toff, &bsum};
     }
-    void init(hipStream_t s);
+    void attach(hipStream_t s);  // no memory yet
+    void init(hipStream_t s);    // attach, and the small buffers
+    bool ready() const { return small.p != nullptr; }
     // Make room for `words` look-back words (new memory is cleared).
     void ensure_status(uint64_t words);
     // Epoch of the next look-back launch; on wrap-around the words are

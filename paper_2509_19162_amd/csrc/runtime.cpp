@@ -8,6 +8,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <vector>
 
 #include "../../include/cayleygrowth.h"
 #include "internal.h"
@@ -281,9 +282,87 @@ void DevBuf::release() {
     bytes = 0;
 }
 
-void PipeWork::init(hipStream_t s) {
+namespace {
+struct IdleKits {
+    std::mutex mu;
+    std::vector<HostKit> kits;
+};
+// never destroyed: the HIP runtime may be gone by then
+IdleKits &idle_kits() {
+    static IdleKits *k = new IdleKits;
+    return *k;
+}
+void destroy_kit(HostKit &k) {
+    if (k.host) (void)hipHostFree(k.host);
+    if (k.stream) (void)hipStreamDestroy(k.stream);
+    k = HostKit();
+}
+}  // namespace
+
+HostKit take_kit(size_t bytes, bool with_stream) {
+    HostKit k;
+    CG_HIP(hipGetDevice(&k.dev));
+    {
+        IdleKits &idle = idle_kits();
+        std::lock_guard<std::mutex> lk(idle.mu);
+        size_t best = idle.kits.size();
+        for (size_t i = 0; i < idle.kits.size(); ++i) {
+            const HostKit &x = idle.kits[i];
+            if (x.dev != k.dev || x.bytes < bytes) continue;
+            // the smallest that does; with a stream if one is wanted, else without
+            auto cost = [&](const HostKit &y) { return 2 * y.bytes + ((y.stream != nullptr) != with_stream ? 1u : 0u); };
+            if (best == idle.kits.size() || cost(x) < cost(idle.kits[best])) best = i;
+        }
+        if (best < idle.kits.size()) {
+            k = idle.kits[best];
+            idle.kits.erase(idle.kits.begin() + (std::ptrdiff_t)best);
+        }
+    }
+    try {
+        if (!k.host) {
+            k.bytes = 16384;
+            while (k.bytes < bytes) k.bytes *= 2;
+            CG_HIP(hipHostMalloc(&k.host, k.bytes, hipHostMallocDefault));
+        }
+        if (with_stream && !k.stream) CG_HIP(hipStreamCreateWithFlags(&k.stream, hipStreamNonBlocking));
+    } catch (...) {
+        destroy_kit(k);
+        throw;
+    }
+    return k;
+}
+
+void give_kit(HostKit &k, bool idle) {
+    if (!k.host && !k.stream) return;
+    if (idle && k.bytes <= kMaxKitBytes) {
+        IdleKits &all = idle_kits();
+        std::lock_guard<std::mutex> lk(all.mu);
+        if (all.kits.size() < kMaxIdleKits) {
+            all.kits.push_back(k);
+            k = HostKit();
+            return;
+        }
+    }
+    destroy_kit(k);
+}
+
+void release_kits() {
+    std::vector<HostKit> gone;
+    {
+        IdleKits &all = idle_kits();
+        std::lock_guard<std::mutex> lk(all.mu);
+        gone.swap(all.kits);
+    }
+    for (HostKit &k : gone) destroy_kit(k);
+}
+
+void PipeWork::attach(hipStream_t s) {
     stream = s;
     for (DevBuf *b : buffers()) b->stream = s;
+}
+
+void PipeWork::init(hipStream_t s) {
+    attach(s);
     hist.ensure(kMaxPasses * 256 * sizeof(uint64_t));
     base.ensure(kMaxPasses * 256 * sizeof(uint64_t));
     small.ensure(32 * sizeof(uint32_t) + 4 * sizeof(uint32_t) + 8 * sizeof(uint64_t) + 256);
