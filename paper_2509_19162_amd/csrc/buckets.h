@@ -49,6 +49,24 @@ struct HashGens {
 // and per generator its first term (k + 1 entries).
 void make_bit_terms(int n, const uint8_t *gens, int k, std::vector<BitTerm> &terms, std::vector<uint32_t> &first);
 
+// Tags. A state's neighbours in layer d-1 are those it came from. So a
+// candidate carries, above the state in its key, the bit of the generator
+// that undoes its own; the bits of equal candidates are OR-ed; and the
+// generators that take a state of a tagged layer back are left out, with
+// them the look at layer d-1. For the LRX moves a state forms two neighbours
+// or one instead of three: S_16 with layers up to 2^29 91 -> 73 ms, the
+// C(32,16) binary states 44 -> 30. As many generators as a key has bits
+// left (64 - 4n, binary 64 - n); at n = 16 four, in place of entry 0, which
+// follows from the others, as the entries' sum is the orbit's.
+constexpr uint32_t kHashMaxTags = 28;
+struct HashTags {
+    uint32_t mask_hi = ~0u;  // of a key's high word: the state without its tags
+    uint32_t shift = 0;      // the tags: the high word from this bit on
+    uint32_t sum = 0;        // n = 16: 16 + the sum of a state's entries modulo 16
+    uint32_t undo[kHashMaxTags] = {};  // the bit of the generator that undoes generator g
+    bool on() const { return mask_hi != ~0u; }
+};
+
 // A layer in buckets: 2^lg of them, each one run of `keys`; bucket[i] =
 // start | count << kHashStartBits. lg == 0: the whole of keys[0..n), no table.
 struct HashLayer {
@@ -56,6 +74,7 @@ struct HashLayer {
     uint64_t n = 0;
     const uint64_t *bucket = nullptr;
     uint32_t lg = 0;
+    bool tagged = false;
 };
 
 // How one layer step is split.
@@ -83,12 +102,16 @@ struct HashBufs {
     uint64_t *next;      // those of the next step (another line), cleared by this one
 };
 // Partitions the candidates of `cur`.
-void launch_hash_partition(const HashPlan &p, const HashGens &g, const HashLayer &cur, const HashBufs &b,
-                           PipeWork &w);
+// (Those of a tagged layer: each state's k - 1 at most; the plan is for as
+// many.)
+void launch_hash_partition(const HashPlan &p, const HashGens &g, const HashTags &t, const HashLayer &cur,
+                           const HashBufs &b, PipeWork &w);
+// dst[i] = the whole key of the state src[i].
+void launch_hash_strip(uint64_t *dst, const uint64_t *src, uint64_t n, const HashTags &t, hipStream_t s);
 // Buckets: new states to out[0..out_cap) (the count in counters[kHashCount]
 // goes on past out_cap), their buckets to out_bucket[0 .. 2^lg_q).
 void launch_hash_buckets(const HashPlan &p, const HashLayer &prev, const HashLayer &cur, const HashBufs &b,
-                         uint64_t *out, uint64_t out_cap, uint64_t *out_bucket, PipeWork &w);
+                         const HashTags &t, uint64_t *out, uint64_t out_cap, uint64_t *out_bucket, PipeWork &w);
 
 struct HashSmallArgs {
     const uint64_t *prev, *cur;
@@ -101,7 +124,7 @@ struct HashSmallArgs {
     uint64_t *sizes;           // sizes of the new layers (the last may be 0)
     uint32_t *state;           // [0] layers added (an empty one included), [1] kSmall*
 };
-void launch_hash_small(const HashSmallArgs &a, const HashGens &g, PipeWork &w);
+void launch_hash_small(const HashSmallArgs &a, const HashGens &g, const HashTags &t, PipeWork &w);
 // Sorts `layers` consecutive runs of keys (at most kSmallSortStates each) in
 // place; the runs' lengths are at sizes[0..layers).
 void launch_hash_sort_small(uint64_t *keys, const uint64_t *sizes, uint32_t layers, hipStream_t s);

@@ -114,13 +114,33 @@ struct BitGens {
     }
 };
 
+// ---- tags --------------------------------------------------------------------------
+__device__ __forceinline__ uint64_t tag_off(uint64_t key, uint32_t mask_hi) {
+    return (uint64_t)((uint32_t)(key >> 32) & mask_hi) << 32 | (uint32_t)key;
+}
+// The whole key: without its tag, entry 0 of n = 16 put back.
+__device__ __forceinline__ uint64_t tag_strip(uint64_t key, const HashTags &t) {
+    key = tag_off(key, t.mask_hi);
+    if (t.sum) {
+        const uint32_t lo = (uint32_t)key, hi = (uint32_t)(key >> 32), m = 0x0F0F0F0Fu;
+        const uint32_t four = (lo & m) + ((lo >> 4) & m) + (hi & m) + ((hi >> 4) & m);  // bytes up to 60
+        key |= (uint64_t)(t.sum - __builtin_amdgcn_sad_u8(four, 0u, 0u)) << 60;
+    }
+    return key;
+}
+
 // Items of (4096 frontier states) x (a range of generators), dealt to the
 // blocks in turn. The item's states stay in registers; each round maps them
-// through one generator. A candidate equal to its state is dropped here.
-template <class G>
+// through one generator. A candidate equal to its state is dropped here. Of
+// a tagged layer there are k - 1 rounds: in the first that would take a
+// state back it takes the last generator (if that does not).
+// kTags: the growth has tags (without, nothing is spent on them: the checks
+// cost the Coxeter growth of a 14-entry coset graph 9%).
+template <class G, bool kTags>
 __global__ __launch_bounds__(kPartBlock) void hash_expand_kernel(const uint64_t *__restrict__ frontier, uint64_t F,
-                                                                 G gens, uint32_t k, uint32_t tiles, uint32_t ranges,
-                                                                 uint32_t lg, PartOut<uint64_t> o, uint64_t *next) {
+                                                                 G gens, uint32_t k, HashTags tags, bool tagged,
+                                                                 uint32_t tiles, uint32_t ranges, uint32_t lg,
+                                                                 PartOut<uint64_t> o, uint64_t *next) {
     __shared__ PartLds<uint64_t> L;
     const uint32_t tid = threadIdx.x;
     // the next step's counters, not this one's: a plain store would reach
@@ -130,28 +150,49 @@ __global__ __launch_bounds__(kPartBlock) void hash_expand_kernel(const uint64_t 
     o.base += (uint64_t)blockIdx.x * o.cap;
     o.count += blockIdx.x;
     uint32_t parity = 0;
+    const uint32_t rounds = kTags && tagged ? k - 1 : k;
     for (uint32_t it = blockIdx.x; it < tiles * ranges; it += gridDim.x) {
         const uint32_t tile = it / ranges, range = it - tile * ranges;
-        const uint32_t g0 = (uint32_t)((uint64_t)k * range / ranges), g1 = (uint32_t)((uint64_t)k * (range + 1) / ranges);
-        uint64_t s[kPartRows];
-        uint32_t in = 0;
+        const uint32_t g0 = (uint32_t)((uint64_t)rounds * range / ranges);
+        const uint32_t g1 = (uint32_t)((uint64_t)rounds * (range + 1) / ranges);
+        uint64_t s[kPartRows], last[kPartRows];
+        uint32_t back[kPartRows], in = 0;
 #pragma unroll
         for (int j = 0; j < kPartRows; ++j) {
             const uint64_t f = (uint64_t)tile * kPartTile + (uint32_t)j * kPartBlock + tid;
-            s[j] = f < F ? frontier[f] : 0ull;
+            const uint64_t x = f < F ? frontier[f] : 0ull;
             if (f < F) in |= 1u << j;
+            s[j] = kTags ? tag_strip(x, tags) : x;
+            back[j] = kTags && tagged ? (uint32_t)(x >> 32) >> tags.shift : 0u;
+        }
+        if (kTags && tagged) {
+#pragma unroll
+            for (int j = 0; j < kPartRows; ++j) last[j] = gens.apply(s[j], k - 1);
         }
         for (uint32_t g = g0; g < g1; ++g) {
             uint64_t c[kPartRows];
-            uint32_t pend = in;
+            uint32_t pend = in, tag[kPartRows];
 #pragma unroll
             for (int j = 0; j < kPartRows; ++j) {
                 c[j] = gens.apply(s[j], g);
+                if constexpr (kTags) {
+                    // g takes the state back, as the first that does: -x & x is its bit
+                    const uint32_t x = back[j];
+                    const bool over = (x >> g) & 1u;
+                    const bool instead = over && (x & (0u - x)) >> g == 1u && !((x >> (k - 1)) & 1u);
+                    if (instead) c[j] = last[j];
+                    if (over && !instead) pend &= ~(1u << j);
+                    tag[j] = instead ? tags.undo[k - 1] : tags.undo[g];
+                }
                 if (c[j] == s[j]) pend &= ~(1u << j);
             }
             uint32_t dig[kPartRows];
 #pragma unroll
-            for (int j = 0; j < kPartRows; ++j) dig[j] = key_hash(c[j]) >> (32 - lg);
+            for (int j = 0; j < kPartRows; ++j) {
+                if constexpr (kTags) c[j] = tag_off(c[j], tags.mask_hi);
+                dig[j] = key_hash(c[j]) >> (32 - lg);
+                if constexpr (kTags) c[j] |= (uint64_t)tag[j] << 32;
+            }
             part_round(L, c, dig, pend, lg, o, parity);
         }
     }
@@ -161,10 +202,11 @@ __global__ __launch_bounds__(kPartBlock) void hash_expand_kernel(const uint64_t 
 // Second partition: block d takes digit d's keys from every first-level
 // block. A wave walks its share of the source blocks' parts; the block goes
 // on while any wave has keys left.
+template <bool kTags>
 __global__ __launch_bounds__(kPartBlock) void hash_split_kernel(const uint64_t *__restrict__ in,
                                                                 const uint32_t *__restrict__ in_count, uint32_t nsrc,
-                                                                uint32_t in_cap, uint32_t lg1, uint32_t lg2,
-                                                                PartOut<uint64_t> o) {
+                                                                uint32_t in_cap, uint32_t mask_hi, uint32_t lg1,
+                                                                uint32_t lg2, PartOut<uint64_t> o) {
     __shared__ PartLds<uint64_t> L;
     constexpr uint32_t kWaves = kPartBlock / kWave;
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -200,7 +242,7 @@ __global__ __launch_bounds__(kPartBlock) void hash_split_kernel(const uint64_t *
         if (!__syncthreads_or(any)) break;
         uint32_t dig[kPartRows];
 #pragma unroll
-        for (int j = 0; j < kPartRows; ++j) dig[j] = (key_hash(key[j]) << lg1) >> (32 - lg2);
+        for (int j = 0; j < kPartRows; ++j) dig[j] = (key_hash(kTags ? tag_off(key[j], mask_hi) : key[j]) << lg1) >> (32 - lg2);
         part_round(L, key, dig, pend, lg2, o, parity);
     }
     part_end(L, lg2, o);
@@ -218,13 +260,16 @@ __device__ __forceinline__ uint64_t uniform(uint64_t x) {
 // odd stride per key. The compare-and-swap is the probe: it reads, and takes
 // a free slot at once. One key per lane at a time: with tables at most 3/8
 // full a wave is done after about three probes. True when the key was not
-// in the table (its slot in `slot`). A probe past kMaxProbes raises *over.
-__device__ __forceinline__ bool table_insert(uint64_t *tab, uint32_t lg, uint64_t key, bool on, uint32_t &slot,
-                                             uint32_t *over) {
+// in the table (its slot in `slot`); keys that differ in their tags only are
+// the same, and their tags are OR-ed. A probe past kMaxProbes raises *over.
+template <bool kTags>
+__device__ __forceinline__ bool table_insert(uint64_t *tab, uint32_t lg, uint64_t key, uint32_t mask_hi, bool on,
+                                             uint32_t &slot, uint32_t *over) {
     // linear in the key's halves: enough among the states of one bucket,
     // which are a random subset (slots fill as by uniform draws on the
     // layers named at the hash above)
-    const uint32_t h = (uint32_t)key * 0x9E3779B1u + (uint32_t)(key >> 32) * 0x85EBCA77u;
+    const uint32_t hi = kTags ? (uint32_t)(key >> 32) & mask_hi : (uint32_t)(key >> 32);
+    const uint32_t h = (uint32_t)key * 0x9E3779B1u + hi * 0x85EBCA77u;
     const uint32_t mask = (1u << lg) - 1u, step = h | 1u;
     slot = h >> (32 - lg);
     bool fresh = false;
@@ -233,7 +278,12 @@ __device__ __forceinline__ bool table_insert(uint64_t *tab, uint32_t lg, uint64_
         const uint64_t old = atomicCAS((unsigned long long *)&tab[slot], (unsigned long long)kSentinel,
                                        (unsigned long long)key);
         fresh = old == kSentinel;
-        if (fresh || old == key) break;
+        if (fresh || (!kTags && old == key)) break;
+        if (kTags && tag_off(old ^ key, mask_hi) == 0) {
+            const uint32_t tags = (uint32_t)(key >> 32) & ~mask_hi;
+            if (tags & ~(uint32_t)(old >> 32)) atomicOr(reinterpret_cast<uint32_t *>(&tab[slot]) + 1, tags);
+            break;
+        }
         slot = (slot + step) & mask;
         if (++probes > kMaxProbes) {
             *over = 1;
@@ -263,6 +313,7 @@ struct BucketArgs {
     uint32_t nsrc, in_cap;
     uint32_t lg_q, lg_sub;     // bucket q of 2^lg_q lies in partition q >> lg_sub
     uint32_t lg_slots;
+    uint32_t mask_hi;          // of the keys' tags
     LayerRef A, B;             // layers d and d-1
     uint64_t *out;
     uint64_t out_cap;
@@ -279,14 +330,18 @@ __device__ __forceinline__ uint64_t run_of(const LayerRef &R, uint32_t q, uint32
 
 // Inserts the keys of `act` that lie in bucket q; the slots of those that
 // were new go to the list (candidates) or are forgotten (references).
+template <bool kTags>
 __device__ __forceinline__ void bucket_insert(BucketLds &L, const BucketArgs &a, const uint64_t (&key)[4],
                                               uint32_t act, uint32_t q, bool filter, bool refs) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         bool on = (act >> u) & 1u;
-        if (filter) on = on && (key_hash(key[u]) >> (32 - a.lg_q)) == q;
+        const uint32_t mask_hi = kTags ? a.mask_hi : ~0u;
+        if (filter) on = on && (key_hash(tag_off(key[u], mask_hi)) >> (32 - a.lg_q)) == q;
         uint32_t slot;
-        const bool fresh = table_insert(L.tab, a.lg_slots, key[u], on, slot, &L.over);
+        // references: with all tags, so that none are added
+        const uint64_t x = refs ? key[u] | (uint64_t)~mask_hi << 32 : key[u];
+        const bool fresh = table_insert<kTags>(L.tab, a.lg_slots, x, mask_hi, on, slot, &L.over);
         if (refs) continue;
         const uint64_t m = __ballot(fresh);
         if (!m) continue;
@@ -326,6 +381,7 @@ __device__ __forceinline__ void bucket_end(BucketLds &L, const BucketArgs &a, ui
 // states (layer d's run, then layer d-1's, as one sequence), the candidates.
 // The first keys of the next stage are loaded before the present one's go
 // into the table, so that the table work covers the loads.
+template <bool kTags>
 __global__ __launch_bounds__(kBucketBlock) __attribute__((amdgpu_waves_per_eu(8))) void hash_bucket_kernel(
     BucketArgs a) {
     __shared__ BucketLds L;
@@ -379,7 +435,7 @@ __global__ __launch_bounds__(kBucketBlock) __attribute__((amdgpu_waves_per_eu(8)
                 pact = load(pre, q, stage ^ 1u, 0);
             }
             for (uint32_t b = 0;;) {
-                bucket_insert(L, a, key, act, at, stage ? a.lg_sub != 0 : filter0, stage == 0);
+                bucket_insert<kTags>(L, a, key, act, at, stage ? a.lg_sub != 0 : filter0, stage == 0);
                 b += 4 * kBucketBlock;
                 if (b >= n) break;
                 act = load(key, at, stage, b);
@@ -402,6 +458,7 @@ __global__ __launch_bounds__(kBucketBlock) __attribute__((amdgpu_waves_per_eu(8)
 // Any other step: candidates in several parts (one partition), or reference
 // layers with more buckets than this step. One block per bucket; its waves
 // take pieces in turn: 256 keys of a run, or a whole (small) run.
+template <bool kTags>
 __global__ __launch_bounds__(kBucketBlock) __attribute__((amdgpu_waves_per_eu(8))) void hash_bucket_pieces_kernel(
     BucketArgs a) {
     __shared__ BucketLds L;
@@ -446,7 +503,7 @@ __global__ __launch_bounds__(kBucketBlock) __attribute__((amdgpu_waves_per_eu(8)
                     key[u] = k < n ? p[k] : 0ull;
                     if (k < n) act |= 1u << u;
                 }
-                bucket_insert(L, a, key, act, q, filter, stage == 0);
+                bucket_insert<kTags>(L, a, key, act, q, filter, stage == 0);
             }
         }
         if (stage == 0) __syncthreads();
@@ -464,8 +521,8 @@ struct SmallLds {
     uint32_t count, over;
 };
 
-template <class G>
-__global__ __launch_bounds__(kPartBlock) void hash_small_kernel(HashSmallArgs a, G gens) {
+template <class G, bool kTags>
+__global__ __launch_bounds__(kPartBlock) void hash_small_kernel(HashSmallArgs a, G gens, HashTags tags) {
     __shared__ SmallLds L;
     const uint32_t tid = threadIdx.x;
     const uint64_t *prev = a.prev, *cur = a.cur;
@@ -490,7 +547,7 @@ __global__ __launch_bounds__(kPartBlock) void hash_small_kernel(HashSmallArgs a,
             const uint32_t n = which ? nc : np;
             for (uint32_t i = tid; i < n; i += kPartBlock) {
                 uint32_t slot;
-                (void)table_insert(L.tab, kSmallLgSlots, p[i], true, slot, &L.over);
+                (void)table_insert<false>(L.tab, kSmallLgSlots, kTags ? tag_strip(p[i], tags) : p[i], ~0u, true, slot, &L.over);
             }
         }
         __syncthreads();
@@ -506,11 +563,11 @@ __global__ __launch_bounds__(kPartBlock) void hash_small_kernel(HashSmallArgs a,
             const uint32_t w = w0 + tid, g = nc == 1 ? w : __umulhi(w, inv), f = w - g * nc;
             uint64_t s = 0, key = 0;
             if (w < work) {
-                s = cur[f];
+                s = kTags ? tag_strip(cur[f], tags) : cur[f];
                 key = gens.apply_lane(s, g);
             }
             uint32_t slot;
-            const bool fresh = table_insert(L.tab, kSmallLgSlots, key, key != s, slot, &L.over);
+            const bool fresh = table_insert<false>(L.tab, kSmallLgSlots, key, ~0u, key != s, slot, &L.over);
             const uint64_t m = __ballot(fresh);
             if (!m) continue;
             uint32_t at = 0;
@@ -546,6 +603,21 @@ __global__ __launch_bounds__(kPartBlock) void hash_small_kernel(HashSmallArgs a,
 }
 
 }  // namespace
+
+namespace {
+__global__ __launch_bounds__(256) void hash_strip_kernel(uint64_t *__restrict__ dst, const uint64_t *__restrict__ src,
+                                                         uint64_t n, HashTags t) {
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (uint64_t)gridDim.x * 256)
+        dst[i] = tag_strip(src[i], t);
+}
+}  // namespace
+
+void launch_hash_strip(uint64_t *dst, const uint64_t *src, uint64_t n, const HashTags &t, hipStream_t s) {
+    const uint64_t blocks = std::min<uint64_t>((n + 255) / 256, 4096);
+    if (!blocks) return;
+    hipLaunchKernelGGL(hash_strip_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, dst, src, n, t);
+    CG_HIP(hipGetLastError());
+}
 
 // ---- sorted small layers (for callers that read states back) -----------------------
 namespace {
@@ -649,47 +721,52 @@ void with_gens(const HashGens &g, Fn &&fn) {
 
 }  // namespace
 
-void launch_hash_partition(const HashPlan &p, const HashGens &g, const HashLayer &cur, const HashBufs &b,
-                           PipeWork &w) {
+void launch_hash_partition(const HashPlan &p, const HashGens &g, const HashTags &t, const HashLayer &cur,
+                           const HashBufs &b, PipeWork &w) {
     if (w.prof) w.prof->begin(K_EXPAND);
     PartOut<uint64_t> o{b.part1, (uint64_t)p.blocks * p.cap1, p.cap1, b.count1, p.blocks,
                         (uint32_t *)&b.counters[kHashFlags], kHashFlagPart};
     with_gens(g, [&](auto gens) {
-        hipLaunchKernelGGL((hash_expand_kernel<decltype(gens)>), dim3(p.blocks), dim3(kPartBlock), 0, w.stream,
-                           cur.keys, cur.n, gens, g.k, p.tiles, p.ranges, p.lg1, o, b.next);
+        auto kernel = t.on() ? hash_expand_kernel<decltype(gens), true> : hash_expand_kernel<decltype(gens), false>;
+        hipLaunchKernelGGL(kernel, dim3(p.blocks), dim3(kPartBlock), 0, w.stream, cur.keys, cur.n, gens, g.k, t,
+                           cur.tagged, p.tiles, p.ranges, p.lg1, o, b.next);
     });
     CG_HIP(hipGetLastError());
     if (w.prof) w.prof->end(K_EXPAND, 8.0 * (double)cur.n + 8.0 * (double)p.C, (double)p.C);
     if (p.lg2) {
         if (w.prof) w.prof->begin(K_SPLIT);
         PartOut<uint64_t> o2{b.part2, p.cap2, p.cap2, b.count2, 1, (uint32_t *)&b.counters[kHashFlags], kHashFlagPart};
-        hipLaunchKernelGGL(hash_split_kernel, dim3(1u << p.lg1), dim3(kPartBlock), 0, w.stream, b.part1, b.count1,
-                           p.blocks, p.cap1, p.lg1, p.lg2, o2);
+        hipLaunchKernelGGL(t.on() ? hash_split_kernel<true> : hash_split_kernel<false>, dim3(1u << p.lg1), dim3(kPartBlock), 0, w.stream, b.part1, b.count1,
+                           p.blocks, p.cap1, t.mask_hi, p.lg1, p.lg2, o2);
         CG_HIP(hipGetLastError());
         if (w.prof) w.prof->end(K_SPLIT, 16.0 * (double)p.C, (double)p.C);
     }
 }
 
 void launch_hash_buckets(const HashPlan &p, const HashLayer &prev, const HashLayer &cur, const HashBufs &b,
-                         uint64_t *out, uint64_t out_cap, uint64_t *out_bucket, PipeWork &w) {
+                         const HashTags &t, uint64_t *out, uint64_t out_cap, uint64_t *out_bucket, PipeWork &w) {
     if (w.prof) w.prof->begin(K_BUCKET);
-    const LayerRef A{cur.keys, cur.bucket, cur.n, cur.lg}, B{prev.keys, prev.bucket, prev.n, prev.lg};
+    const LayerRef A{cur.keys, cur.bucket, cur.n, cur.lg};
+    const LayerRef B = cur.tagged ? LayerRef{nullptr, nullptr, 0, 0} : LayerRef{prev.keys, prev.bucket, prev.n, prev.lg};
     const bool two = p.lg2 != 0;
     const uint32_t lg_q = p.lg_q();
     BucketArgs a{two ? b.part2 : b.part1, two ? b.count2 : b.count1, two ? 1u : p.blocks, two ? p.cap2 : p.cap1,
-                 lg_q, p.lg_sub, p.lg_slots, A, B, out, out_cap, out_bucket, b.counters};
+                 lg_q, p.lg_sub, p.lg_slots, t.mask_hi, A, B, out, out_cap, out_bucket, b.counters};
     if (two && A.lg <= lg_q && B.lg <= lg_q)
-        hipLaunchKernelGGL(hash_bucket_kernel, dim3(std::min(1u << lg_q, 512u)), dim3(kBucketBlock), 0, w.stream, a);
+        hipLaunchKernelGGL(t.on() ? hash_bucket_kernel<true> : hash_bucket_kernel<false>,
+                           dim3(std::min(1u << lg_q, 512u)), dim3(kBucketBlock), 0, w.stream, a);
     else
-        hipLaunchKernelGGL(hash_bucket_pieces_kernel, dim3(1u << lg_q), dim3(kBucketBlock), 0, w.stream, a);
+        hipLaunchKernelGGL(t.on() ? hash_bucket_pieces_kernel<true> : hash_bucket_pieces_kernel<false>,
+                           dim3(1u << lg_q), dim3(kBucketBlock), 0, w.stream, a);
     CG_HIP(hipGetLastError());
-    if (w.prof) w.prof->end(K_BUCKET, 8.0 * (double)(p.C + cur.n + prev.n), (double)p.C);
+    if (w.prof) w.prof->end(K_BUCKET, 8.0 * (double)(p.C + A.n + B.n), (double)p.C);
 }
 
-void launch_hash_small(const HashSmallArgs &a, const HashGens &g, PipeWork &w) {
+void launch_hash_small(const HashSmallArgs &a, const HashGens &g, const HashTags &t, PipeWork &w) {
     if (w.prof) w.prof->begin(K_SMALL);
     with_gens(g, [&](auto gens) {
-        hipLaunchKernelGGL((hash_small_kernel<decltype(gens)>), dim3(1), dim3(kPartBlock), 0, w.stream, a, gens);
+        auto kernel = t.on() ? hash_small_kernel<decltype(gens), true> : hash_small_kernel<decltype(gens), false>;
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kPartBlock), 0, w.stream, a, gens, t);
     });
     CG_HIP(hipGetLastError());
     if (w.prof) w.prof->end(K_SMALL, 0, 0);

@@ -372,6 +372,7 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
     binary_ = binary;
     const uint64_t key0 = binary ? pack_bits_host(n, spec.start) : pack_host(n, spec.start);
     Progress pg;
+    tags_ = HashTags();
     bool finished = rank_layers(spec) && run_ranked(spec, res, key0, pg);
     if (!finished) {
         const bool hashed = hash_layers(spec);

@@ -102,6 +102,7 @@ private:
     DevBuf part_[2], part_cnt_[2], tab_[3], small_[3], hctr_, ssz_, order_[2];
     class WgRunner *wg_ = nullptr;  // small-job engine (created on first use)
     static constexpr size_t kHostSmallBytes = 16384;
+    HashTags tags_;                   // of the layers that hash buckets hold now
     HostKit kit_;
     uint64_t *host_small_ = nullptr;  // of the kit: counters read back, inputs uploaded
 };

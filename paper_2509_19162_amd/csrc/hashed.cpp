@@ -67,12 +67,45 @@ uint64_t hash_layers_bytes(const JobSpec &spec) {
     return (uint64_t)(1.25 * ((double)parts + layers + 3.0 * (double)tab)) + (64ull << 20);
 }
 
-// keys[0..n) sorted, in a or b (each n keys); keys is left as it is.
+// The tags of a growth, where it can have them. (Layers that stay resident
+// hold whole keys.)
+HashTags make_tags(const JobSpec &spec) {
+    HashTags t;
+    const int n = spec.n, k = spec.k;
+    const bool implied = !spec.binary && n == 16;  // entry 0
+    const int bits = implied ? 4 : 64 - (spec.binary ? n : 4 * n);
+    if (k < 2 || k > bits || k > (int)kHashMaxTags || (spec.flags & CG_KEEP_ALL_LAYERS)) return t;
+    const int width = implied ? 4 : k;
+    for (int g = 0; g < k; ++g) {
+        const uint8_t *a = spec.gens.data() + (size_t)g * n;
+        int undo = -1;
+        for (int h = 0; h < k && undo < 0; ++h) {
+            const uint8_t *b = spec.gens.data() + (size_t)h * n;
+            bool id = true;
+            for (int i = 0; i < n && id; ++i) id = a[b[i]] == i;
+            if (id) undo = h;
+        }
+        if (undo < 0) return HashTags();  // never, in a set closed under inverses
+        t.undo[g] = 1u << (32 - width + undo);
+    }
+    t.shift = (uint32_t)(32 - width);
+    t.mask_hi = (1u << t.shift) - 1u;
+    if (implied) {
+        for (int i = 0; i < n; ++i) t.sum += spec.start[i];
+        t.sum = 16u + t.sum % 16u;
+    }
+    return t;
+}
+
+// keys[0..n) sorted, whole keys, in a or b (each n keys); keys is left as it is.
 uint64_t *Engine::sorted_copy(const JobSpec &spec, const uint64_t *keys, uint64_t n, DevBuf &a, DevBuf &b) {
     if (!w_.ready()) w_.init(stream_);
     a.ensure(std::max<uint64_t>(n, 1) * 8);
     b.ensure(std::max<uint64_t>(n, 1) * 8);
-    CG_HIP(hipMemcpyAsync(a.p, keys, n * 8, hipMemcpyDeviceToDevice, stream_));
+    if (tags_.on())
+        launch_hash_strip(a.as<uint64_t>(), keys, n, tags_, stream_);
+    else
+        CG_HIP(hipMemcpyAsync(a.p, keys, n * 8, hipMemcpyDeviceToDevice, stream_));
     return radix_sort(a.as<uint64_t>(), b.as<uint64_t>(), n, spec.binary ? 0 : 4, spec.binary ? spec.n : 4 * spec.n,
                       w_, spec.binary);
 }
@@ -143,6 +176,7 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
     gens.sel = reinterpret_cast<const GenSel *>(gsel_.as<uint8_t>() + at_sel);
     gens.term = reinterpret_cast<const BitTerm *>(gsel_.as<uint8_t>() + at_term);
     gens.first = reinterpret_cast<const uint32_t *>(gsel_.as<uint8_t>() + at_first);
+    tags_ = make_tags(spec);
 
     // two sets of counters: a step clears the other one's
     hctr_.ensure(2 * kHashCounterStride * 8);
@@ -234,7 +268,7 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
             a.out = out;
             a.state = ssz_.as<uint32_t>();
             a.sizes = ssz_.as<uint64_t>() + 1;
-            launch_hash_small(a, gens, w_);
+            launch_hash_small(a, gens, tags_, w_);
             CG_HIP(hipMemcpyAsync(host_small_, ssz_.p, 8 + kSmallMaxLayers * 8, hipMemcpyDeviceToHost, stream_));
             CG_HIP(hipStreamSynchronize(stream_));
             if (prof_.on) prof_.collect();
@@ -251,7 +285,7 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
                     throw Error(CG_E_DEVICE, "layer size out of range (device error)");
                 if (!N) break;
                 prev = cur;
-                cur = HashLayer{out + used, N, nullptr, 0};
+                cur = HashLayer{out + used, N, nullptr, 0, false};
                 used += N;
                 ++filled;
                 sizes[p.layers++] = N;
@@ -280,9 +314,9 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
         }
         expect = std::max<uint64_t>(expect, 1);
         const uint64_t most = p.np + p.F + std::min(C, room);
-        const uint64_t states = std::max(states_try, p.np + p.F + expect);
+        const uint64_t states = std::max(states_try, (cur.tagged ? 0 : p.np) + p.F + expect);
         HashPlan plan;
-        bool ok = C <= most_candidates && hash_plan(p.F, k, states, &plan);
+        bool ok = C <= most_candidates && hash_plan(p.F, cur.tagged ? k - 1 : k, states, &plan);
         HashBufs hb{};
         uint64_t *out = nullptr, out_cap = 0;
         DevBuf &out_buf = lay_[lay_at];
@@ -315,10 +349,10 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
             set ^= 1u;
             hb = {part_[0].as<uint64_t>(),     part_[1].as<uint64_t>(), part_cnt_[0].as<uint32_t>(),
                   part_cnt_[1].as<uint32_t>(), ctr,                     hctr_.as<uint64_t>() + set * kHashCounterStride};
-            launch_hash_partition(plan, gens, cur, hb, w_);
+            launch_hash_partition(plan, gens, tags_, cur, hb, w_);
             uint64_t flags = 0;
             for (int attempt = 0;; ++attempt) {
-                launch_hash_buckets(plan, prev, cur, hb, out, out_cap, tab_[tab_at].as<uint64_t>(), w_);
+                launch_hash_buckets(plan, prev, cur, hb, tags_, out, out_cap, tab_[tab_at].as<uint64_t>(), w_);
                 CG_HIP(hipMemcpyAsync(host_small_, ctr, kHashCounters * 8, hipMemcpyDeviceToHost, stream_));
                 CG_HIP(hipStreamSynchronize(stream_));
                 N = host_small_[kHashCount];
@@ -367,7 +401,7 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
             return true;
         }
         sizes[p.layers++] = N;
-        const HashLayer next{out, N, tab_[tab_at].as<uint64_t>(), plan.lg_q()};
+        const HashLayer next{out, N, tab_[tab_at].as<uint64_t>(), plan.lg_q(), tags_.on()};
         if (spec.layers_out) {
             if (p.written < spec.layers_out_cap)
                 export_layer(spec, sorted_copy(spec, out, N, order_[0], order_[1]), N, p.written);

@@ -138,7 +138,7 @@ bool Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
                 HashGens gens;
                 gens.k = k;
                 gens.sel = a.sel;
-                launch_hash_small(s, gens, w_);
+                launch_hash_small(s, gens, HashTags(), w_);
                 CG_HIP(hipMemcpyAsync(host_small_, ssz_.p, 8 + kSmallMaxLayers * 8, hipMemcpyDeviceToHost, stream_));
                 CG_HIP(hipStreamSynchronize(stream_));
                 if (prof_.on) prof_.collect();
