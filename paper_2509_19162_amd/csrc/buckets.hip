@@ -118,13 +118,13 @@ struct BitGens {
 __device__ __forceinline__ uint64_t tag_off(uint64_t key, uint32_t mask_hi) {
     return (uint64_t)((uint32_t)(key >> 32) & mask_hi) << 32 | (uint32_t)key;
 }
-// The whole key: without its tag, entry 0 of n = 16 put back.
+// The whole key: without its tags, entry 0 put back where it was left out.
 __device__ __forceinline__ uint64_t tag_strip(uint64_t key, const HashTags &t) {
     key = tag_off(key, t.mask_hi);
     if (t.sum) {
         const uint32_t lo = (uint32_t)key, hi = (uint32_t)(key >> 32), m = 0x0F0F0F0Fu;
         const uint32_t four = (lo & m) + ((lo >> 4) & m) + (hi & m) + ((hi >> 4) & m);  // bytes up to 60
-        key |= (uint64_t)(t.sum - __builtin_amdgcn_sad_u8(four, 0u, 0u)) << 60;
+        key |= (uint64_t)(((t.sum - __builtin_amdgcn_sad_u8(four, 0u, 0u)) & 15u) << t.place) << 32;
     }
     return key;
 }
@@ -132,8 +132,8 @@ __device__ __forceinline__ uint64_t tag_strip(uint64_t key, const HashTags &t) {
 // Items of (4096 frontier states) x (a range of generators), dealt to the
 // blocks in turn. The item's states stay in registers; each round maps them
 // through one generator. A candidate equal to its state is dropped here. Of
-// a tagged layer there are k - 1 rounds: in the first that would take a
-// state back it takes the last generator (if that does not).
+// a layer with all tags there are k - 1 rounds: in the first that would take
+// a state back it takes the last generator (if that does not).
 // kTags: the growth has tags (without, nothing is spent on them: the checks
 // cost the Coxeter growth of a 14-entry coset graph 9%).
 template <class G, bool kTags>
@@ -150,7 +150,8 @@ __global__ __launch_bounds__(kPartBlock) void hash_expand_kernel(const uint64_t 
     o.base += (uint64_t)blockIdx.x * o.cap;
     o.count += blockIdx.x;
     uint32_t parity = 0;
-    const uint32_t rounds = kTags && tagged ? k - 1 : k;
+    const bool swap = kTags && tagged && tags.all;
+    const uint32_t rounds = swap ? k - 1 : k;
     for (uint32_t it = blockIdx.x; it < tiles * ranges; it += gridDim.x) {
         const uint32_t tile = it / ranges, range = it - tile * ranges;
         const uint32_t g0 = (uint32_t)((uint64_t)rounds * range / ranges);
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(kPartBlock) void hash_expand_kernel(const uint64_t 
             s[j] = kTags ? tag_strip(x, tags) : x;
             back[j] = kTags && tagged ? (uint32_t)(x >> 32) >> tags.shift : 0u;
         }
-        if (kTags && tagged) {
+        if (swap) {
 #pragma unroll
             for (int j = 0; j < kPartRows; ++j) last[j] = gens.apply(s[j], k - 1);
         }
@@ -179,7 +180,7 @@ __global__ __launch_bounds__(kPartBlock) void hash_expand_kernel(const uint64_t 
                     // g takes the state back, as the first that does: -x & x is its bit
                     const uint32_t x = back[j];
                     const bool over = (x >> g) & 1u;
-                    const bool instead = over && (x & (0u - x)) >> g == 1u && !((x >> (k - 1)) & 1u);
+                    const bool instead = swap && over && (x & (0u - x)) >> g == 1u && !((x >> (k - 1)) & 1u);
                     if (instead) c[j] = last[j];
                     if (over && !instead) pend &= ~(1u << j);
                     tag[j] = instead ? tags.undo[k - 1] : tags.undo[g];
@@ -747,7 +748,7 @@ void launch_hash_buckets(const HashPlan &p, const HashLayer &prev, const HashLay
                          const HashTags &t, uint64_t *out, uint64_t out_cap, uint64_t *out_bucket, PipeWork &w) {
     if (w.prof) w.prof->begin(K_BUCKET);
     const LayerRef A{cur.keys, cur.bucket, cur.n, cur.lg};
-    const LayerRef B = cur.tagged ? LayerRef{nullptr, nullptr, 0, 0} : LayerRef{prev.keys, prev.bucket, prev.n, prev.lg};
+    const LayerRef B = cur.tagged && t.all ? LayerRef{nullptr, nullptr, 0, 0} : LayerRef{prev.keys, prev.bucket, prev.n, prev.lg};
     const bool two = p.lg2 != 0;
     const uint32_t lg_q = p.lg_q();
     BucketArgs a{two ? b.part2 : b.part1, two ? b.count2 : b.count1, two ? 1u : p.blocks, two ? p.cap2 : p.cap1,

@@ -72,10 +72,10 @@ uint64_t hash_layers_bytes(const JobSpec &spec) {
 HashTags make_tags(const JobSpec &spec) {
     HashTags t;
     const int n = spec.n, k = spec.k;
-    const bool implied = !spec.binary && n == 16;  // entry 0
-    const int bits = implied ? 4 : 64 - (spec.binary ? n : 4 * n);
-    if (k < 2 || k > bits || k > (int)kHashMaxTags || (spec.flags & CG_KEEP_ALL_LAYERS)) return t;
-    const int width = implied ? 4 : k;
+    const int left = 64 - (spec.binary ? n : 4 * n);
+    const bool implied = !spec.binary && n >= 9 && k > left;  // entry 0 (its bits are in the high word)
+    const int width = std::min({k, implied ? left + 4 : left, (int)kHashMaxTags});
+    if (k < 2 || k > (int)kHashMaxTags || 2 * width < k || (spec.flags & CG_KEEP_ALL_LAYERS)) return t;
     for (int g = 0; g < k; ++g) {
         const uint8_t *a = spec.gens.data() + (size_t)g * n;
         int undo = -1;
@@ -86,11 +86,14 @@ HashTags make_tags(const JobSpec &spec) {
             if (id) undo = h;
         }
         if (undo < 0) return HashTags();  // never, in a set closed under inverses
-        t.undo[g] = 1u << (32 - width + undo);
+        if (undo < width) t.undo[g] = 1u << (32 - width + undo);
     }
+    t.all = width == k;
     t.shift = (uint32_t)(32 - width);
     t.mask_hi = (1u << t.shift) - 1u;
     if (implied) {
+        t.place = (uint32_t)(4 * (n - 1) - 32);
+        t.mask_hi = (1u << t.place) - 1u;
         for (int i = 0; i < n; ++i) t.sum += spec.start[i];
         t.sum = 16u + t.sum % 16u;
     }
@@ -314,9 +317,10 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
         }
         expect = std::max<uint64_t>(expect, 1);
         const uint64_t most = p.np + p.F + std::min(C, room);
-        const uint64_t states = std::max(states_try, (cur.tagged ? 0 : p.np) + p.F + expect);
+        const bool all_tags = cur.tagged && tags_.all;
+        const uint64_t states = std::max(states_try, (all_tags ? 0 : p.np) + p.F + expect);
         HashPlan plan;
-        bool ok = C <= most_candidates && hash_plan(p.F, cur.tagged ? k - 1 : k, states, &plan);
+        bool ok = C <= most_candidates && hash_plan(p.F, all_tags ? k - 1 : k, states, &plan);
         HashBufs hb{};
         uint64_t *out = nullptr, out_cap = 0;
         DevBuf &out_buf = lay_[lay_at];

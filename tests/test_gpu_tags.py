@@ -1,7 +1,7 @@
 """Hash-bucket layers whose states remember the generators that take them back:
 sizes and exported layers against the sort path on the same calls. Every place
-the bits can lie (above the key, at n = 16 in entry 0's place), sets that just
-fit and that do not, repeated entries, involutions and pairs, layers that grow
+the bits can lie (above the key, in entry 0's place), sets of which all have a
+bit, some, or none, repeated entries, involutions and pairs, layers that grow
 and shrink between the one-workgroup kernel and the buckets. Exact."""
 
 import numpy as np
@@ -33,7 +33,7 @@ def test_permutations(n, fam):
 
 
 @pytest.mark.parametrize("n,counts", [(16, (8, 8)), (16, (4, 4, 4, 4)), (16, (7, 5, 2, 2)), (15, (5, 5, 5)),
-                                      (14, (3, 3, 3, 3, 2)), (11, (4, 4, 3))])
+                                      (14, (3, 3, 3, 3, 2)), (13, (4, 4, 5)), (12, (5, 5, 1, 1)), (11, (4, 4, 3))])
 @pytest.mark.parametrize("fam", ["lrx", "coxeter"])
 def test_repeated_entries(n, counts, fam):
     start = [c for c, m in enumerate(counts) for _ in range(m)]
@@ -49,7 +49,8 @@ def test_binary(n, ones, fam):
 
 
 @pytest.mark.parametrize("n,m,involutions", [(16, 1, 0), (16, 0, 2), (16, 1, 2), (16, 2, 0), (16, 2, 1), (13, 6, 0),
-                                             (13, 6, 1), (14, 4, 0), (14, 3, 3), (15, 1, 1)])
+                                             (13, 6, 1), (14, 4, 0), (14, 3, 3), (15, 1, 1), (13, 8, 0), (13, 8, 1),
+                                             (14, 6, 1), (15, 4, 1), (15, 8, 0), (15, 8, 1)])
 def test_random_sets(n, m, involutions):
     r = I.rng_for(n, seed=91 + m)
     gens = I.random_perms_with_inverses(n, m, r) + [I.random_involution(n, r) for _ in range(involutions)]
