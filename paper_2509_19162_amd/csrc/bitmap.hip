@@ -83,7 +83,7 @@ static_assert((uint64_t)kWgParts << kWgLgPart >= factorial(10), "parts cover the
 // Words of a slot: three bitmaps and the lists of neighbours (their length
 // is divided among the waves and parts).
 constexpr uint64_t kWgSlotBits = (wg_words(10) + 63) / 64 * 64;
-constexpr uint64_t kWgListWords = 512u << 10;
+constexpr uint64_t kWgListWords = 1u << 20;
 constexpr uint64_t kWgListWordsNoAlloc = 64u << 10;
 
 // ---- states of n <= 8 ------------------------------------------------------------
