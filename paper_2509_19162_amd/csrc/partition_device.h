@@ -31,12 +31,14 @@ struct PartLds {
         return sizeof(K) == 4 ? 5u : (lg > 9 ? 3u : 4u);
     }
     K buf[1u << kLgBuf];
-    uint32_t tail[kMaxDigits];   // keys taken in so far (may overshoot within a round)
+    // a ring: its first key's place (high half) and how many it holds (low
+    // half; may overshoot within a round). One word, so that a key's atomic
+    // brings both.
+    uint32_t ring[kMaxDigits];
     uint32_t head[kMaxDigits];   // keys written out so far, this round's lines included
-    // the lines to write this round: first key in buf, position in the
-    // digit's part (past its end: dropped), digit
+    // the lines to write this round: first key in buf, and where to: lines
+    // from the output's start (all ones: past the part's end, dropped)
     uint16_t line[kMaxLines];
-    uint16_t dig[kMaxLines];
     uint32_t at[kMaxLines];
     uint32_t lines[2];           // how many (by round parity)
     uint32_t more[2];            // some key of the block waits (by round parity)
@@ -72,7 +74,7 @@ struct PartShared {
 
 template <class K>
 __device__ __forceinline__ void part_begin(PartLds<K> &L, uint32_t digits) {
-    for (uint32_t i = threadIdx.x; i < digits; i += kPartBlock) L.tail[i] = L.head[i] = 0;
+    for (uint32_t i = threadIdx.x; i < digits; i += kPartBlock) L.ring[i] = L.head[i] = 0;
     if (threadIdx.x < 2) L.more[threadIdx.x] = L.lines[threadIdx.x] = 0;
     __syncthreads();
 }
@@ -89,9 +91,9 @@ __device__ __forceinline__ void part_round(PartLds<K> &L, const K (&key)[R], con
         for (int r = 0; r < R; ++r) {
             if ((pend >> r) & 1u) {
                 const uint32_t d = dig[r];
-                const uint32_t slot = atomicAdd(&L.tail[d], 1u);
-                if (slot - L.head[d] < depth) {
-                    L.buf[(d << lg_depth) + (slot & (depth - 1))] = key[r];
+                const uint32_t w = atomicAdd(&L.ring[d], 1u), n = w & 0xFFFFu;
+                if (n < depth) {
+                    L.buf[(d << lg_depth) + (((w >> 16) + n) & (depth - 1))] = key[r];
                     pend &= ~(1u << r);
                 }
             }
@@ -99,23 +101,19 @@ __device__ __forceinline__ void part_round(PartLds<K> &L, const K (&key)[R], con
         if (pend) L.more[parity] = 1;
         __syncthreads();
         for (uint32_t d = tid; d < (1u << lg); d += kPartBlock) {
-            const uint32_t head = L.head[d];
-            uint32_t have = L.tail[d] - head;
-            if (have > depth) {  // the overshoot of the keys that wait
-                have = depth;
-                L.tail[d] = head + depth;
-            }
-            const uint32_t n = have >> lg_line;
+            const uint32_t w = L.ring[d], pos = w >> 16;
+            const uint32_t have = min(w & 0xFFFFu, depth);  // less the keys that wait
+            const uint32_t n = have >> lg_line, keys = n << lg_line;
+            if (n || have != (w & 0xFFFFu)) L.ring[d] = ((pos + keys) & (depth - 1)) << 16 | (have - keys);
             if (n) {
-                const uint32_t first = atomicAdd(&L.lines[parity], n);
-                const uint32_t to = o.place(d, head, n << lg_line);
+                const uint32_t head = L.head[d], first = atomicAdd(&L.lines[parity], n);
+                const uint32_t to = o.place(d, head, keys);
                 for (uint32_t l = 0; l < n; ++l) {
-                    const uint32_t at = l << lg_line;
-                    L.line[first + l] = (uint16_t)((d << lg_depth) + ((head + at) & (depth - 1)));
-                    L.at[first + l] = to + at;
-                    L.dig[first + l] = (uint16_t)d;
+                    const uint32_t at = to + (l << lg_line);
+                    L.line[first + l] = (uint16_t)((d << lg_depth) + ((pos + (l << lg_line)) & (depth - 1)));
+                    L.at[first + l] = at < o.cap ? (uint32_t)(((uint64_t)d * o.stride + at) >> lg_line) : ~0u;
                 }
-                L.head[d] = head + (n << lg_line);
+                L.head[d] = head + keys;
             }
         }
         if (tid == 0) L.more[parity ^ 1u] = L.lines[parity ^ 1u] = 0;
@@ -123,7 +121,7 @@ __device__ __forceinline__ void part_round(PartLds<K> &L, const K (&key)[R], con
         const uint32_t nl = L.lines[parity];
         for (uint32_t i = grp; i < nl; i += kPartBlock >> lg_line) {
             const uint32_t at = L.at[i];
-            if (at < o.cap) o.base[(uint64_t)L.dig[i] * o.stride + at + sub] = L.buf[L.line[i] + sub];
+            if (at != ~0u) o.base[((uint64_t)at << lg_line) + sub] = L.buf[L.line[i] + sub];
         }
         const bool more = L.more[parity] != 0;
         parity ^= 1u;
@@ -139,9 +137,9 @@ __device__ __forceinline__ void part_end(PartLds<K> &L, uint32_t lg, const PartO
     const uint32_t lg_line = PartLds<K>::lg_line(lg);
     const uint32_t sub = threadIdx.x & ((1u << lg_line) - 1), grp = threadIdx.x >> lg_line;
     for (uint32_t d = grp; d < (1u << lg); d += kPartBlock >> lg_line) {
-        const uint32_t at = L.head[d] + sub, t = L.tail[d];
-        if (at < t && at < o.cap)
-            o.base[(uint64_t)d * o.stride + at] = L.buf[(d << lg_depth) + (at & (depth - 1))];
+        const uint32_t w = L.ring[d], n = w & 0xFFFFu, at = L.head[d] + sub, t = L.head[d] + n;
+        if (sub < n && at < o.cap)
+            o.base[(uint64_t)d * o.stride + at] = L.buf[(d << lg_depth) + (((w >> 16) + sub) & (depth - 1))];
         if (sub == 0) {
             o.count[(uint64_t)d * o.count_stride] = t < o.cap ? t : o.cap;
             if (t > o.cap) atomicOr(o.flags, o.flag);
@@ -155,15 +153,16 @@ __device__ __forceinline__ void part_end(PartLds<K> &L, uint32_t lg, const PartS
     const uint32_t lg_depth = PartLds<K>::kLgBuf - lg, depth = 1u << lg_depth;
     const uint32_t lg_line = PartLds<K>::lg_line(lg), line = 1u << lg_line;
     for (uint32_t d = threadIdx.x; d < (1u << lg); d += kPartBlock)
-        if (L.tail[d] != L.head[d]) L.at[d] = o.place(d, 0, line);
+        if (L.ring[d] & 0xFFFFu) L.at[d] = o.place(d, 0, line);
     __syncthreads();
     const uint32_t sub = threadIdx.x & (line - 1), grp = threadIdx.x >> lg_line;
     for (uint32_t d = grp; d < (1u << lg); d += kPartBlock >> lg_line) {
-        const uint32_t from = L.head[d] + sub, t = L.tail[d];
-        if (t == L.head[d]) continue;
+        const uint32_t w = L.ring[d], n = w & 0xFFFFu;
+        if (!n) continue;
         const uint32_t to = L.at[d];
         if (to < o.cap)
-            o.base[(uint64_t)d * o.stride + to + sub] = from < t ? L.buf[(d << lg_depth) + (from & (depth - 1))] : (K)~(K)0;
+            o.base[(uint64_t)d * o.stride + to + sub] =
+                sub < n ? L.buf[(d << lg_depth) + (((w >> 16) + sub) & (depth - 1))] : (K)~(K)0;
     }
 }
 
