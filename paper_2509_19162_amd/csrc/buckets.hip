@@ -700,7 +700,12 @@ bool hash_plan(uint64_t F, uint32_t k, uint64_t states, HashPlan *p) {
         p->lg1 = std::max(4u, std::min(9u, ceil_log2((states + 511) / 512)));
     } else {
         const uint32_t lg = ceil_log2((states + kHashBucket - 1) / kHashBucket);
-        p->lg1 = 9;
+        // a workgroup of the second one per digit: one per CU, where that
+        // makes buckets enough (of 8192 small ones their number is what
+        // costs: 12 ns each for their place in the layer; 14-entry coset
+        // graph under 13 swaps with 512 digits throughout 9.4 ms, now 8.0,
+        // C(32,16) binary LRX 29.5 and 28.8)
+        p->lg1 = lg <= 12 ? 8u : 9u;
         p->lg2 = std::min(kHashMaxLgDigits, std::max(4u, lg - p->lg1));
         if (lg > p->lg1 + p->lg2) p->lg_sub = lg - p->lg1 - p->lg2;
         if (p->lg_sub > kHashMaxLgSub) return false;
