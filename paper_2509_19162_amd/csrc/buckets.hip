@@ -294,7 +294,7 @@ __device__ __forceinline__ bool table_insert(uint64_t *tab, uint32_t lg, uint64_
     return fresh;
 }
 
-struct BucketLds {
+struct alignas(16) BucketLds {
     uint64_t tab[1u << kHashLgSlots];
     uint16_t list[kHashMaxNew];  // slots of the new states
     uint32_t found, over;
@@ -354,7 +354,9 @@ __device__ __forceinline__ void bucket_insert(BucketLds &L, const BucketArgs &a,
 }
 
 __device__ __forceinline__ void bucket_begin(BucketLds &L, uint32_t lg_slots) {
-    for (uint32_t i = threadIdx.x; i < (1u << lg_slots); i += kBucketBlock) L.tab[i] = kSentinel;
+    // two slots per store (lg_slots >= 9)
+    ulonglong2 *const t = reinterpret_cast<ulonglong2 *>(L.tab);
+    for (uint32_t i = threadIdx.x; i < (1u << lg_slots) / 2; i += kBucketBlock) t[i] = make_ulonglong2(kSentinel, kSentinel);
     if (threadIdx.x == 0) L.found = L.over = 0;
     __syncthreads();
 }
