@@ -850,6 +850,51 @@ void with_bm_lists_n(int n, F &&f) {
         default: f(std::integral_constant<int, 13>{}); break;
     }
 }
+// Lists are for generators that scatter. Where g leaves the last entries in
+// place, or moves late ones only, the neighbours of states with nearby ranks
+// lie in a few lines, and testing them directly takes 3 to 6 ps (S_12 under
+// all 66 transpositions 230 ms, through lists 2100; S_13 2.9 s and 7.7),
+// where scattered ones take 31 and the lists 9 to 13 (by this rule 167 ms and
+// 1.9 s; star S_13 673 -> 492, pancake 1046 -> 618, LRX 762 -> 592, against
+// direct tests of all). It depends on how near
+// the layer's ranks are: lines that 64 of them come to under g, per rank, in
+// two places, for one in 1, 4, 16 or 64 ranks in the layer.
+constexpr int kBmDensities = 4;
+struct BmSpread {
+    double at[kBmDensities];
+};
+template <int N>
+BmSpread bm_spread(const uint8_t *row) {
+    constexpr uint32_t kRanks = 64, kLgLine = 10;
+    BmSpread out;
+    for (int d = 0; d < kBmDensities; ++d) {
+        uint32_t lines = 0;
+        for (uint64_t place = 0; place < 2; ++place) {
+            const uint64_t r0 = (factorial(N) / 5 * (2 * place + 1)) / 4096 * 4096;
+            uint64_t line[kRanks];
+            for (uint32_t i = 0; i < kRanks; ++i) {
+                const uint64_t key = perm_unrank_t<N, RankOf<N>>((RankOf<N>)(r0 + ((uint64_t)i << (2 * d))));
+                uint64_t t = 0;
+                for (int j = 0; j < N; ++j) t = t << 4 | ((key >> (4 * (N - 1 - row[j]))) & 15u);
+                line[i] = (uint64_t)perm_rank_t<N, RankOf<N>>(t) >> kLgLine;
+            }
+            std::sort(line, line + kRanks);
+            lines += (uint32_t)(std::unique(line, line + kRanks) - line);
+        }
+        out.at[d] = (double)lines / (2.0 * kRanks);
+    }
+    return out;
+}
+int bm_density(uint64_t F, uint64_t S) { return 2 * F >= S ? 0 : (8 * F >= S ? 1 : (32 * F >= S ? 2 : 3)); }
+// From this many lines per neighbour on a generator goes through lists, at 13
+// ps. A direct test takes 28 ps per line, and its 95 instructions, with its
+// share of the state's 250, more of a wave the fewer of its lanes have a
+// state (0.0256 ps each when all have).
+double bm_scattered(int density, int k) {
+    constexpr double kLanes[kBmDensities] = {1.2, 1.5, 2.5, 4.0};
+    return std::max(0.0, (13.0 - (95.0 + 250.0 / k) * 0.0256 * kLanes[density]) / 28.0);
+}
+
 // From this many neighbours on a layer goes through lists: below, clearing
 // and writing back every segment (0.3 ms at n = 13) is more than the tests.
 constexpr uint64_t kBmListsMin = 1ull << 23;
@@ -1451,7 +1496,7 @@ std::string bitmask_unsupported(const JobSpec &spec) {
 uint64_t bitmask_list_bytes(const JobSpec &spec) {
     const uint64_t k = (uint64_t)spec.k;
     if (spec.max_frontier && spec.max_frontier < kBmListsMin / std::max<uint64_t>(1, k)) return 0;
-    const BmLists l = bm_lists(spec.n, spec.k);
+    const BmLists l = bm_lists(spec.n, (uint32_t)spec.k);
     return l.per_piece ? (l.words() + kBmCursors) * sizeof(uint32_t) : 0;
 }
 
@@ -1481,9 +1526,27 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     scur.ensure(sw * 4);
     snxt.ensure(sw * 4);
     cnt.ensure(64);
-    std::vector<GenSel> hs(std::max(1, 2 * k));  // the generators, then their inverses
+    // the generators, those that scatter most first, then the inverses
+    std::vector<GenSel> hs(std::max(1, 2 * k));
+    std::vector<int> order(k);
+    std::vector<BmSpread> spread(k, BmSpread{});
     for (int g = 0; g < k; ++g) {
-        const uint8_t *row = spec.gens.data() + (size_t)g * n;
+        order[g] = g;
+        if (bm_lists(n, (uint32_t)k).per_piece)
+            with_bm_lists_n(n, [&](auto NN) {
+                spread[g] = bm_spread<decltype(NN)::value>(spec.gens.data() + (size_t)g * n);
+            });
+    }
+    auto sum = [&](int g) { return spread[g].at[0] + spread[g].at[1] + spread[g].at[2] + spread[g].at[3]; };
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return sum(a) > sum(b); });
+    // how many go through lists, by the layer's density
+    int scattered[kBmDensities] = {0};
+    for (int d = 0; d < kBmDensities; ++d) {
+        for (int g = 0; g < k; ++g) scattered[d] += spread[g].at[d] >= bm_scattered(d, k);
+        scattered[d] = std::min(k, (scattered[d] + 3) / 4 * 4);  // (a round takes four)
+    }
+    for (int g = 0; g < k; ++g) {
+        const uint8_t *row = spec.gens.data() + (size_t)order[g] * n;
         uint8_t inv[16] = {0};
         for (int i = 0; i < n; ++i) inv[row[i]] = (uint8_t)i;
         hs[g] = make_gensel(n, row);
@@ -1517,7 +1580,6 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     // layers whose neighbours are fewer than its words
     const uint32_t grid_all = (uint32_t)std::min<uint64_t>((W + 63) / 64, (uint64_t)device_cus() * 32);
     BmLists L = bm_lists(n, (uint32_t)k);
-    uint64_t lists_from = kBmListsMin;
     // the lists are there from the first large layer on, if memory allows
     auto room_for_lists = [&]() {
         if (!lists.p) {
@@ -1544,13 +1606,14 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
                 status = CG_TRUNCATED;
                 break;
             }
-            const bool large = L.per_piece && F * (uint64_t)k >= lists_from;
-            // (a test costs two and a half neighbours that go through lists)
-            const bool pull =
-                F * (uint64_t)k >= W && pull_is_less(S - seen, F, before, (uint64_t)k, large ? 2.5 : 1.0);
+            const int kf = scattered[bm_density(F, S)];
+            const bool large = L.per_piece && F * (uint64_t)kf >= kBmListsMin;
+            // (a scattered test costs two and a half neighbours that go through lists)
+            const bool pull = F * (uint64_t)k >= W && pull_is_less(S - seen, F, before, (uint64_t)k,
+                                                                   large ? 1.0 + 1.5 * (double)kf / (double)k : 1.0);
             bool by_lists = large && !pull && room_for_lists();
             if (by_lists) {
-                const uint32_t pieces = (uint32_t)((F * (uint64_t)k + L.per_piece - 1) / L.per_piece);
+                const uint32_t pieces = (uint32_t)((F * (uint64_t)kf + L.per_piece - 1) / L.per_piece);
                 uint32_t *const flag = cnt.as<uint32_t>() + 2;  // after the layer's count
                 const PartShared<uint32_t> o{lists.as<uint32_t>(), (uint64_t)kBmSets * L.cap, L.cap,
                                              list_cnt.as<uint32_t>()};
@@ -1561,7 +1624,7 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
                                            list_cnt.as<uint32_t>(), (uint64_t)kBmCursors,
                                            (unsigned long long *)nullptr);
                         hipLaunchKernelGGL(bm_part_kernel<N>, dim3(kBmPartBlocks), dim3(kPartBlock), 0, s, pc, W, p,
-                                           pieces, gsel.as<const GenSel>(), (uint32_t)k, o);
+                                           pieces, gsel.as<const GenSel>(), (uint32_t)kf, o);
                         hipLaunchKernelGGL(bm_apply_kernel<N>, dim3(BmSeg<N>::kSubs << kBmLgDigits), dim3(kPartBlock),
                                            0, s, lists.as<const uint32_t>(), list_cnt.as<const uint32_t>(), L.cap,
                                            vis.as<const uint32_t>(), pn, sn, W, flag);
@@ -1570,13 +1633,22 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
                 CG_HIP(hipGetLastError());
             }
             with_bm_n(n, [&](auto NN) {
-                if (pull)
-                    hipLaunchKernelGGL(bm_pull_kernel<decltype(NN)::value>, dim3(grid_all), dim3(kBmBlock), 0, s,
-                                       vis.as<const uint32_t>(), pn, sn, W, gsel.as<const GenSel>() + k, k);
-                else
-                    hipLaunchKernelGGL(bm_expand_kernel<decltype(NN)::value>, dim3(grid), dim3(kBmBlock), 0, s,
-                                       pc, sc, vis.as<const uint32_t>(), pn, sn, W, nchunks, gsel.as<const GenSel>(),
-                                       k, by_lists ? cnt.as<const uint32_t>() + 2 : (const uint32_t *)nullptr);
+                constexpr int N = decltype(NN)::value;
+                const GenSel *const sel = gsel.as<const GenSel>();
+                auto expand = [&](int g0, int g1, const uint32_t *go) {
+                    if (g0 < g1)
+                        hipLaunchKernelGGL(bm_expand_kernel<N>, dim3(grid), dim3(kBmBlock), 0, s, pc, sc,
+                                           vis.as<const uint32_t>(), pn, sn, W, nchunks, sel + g0, g1 - g0, go);
+                };
+                if (pull) {
+                    hipLaunchKernelGGL(bm_pull_kernel<N>, dim3(grid_all), dim3(kBmBlock), 0, s,
+                                       vis.as<const uint32_t>(), pn, sn, W, sel + k, k);
+                } else if (by_lists) {
+                    expand(0, kf, cnt.as<const uint32_t>() + 2);  // if lists overran
+                    expand(kf, k, nullptr);
+                } else {
+                    expand(0, k, nullptr);
+                }
             });
             CG_HIP(hipGetLastError());
             hipLaunchKernelGGL(bm_fold_kernel, dim3(grid), dim3(kBmBlock), 0, s, vis.as<uint32_t>(), pc, sc, pn, sn,
@@ -1591,9 +1663,12 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
                                cnt.as<unsigned long long>());
             CG_HIP(hipStreamSynchronize(s));
             const uint64_t N = host_cnt[0];
-            // an orbit in few segments overruns every time: wait for layers
-            // four times as large
-            if (by_lists && (uint32_t)host_cnt[1]) lists_from = 4 * F * (uint64_t)k;
+            // an orbit in few segments, or crowded there, overruns every
+            // time: no more lists
+            if (by_lists && (uint32_t)host_cnt[1]) {
+                L.per_piece = 0;
+                lists.release();
+            }
             res->states_expanded += F;
             res->candidates += F * (uint64_t)k;
             std::swap(pc, pn);
