@@ -67,9 +67,10 @@ extern "C" {
                                     vector with repeated entries)            */
 #define CG_PROFILE 0x8u          /* record per-kernel HIP-event timings into
                                     cg_result_t.kstats                        */
-#define CG_PACKED_SORT 0x10u     /* sort candidates as packed 64-bit keys
-                                    even when n <= 12 (by default they sort
-                                    as 32-bit lexicographic ranks there)     */
+#define CG_PACKED_SORT 0x10u     /* make every layer by sorting candidates as
+                                    packed 64-bit keys (by default a rank
+                                    bitmap or hash buckets make them, or a
+                                    sort of lexicographic ranks)             */
 #define CG_BITMASK 0x20u         /* run the bitmask engine instead of the
                                     sort-based one: three bitmaps over the
                                     n! lexicographic ranks (visited, layer d,
@@ -95,10 +96,8 @@ extern "C" {
                                     graphs of the paper's section "Growth of
                                     Reversals and Transposons on binary
                                     cosets"). Implied for n > 16, up to
-                                    n = 64. Sort path only (no CG_BITMASK,
-                                    CG_SMALL_JOB, batches or queue); a
-                                    layer's candidates must fit in device
-                                    memory at once (no key-range chunks).   */
+                                    n = 64. No CG_BITMASK, CG_SMALL_JOB,
+                                    batches or queue.                        */
 
 /*
  * A growth job.

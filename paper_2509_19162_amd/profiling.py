@@ -44,8 +44,13 @@ KERNEL_SOURCES = {
     "sort_pass": ["radix_sort.hip", "device_util.h", "expand_device.h", "perm_rank.h"],
     "sort_pass_expand": ["radix_sort.hip", "device_util.h", "expand_device.h"],
     "dedup_compact": ["dedup.hip", "device_util.h", "perm_rank.h"],
-    "expand": ["radix_sort.hip", "expand.hip", "expand_device.h", "perm_rank.h"],
+    "expand": ["radix_sort.hip", "expand.hip", "buckets.hip", "rankbits.hip", "partition_device.h", "expand_device.h",
+               "perm_rank.h"],
     "digit_hist": ["radix_sort.hip", "expand_device.h"],
+    "bucket_split": ["buckets.hip", "partition_device.h"],
+    "bucket_dedup": ["buckets.hip", "rankbits.hip", "perm_rank.h"],
+    "small_layers": ["buckets.hip", "expand_device.h"],
+    "bitmap_step": ["rankbits.hip", "expand_device.h", "perm_rank.h"],
 }
 
 
