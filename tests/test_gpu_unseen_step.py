@@ -50,3 +50,23 @@ def test_orbit_in_few_segments(n, m):
     exp = api.growth_ex(11, small, max_layers=512)
     got = api.growth_ex(n, gens, max_layers=512, bitmask=True)
     assert (got.sizes, got.states_expanded, got.candidates) == (exp.sizes, exp.states_expanded, exp.candidates)
+
+
+@pytest.mark.parametrize("n", [11, 12])
+@pytest.mark.parametrize("fam", ["star", "pancake", "lrx", "all_transpositions", "cyclic_coxeter"])
+def test_scattering_and_near_generators(n, fam):
+    """Sets of which some generators go through lists and some are tested
+    directly, the lists' rounds filled with near ones, and none by lists."""
+    gens = I.family(fam, n)
+    exp = api.growth_ex(n, gens, max_layers=512)
+    got = api.growth_ex(n, gens, max_layers=512, bitmask=True)
+    assert (got.sizes, got.states_expanded, got.candidates) == (exp.sizes, exp.states_expanded, exp.candidates)
+
+
+def test_scattering_and_near_generators_13():
+    """64-bit ranks: prefix reversals of S_13, all of its states, up to the
+    known diameter 15 of the pancake graph."""
+    got = api.growth_ex(13, I.family("pancake", 13), max_layers=512, bitmask=True)
+    assert sum(got.sizes) == 6227020800 and len(got.sizes) == 16 and got.status == 0
+    ref = api.growth_ex(13, I.family("pancake", 13), max_layers=512, max_frontier=10**8)
+    assert got.sizes[: len(ref.sizes)] == ref.sizes
