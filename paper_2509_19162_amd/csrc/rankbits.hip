@@ -511,7 +511,7 @@ void launch_rb_pull(int n, const RbArgs &a, uint32_t d, uint64_t off, uint64_t F
                            to);
     });
     CG_HIP(hipGetLastError());
-    if (w.prof) w.prof->end(K_STEP, 0, 0);
+    if (w.prof) w.prof->end(K_STEP, 8.0 * (double)rb_bitmap_words(n), 0);  // both bitmaps once
 }
 
 }  // namespace cg
