@@ -136,7 +136,29 @@ void Engine::hand_to_sort(const JobSpec &spec, const HashLayer &prev, const Hash
     if (!keep_all)
         for (int i = 0; i < 2; ++i) lay_[i].swap(out[i]);
     for (DevBuf *x : {&small_[0], &small_[1], &small_[2], &tab_[0], &tab_[1], &tab_[2]}) x->release();
-    if (!keep_all) lay_[2].release();
+    if (keep_all) return;
+    lay_[2].release();
+    // The sort path's chunks take the largest free block: a layer that lies
+    // between two moves where a smaller one holds it.
+    for (int pass = 0; pass < 2; ++pass)
+        for (int i = 0; i < 2; ++i) {
+            const size_t bytes = lay_[i].bytes, largest = device_bytes_available();
+            if (bytes < (1u << 30)) continue;
+            DevBuf moved;
+            moved.stream = stream_;
+            try {
+                moved.ensure(bytes);
+            } catch (const Error &e) {
+                if (!is_nomem(e)) throw;
+                continue;
+            }
+            if (moved.in_arena && device_bytes_available() == largest) {
+                CG_HIP(hipMemcpyAsync(moved.p, lay_[i].p, bytes, hipMemcpyDeviceToDevice, stream_));
+                CG_HIP(hipStreamSynchronize(stream_));
+                lay_[i].swap(moved);
+            }
+            moved.release();
+        }
 }
 
 bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p) {
