@@ -373,7 +373,18 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
     const uint64_t key0 = binary ? pack_bits_host(n, spec.start) : pack_host(n, spec.start);
     Progress pg;
     tags_ = HashTags();
-    bool finished = rank_layers(spec) && run_ranked(spec, res, key0, pg);
+    bool finished = false;
+    if (rank_layers(spec)) {
+        try {
+            run_ranked(spec, res, key0, pg);
+            finished = true;
+        } catch (const Error &e) {
+            // too little device memory, for every layer or to read them back:
+            // again by sorting, which keeps two
+            if (e.code != CG_E_NOMEM) throw;
+            start_over(spec, res, pg);
+        }
+    }
     if (!finished) {
         const bool hashed = hash_layers(spec);
         finished = hashed && run_hashed(spec, res, key0, pg);
@@ -396,6 +407,17 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
     res->t_submit = t0;
     res->t_admit = t0;
     res->t_done = t1;
+}
+
+void Engine::start_over(const JobSpec &spec, cg_result_t *res, Progress &p) {
+    CG_HIP(hipStreamSynchronize(stream_));
+    prof_.collect();
+    release_buffers();
+    std::memset(res->layer_sizes, 0, sizeof(uint64_t) * (size_t)spec.max_layers);
+    res->layer_sizes[0] = 1;
+    res->states_expanded = res->candidates = 0;
+    tags_ = HashTags();
+    p = Progress{};
 }
 
 // The layer loop by sorting, from layer 0 or (resume) from where the hash

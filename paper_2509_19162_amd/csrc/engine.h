@@ -30,7 +30,7 @@ JobSpec canonicalize(const cg_job_t &job, bool batch);
 
 // Whether a job's layers go by hash buckets (Engine::run_hashed).
 bool hash_layers(const JobSpec &spec);
-// Whether they go over a rank bitmap (Engine::run_ranked, tried first).
+// Whether they go over a rank bitmap (Engine::run_ranked).
 bool rank_layers(const JobSpec &spec);
 // Upper bound of the device bytes a job by hash buckets makes an engine hold.
 uint64_t hash_layers_bytes(const JobSpec &spec);
@@ -72,10 +72,11 @@ private:
     // then sorted in lay_[0] and lay_[1] (keep_all: in arena_).
     bool run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p);
     // Layers over a rank bitmap (rankbits.hip): permutations of up to 12
-    // entries. False when device memory is too short: `p` is then as at the
-    // start.
-    bool run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p);
+    // entries.
+    void run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p);
     bool take_layer(const JobSpec &spec, cg_result_t *res, uint64_t N, Progress &p);
+    // As before the first layer, with no buffer held.
+    void start_over(const JobSpec &spec, cg_result_t *res, Progress &p);
     void export_ranked(const JobSpec &spec, const uint64_t *sizes, int layers);
     void run_sorted(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p, bool resume);
     void hand_to_sort(const JobSpec &spec, const HashLayer &prev, const HashLayer &cur, const Progress &p);

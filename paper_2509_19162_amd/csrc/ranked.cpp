@@ -28,8 +28,8 @@ bool rank_layers(const JobSpec &spec) {
     return !std::getenv("CG_CHUNK_CANDIDATES") && !std::getenv("CG_RANK_FULL");
 }
 
-// Reads the states of every layer back, in order: layers are sorted first
-// (small ones all in one launch, in place).
+// Reads the states of every layer back, in order: layers are sorted first,
+// in place (small ones all in one launch).
 void Engine::export_ranked(const JobSpec &spec, const uint64_t *sizes, int layers) {
     uint64_t off = 0, written = 0;
     uint64_t *all = arena_.as<uint64_t>();
@@ -45,14 +45,16 @@ void Engine::export_ranked(const JobSpec &spec, const uint64_t *sizes, int layer
         } else {
             run = sizes[d];
             e = d + 1;
-            export_layer(spec, sorted_copy(spec, all + off, run, order_[0], order_[1]), run, written);
+            if (!w_.ready()) w_.init(stream_);
+            order_[0].ensure(run * 8);
+            export_layer(spec, radix_sort(all + off, order_[0].as<uint64_t>(), run, 4, 4 * spec.n, w_), run, written);
         }
         off += run;
         d = e;
     }
 }
 
-bool Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p) {
+void Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p) {
     const int n = spec.n;
     const uint32_t k = (uint32_t)spec.k;
     uint64_t *sizes = res->layer_sizes;
@@ -103,155 +105,141 @@ bool Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
     bool unused_marked = false;  // bit numbers of no rank are marked in it
     const uint64_t words = rb_bitmap_words(n);
     bool large_ok = n >= kRbLargeMinN;
-    try {
-        room_for(n <= 10 ? orbit : std::min<uint64_t>(orbit, 1u << 20));
-        CG_HIP(hipMemcpyAsync(a.all, gsel_.p, 8, hipMemcpyDeviceToDevice, stream_));
-        bool small_ok = spec.inverse_closed;
-        for (;;) {
-            if (spec.max_frontier && p.F > spec.max_frontier) {
-                p.status = CG_TRUNCATED;
-                break;
-            }
-            if (p.layers >= spec.max_layers) {
-                p.status = CG_TRUNCATED;
-                break;
-            }
-            const uint64_t C = p.F * (uint64_t)k;
-            if (small_ok && p.np + p.F <= kSmallStates && C <= kSmallMaxCand) {
-                // small layers in one workgroup, straight behind the last one
-                ssz_.ensure(8 + kSmallMaxLayers * 8);
-                room_for(p.total + (n <= 10 ? orbit : (1u << 18)));
-                HashSmallArgs s{};
-                s.cur = a.all + p.total - p.F;
-                s.prev = a.all + p.total - p.F - p.np;
-                s.np = (uint32_t)p.np;
-                s.nc = (uint32_t)p.F;
-                s.k = k;
-                const uint64_t left = (uint64_t)(spec.max_layers - p.layers);
-                s.max_new = (uint32_t)std::min<uint64_t>(left, kSmallMaxLayers - 1);
-                s.max_new_is_rule = s.max_new == left;
-                s.max_frontier = spec.max_frontier;
-                s.out = a.all + p.total;
-                s.out_cap = a.cap - p.total;
-                s.state = ssz_.as<uint32_t>();
-                s.sizes = ssz_.as<uint64_t>() + 1;
-                HashGens gens;
-                gens.k = k;
-                gens.sel = a.sel;
-                launch_hash_small(s, gens, HashTags(), w_);
-                CG_HIP(hipMemcpyAsync(host_small_, ssz_.p, 8 + kSmallMaxLayers * 8, hipMemcpyDeviceToHost, stream_));
-                CG_HIP(hipStreamSynchronize(stream_));
-                if (prof_.on) prof_.collect();
-                const uint32_t made = ((const uint32_t *)host_small_)[0], code = ((const uint32_t *)host_small_)[1];
-                if (made > s.max_new) throw Error(CG_E_DEVICE, "small-layer count out of range (device error)");
-                for (uint32_t i = 0; i < made; ++i)
-                    if (!take_layer(spec, res, host_small_[1 + i], p)) break;
-                marked = false;
-                if (code == kSmallDone) {
-                    p.status = CG_OK;
-                    break;
-                }
-                small_ok = made != 0 && code != kSmallFull;
-                continue;
-            }
-            // a large layer takes a step of its own; smaller ones a chain of
-            // steps, as long as they are expected to stay small, whose sizes
-            // are read back together
-            bool large = large_ok && C >= kRbLargeCandidates;
-            const bool pull = large && pull_is_less(orbit - p.total, p.F, p.np, k);
-            RbPlan plan;
-            uint32_t chain = 1;
-            uint64_t most = p.F, sum = std::min(orbit, C);
-            if (!large) {
-                const uint32_t longest = (uint32_t)std::min<int>(kRbChain, spec.max_layers - p.layers);
-                const double grow = std::min((double)k, p.np ? 1.25 * (double)p.F / (double)p.np : (double)k);
-                double c = (double)C * grow;
-                // a shrinking growth is about to end
-                const uint32_t enough = p.F < p.np ? 4 : longest;
-                while (chain < std::min(longest, enough) && (!large_ok || c < (double)kRbLargeCandidates) &&
-                       (n <= 11 || sum < kRbChainStates)) {
-                    sum = std::min(orbit, sum + sum * k);
-                    c *= std::max(grow, 0.5);
-                    ++chain;
-                }
-            } else if (!pull) {
-                plan = rb_plan(p.F, k);
-                try {
-                    part_[0].ensure(plan.bytes());
-                    part_cnt_[0].ensure(plan.parts() * 4);
-                } catch (const Error &e) {
-                    if (e.code != CG_E_NOMEM) throw;
-                    part_[0].release();
-                    large = large_ok = false;
-                }
-            }
-            room_for(n <= 11 ? orbit : p.total + sum);
-            if (!marked) {
-                vis_[0].ensure(words * 4);
-                hctr_.ensure((2 * kRbWindow * kRbStride + 16) * 8);
-                a.seen = vis_[0].as<uint32_t>();
-                a.cnt = hctr_.as<uint64_t>() + 16;
-                a.off = a.cnt + kRbWindow * kRbStride;
-                a.flags = hctr_.as<uint32_t>();
-                CG_HIP(hipMemsetAsync(a.seen, 0, words * 4, stream_));
-                launch_rb_begin(n, a, (uint32_t)(p.layers - 1), p.total - p.F, p.F, stream_);
-                marked = true;
-                unused_marked = false;
-            }
-            if (pull) {
-                vis_[1].ensure(words * 4);
-                if (!unused_marked) launch_rb_mark_unused(n, a.seen, stream_);
-                unused_marked = true;
-                uint32_t *to = a.seen == vis_[0].as<uint32_t>() ? vis_[1].as<uint32_t>() : vis_[0].as<uint32_t>();
-                launch_rb_pull(n, a, (uint32_t)(p.layers - 1), p.total - p.F, p.F, a.sel + k, to, w_);
-                a.seen = to;
-            } else if (large)
-                launch_rb_large(n, a, (uint32_t)(p.layers - 1), p.total - p.F, p.F, plan, part_[0].as<uint32_t>(),
-                                part_cnt_[0].as<uint32_t>(), w_);
-            for (uint32_t i = 0; !large && i < chain; ++i) {
-                launch_rb_step(n, a, (uint32_t)(p.layers - 1) + i, most, w_);
-                most = std::min(orbit, most * k);
-            }
-            const size_t span = (16 + kRbWindow * kRbStride) * 8;
-            static_assert((16 + kRbWindow * kRbStride) * 8 <= kHostSmallBytes, "counters fit the pinned buffer");
-            CG_HIP(hipMemcpyAsync(host_small_, hctr_.p, span, hipMemcpyDeviceToHost, stream_));
+    room_for(n <= 10 ? orbit : std::min<uint64_t>(orbit, 1u << 20));
+    CG_HIP(hipMemcpyAsync(a.all, gsel_.p, 8, hipMemcpyDeviceToDevice, stream_));
+    bool small_ok = spec.inverse_closed;
+    for (;;) {
+        if (spec.max_frontier && p.F > spec.max_frontier) {
+            p.status = CG_TRUNCATED;
+            break;
+        }
+        if (p.layers >= spec.max_layers) {
+            p.status = CG_TRUNCATED;
+            break;
+        }
+        const uint64_t C = p.F * (uint64_t)k;
+        if (small_ok && p.np + p.F <= kSmallStates && C <= kSmallMaxCand) {
+            // small layers in one workgroup, straight behind the last one
+            ssz_.ensure(8 + kSmallMaxLayers * 8);
+            room_for(p.total + (n <= 10 ? orbit : (1u << 18)));
+            HashSmallArgs s{};
+            s.cur = a.all + p.total - p.F;
+            s.prev = a.all + p.total - p.F - p.np;
+            s.np = (uint32_t)p.np;
+            s.nc = (uint32_t)p.F;
+            s.k = k;
+            const uint64_t left = (uint64_t)(spec.max_layers - p.layers);
+            s.max_new = (uint32_t)std::min<uint64_t>(left, kSmallMaxLayers - 1);
+            s.max_new_is_rule = s.max_new == left;
+            s.max_frontier = spec.max_frontier;
+            s.out = a.all + p.total;
+            s.out_cap = a.cap - p.total;
+            s.state = ssz_.as<uint32_t>();
+            s.sizes = ssz_.as<uint64_t>() + 1;
+            HashGens gens;
+            gens.k = k;
+            gens.sel = a.sel;
+            launch_hash_small(s, gens, HashTags(), w_);
+            CG_HIP(hipMemcpyAsync(host_small_, ssz_.p, 8 + kSmallMaxLayers * 8, hipMemcpyDeviceToHost, stream_));
             CG_HIP(hipStreamSynchronize(stream_));
             if (prof_.on) prof_.collect();
-            const uint32_t flags = *(const uint32_t *)host_small_;
-            if (flags & kRbFlagRoom) throw Error(CG_E_DEVICE, "layer larger than its room (device error)");
-            if (flags & kRbFlagPart) {
-                // a part overran: some neighbours are missing. What was found
-                // is marked as seen, so the bitmap is built again from the
-                // layers, and no further layer goes this way.
-                large_ok = marked = false;
-                continue;
-            }
-            const uint32_t d0 = (uint32_t)(p.layers - 1);
-            bool ended = false;
-            for (uint32_t i = 0; i < chain && !ended; ++i) {
-                if (spec.max_frontier && p.F > spec.max_frontier) break;  // it was not expanded
-                ended = !take_layer(spec, res, host_small_[16 + ((d0 + i + 1) % kRbWindow) * kRbStride], p);
-            }
-            if (ended) {
+            const uint32_t made = ((const uint32_t *)host_small_)[0], code = ((const uint32_t *)host_small_)[1];
+            if (made > s.max_new) throw Error(CG_E_DEVICE, "small-layer count out of range (device error)");
+            for (uint32_t i = 0; i < made; ++i)
+                if (!take_layer(spec, res, host_small_[1 + i], p)) break;
+            marked = false;
+            if (code == kSmallDone) {
                 p.status = CG_OK;
                 break;
             }
-            small_ok = false;
+            small_ok = made != 0 && code != kSmallFull;
+            continue;
         }
-    } catch (const Error &e) {
-        if (e.code != CG_E_NOMEM) throw;
-        // too little device memory for every layer: from the start again on
-        // the sort path, which keeps two
+        // a large layer takes a step of its own; smaller ones a chain of
+        // steps, as long as they are expected to stay small, whose sizes
+        // are read back together
+        bool large = large_ok && C >= kRbLargeCandidates;
+        const bool pull = large && pull_is_less(orbit - p.total, p.F, p.np, k);
+        RbPlan plan;
+        uint32_t chain = 1;
+        uint64_t most = p.F, sum = std::min(orbit, C);
+        if (!large) {
+            const uint32_t longest = (uint32_t)std::min<int>(kRbChain, spec.max_layers - p.layers);
+            const double grow = std::min((double)k, p.np ? 1.25 * (double)p.F / (double)p.np : (double)k);
+            double c = (double)C * grow;
+            // a shrinking growth is about to end
+            const uint32_t enough = p.F < p.np ? 4 : longest;
+            while (chain < std::min(longest, enough) && (!large_ok || c < (double)kRbLargeCandidates) &&
+                   (n <= 11 || sum < kRbChainStates)) {
+                sum = std::min(orbit, sum + sum * k);
+                c *= std::max(grow, 0.5);
+                ++chain;
+            }
+        } else if (!pull) {
+            plan = rb_plan(p.F, k);
+            try {
+                part_[0].ensure(plan.bytes());
+                part_cnt_[0].ensure(plan.parts() * 4);
+            } catch (const Error &e) {
+                if (e.code != CG_E_NOMEM) throw;
+                part_[0].release();
+                large = large_ok = false;
+            }
+        }
+        room_for(n <= 11 ? orbit : p.total + sum);
+        if (!marked) {
+            vis_[0].ensure(words * 4);
+            hctr_.ensure((2 * kRbWindow * kRbStride + 16) * 8);
+            a.seen = vis_[0].as<uint32_t>();
+            a.cnt = hctr_.as<uint64_t>() + 16;
+            a.off = a.cnt + kRbWindow * kRbStride;
+            a.flags = hctr_.as<uint32_t>();
+            CG_HIP(hipMemsetAsync(a.seen, 0, words * 4, stream_));
+            launch_rb_begin(n, a, (uint32_t)(p.layers - 1), p.total - p.F, p.F, stream_);
+            marked = true;
+            unused_marked = false;
+        }
+        if (pull) {
+            vis_[1].ensure(words * 4);
+            if (!unused_marked) launch_rb_mark_unused(n, a.seen, stream_);
+            unused_marked = true;
+            uint32_t *to = a.seen == vis_[0].as<uint32_t>() ? vis_[1].as<uint32_t>() : vis_[0].as<uint32_t>();
+            launch_rb_pull(n, a, (uint32_t)(p.layers - 1), p.total - p.F, p.F, a.sel + k, to, w_);
+            a.seen = to;
+        } else if (large)
+            launch_rb_large(n, a, (uint32_t)(p.layers - 1), p.total - p.F, p.F, plan, part_[0].as<uint32_t>(),
+                            part_cnt_[0].as<uint32_t>(), w_);
+        for (uint32_t i = 0; !large && i < chain; ++i) {
+            launch_rb_step(n, a, (uint32_t)(p.layers - 1) + i, most, w_);
+            most = std::min(orbit, most * k);
+        }
+        const size_t span = (16 + kRbWindow * kRbStride) * 8;
+        static_assert((16 + kRbWindow * kRbStride) * 8 <= kHostSmallBytes, "counters fit the pinned buffer");
+        CG_HIP(hipMemcpyAsync(host_small_, hctr_.p, span, hipMemcpyDeviceToHost, stream_));
         CG_HIP(hipStreamSynchronize(stream_));
-        for (DevBuf *b : {&arena_, &vis_[0], &order_[0], &order_[1]}) b->release();
-        std::memset(sizes, 0, sizeof(uint64_t) * (size_t)spec.max_layers);
-        sizes[0] = 1;
-        res->states_expanded = res->candidates = 0;
-        p = Progress{};
-        return false;
+        if (prof_.on) prof_.collect();
+        const uint32_t flags = *(const uint32_t *)host_small_;
+        if (flags & kRbFlagRoom) throw Error(CG_E_DEVICE, "layer larger than its room (device error)");
+        if (flags & kRbFlagPart) {
+            // a part overran: some neighbours are missing. What was found
+            // is marked as seen, so the bitmap is built again from the
+            // layers, and no further layer goes this way.
+            large_ok = marked = false;
+            continue;
+        }
+        const uint32_t d0 = (uint32_t)(p.layers - 1);
+        bool ended = false;
+        for (uint32_t i = 0; i < chain && !ended; ++i) {
+            if (spec.max_frontier && p.F > spec.max_frontier) break;  // it was not expanded
+            ended = !take_layer(spec, res, host_small_[16 + ((d0 + i + 1) % kRbWindow) * kRbStride], p);
+        }
+        if (ended) {
+            p.status = CG_OK;
+            break;
+        }
+        small_ok = false;
     }
     if (spec.layers_out) export_ranked(spec, sizes, p.layers);
-    return true;
 }
 
 // Books the expansion of layer d, which found N new states. False when none.

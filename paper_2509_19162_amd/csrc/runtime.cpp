@@ -184,24 +184,6 @@ bool arena_active() {
     return it != arenas().arena.end() && it->second.base;
 }
 
-size_t device_bytes_available() {
-    const int dev = current_device();
-    {
-        std::lock_guard<std::mutex> lk(arenas().mu);
-        auto it = arenas().arena.find(dev);
-        if (it != arenas().arena.end() && it->second.base) {
-            const auto &by_len = it->second.by_len;
-            return by_len.empty() ? 0 : by_len.rbegin()->first;
-        }
-    }
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
-        (void)hipGetLastError();
-        return 0;
-    }
-    return free_b;
-}
-
 namespace {
 // bytes held by every DevBuf of the process (all devices), and the most
 // they held at once since the last reset
@@ -213,7 +195,36 @@ void count_held(uint64_t add) {
     while (now > pk && !g_peak_held.compare_exchange_weak(pk, now)) {
     }
 }
+
+// Bytes that the library's buffers may hold together: CG_DEVICE_BYTES (for
+// tests of what happens when device memory is short), no limit by default.
+uint64_t device_bytes_limit() {
+    const char *e = std::getenv("CG_DEVICE_BYTES");
+    return e ? std::strtoull(e, nullptr, 10) : ~0ull;
+}
+size_t under_limit(size_t avail) {
+    const uint64_t limit = device_bytes_limit(), held = g_held.load();
+    return (size_t)std::min<uint64_t>(avail, limit > held ? limit - held : 0);
+}
 }  // namespace
+
+size_t device_bytes_available() {
+    const int dev = current_device();
+    {
+        std::lock_guard<std::mutex> lk(arenas().mu);
+        auto it = arenas().arena.find(dev);
+        if (it != arenas().arena.end() && it->second.base) {
+            const auto &by_len = it->second.by_len;
+            return by_len.empty() ? 0 : under_limit(by_len.rbegin()->first);
+        }
+    }
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return under_limit(free_b);
+}
 
 void memory_stats(cg_memory_stats_t *out, bool reset_peak) {
     out->held_bytes = g_held.load();
@@ -238,6 +249,8 @@ bool DevBuf::ensure(size_t need, double slack) {
     if (arena_active()) want = need;  // re-carving the arena is cheap: no slack
     want = (std::max<size_t>(want, 256) + kAlign - 1) / kAlign * kAlign;
     dev = current_device();
+    if (want > under_limit(want)) want = (need + kAlign - 1) / kAlign * kAlign;
+    if (want > under_limit(want)) throw Error(CG_E_NOMEM, "beyond CG_DEVICE_BYTES");
     void *q = arena_alloc(dev, want);
     if (q) {
         in_arena = true;

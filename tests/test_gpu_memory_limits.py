@@ -1,0 +1,61 @@
+"""Growths under a limit on device memory (CG_DEVICE_BYTES): wherever the
+sort path finishes, the default engines do as well, with its results, and the
+states of the layers are the same. Tolerance: none (exact integers)."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2509_19162_amd import _native as N  # noqa: E402
+from paper_2509_19162_amd import api  # noqa: E402
+from paper_2509_19162_amd import inputs as I  # noqa: E402
+
+LIMITS_MIB = (2, 4, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 1024)
+OPTIONS = [{}, {"export_layers": 2_000_000}, {"keep_all_layers": True},
+           {"keep_all_layers": True, "export_layers": 2_000_000}]
+
+
+def _run(monkeypatch, sort_path, n, gens, **kw):
+    """The growth, or None when device memory is too short for it. Chunks of
+    any size turn the other engines off."""
+    with monkeypatch.context() as m:
+        if sort_path:
+            m.setenv("CG_CHUNK_CANDIDATES", str(10 ** 17))
+        try:
+            return api.growth_ex(n, gens, max_layers=512, **kw)
+        except api.CGError as e:
+            assert e.code == N.CG_E_NOMEM
+            return None
+
+
+def _same(got, ref):
+    assert (got.status, got.sizes, got.states_expanded, got.candidates) == (
+        ref.status, ref.sizes, ref.states_expanded, ref.candidates)
+    for a, b in zip(got.layers or [], ref.layers or []):
+        assert np.array_equal(a, b)
+
+
+def _finishes_where_sorting_does(monkeypatch, n, gens, **kw):
+    ref = _run(monkeypatch, True, n, gens, **kw)
+    finished = 0
+    for mib in LIMITS_MIB:
+        monkeypatch.setenv("CG_DEVICE_BYTES", str(api.memory_stats()["held_bytes"] + (mib << 20)))
+        by_sort = _run(monkeypatch, True, n, gens, **kw)
+        got = _run(monkeypatch, False, n, gens, **kw)
+        assert got is not None or by_sort is None, mib
+        if got is not None:
+            _same(got, ref)
+            finished += 1
+    assert finished
+
+
+@pytest.mark.parametrize("options", OPTIONS)
+@pytest.mark.parametrize("n,fam,frontier", [(10, "pancake", None), (11, "lrx", 300_000), (12, "pancake", 3_000_000)])
+def test_permutations_over_the_rank_bitmap(n, fam, frontier, options, monkeypatch):
+    _finishes_where_sorting_does(monkeypatch, n, I.family(fam, n), max_frontier=frontier, **options)
+
+
+@pytest.mark.parametrize("options", OPTIONS)
+def test_directed_permutations(options, monkeypatch):
+    _finishes_where_sorting_does(monkeypatch, 10, I.lx(10), allow_directed=True, **options)
