@@ -373,23 +373,26 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
     const uint64_t key0 = binary ? pack_bits_host(n, spec.start) : pack_host(n, spec.start);
     Progress pg;
     tags_ = HashTags();
-    bool finished = false;
-    if (rank_layers(spec)) {
+    const bool ranked = rank_layers(spec), hashed = hash_layers(spec);
+    bool finished = false, by_sort = !ranked && !hashed;
+    if (!by_sort) {
         try {
-            run_ranked(spec, res, key0, pg);
-            finished = true;
+            if (ranked) {
+                run_ranked(spec, res, key0, pg);
+                finished = true;
+            } else {
+                finished = run_hashed(spec, res, key0, pg);
+                if (!finished) run_sorted(spec, res, key0, pg, true);
+            }
         } catch (const Error &e) {
-            // too little device memory, for every layer or to read them back:
-            // again by sorting, which keeps two
+            // too little device memory, for the layers or to read them back:
+            // again by sorting, which needs least
             if (e.code != CG_E_NOMEM) throw;
             start_over(spec, res, pg);
+            by_sort = true;
         }
     }
-    if (!finished) {
-        const bool hashed = hash_layers(spec);
-        finished = hashed && run_hashed(spec, res, key0, pg);
-        if (!finished) run_sorted(spec, res, key0, pg, hashed);
-    }
+    if (by_sort) run_sorted(spec, res, key0, pg, false);
 
     CG_HIP(hipEventRecord(ev1, stream_));
     CG_HIP(hipEventSynchronize(ev1));

@@ -420,6 +420,20 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
         }
         states_try = 0;
         if (N > C || N > room) throw Error(CG_E_DEVICE, "layer size out of range (device error)");
+        if (spec.layers_out && N) {
+            try {
+                if (p.written < spec.layers_out_cap)
+                    export_layer(spec, sorted_copy(spec, out, N, order_[0], order_[1]), N, p.written);
+                else
+                    p.written += N;
+            } catch (const Error &e) {
+                // no room for the copies: the sort path, whose layers are
+                // in order, makes the layer again
+                if (!is_nomem(e)) throw;
+                hand_to_sort(spec, prev, cur, p);
+                return false;
+            }
+        }
         res->states_expanded += p.F;
         res->candidates += C;
         if (!N) {
@@ -428,12 +442,6 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
         }
         sizes[p.layers++] = N;
         const HashLayer next{out, N, tab_[tab_at].as<uint64_t>(), plan.lg_q(), tags_.on()};
-        if (spec.layers_out) {
-            if (p.written < spec.layers_out_cap)
-                export_layer(spec, sorted_copy(spec, out, N, order_[0], order_[1]), N, p.written);
-            else
-                p.written += N;
-        }
         p.total += N;
         if (keep_all) p.off.push_back(p.total);
         prev = cur;

@@ -59,3 +59,11 @@ def test_permutations_over_the_rank_bitmap(n, fam, frontier, options, monkeypatc
 @pytest.mark.parametrize("options", OPTIONS)
 def test_directed_permutations(options, monkeypatch):
     _finishes_where_sorting_does(monkeypatch, 10, I.lx(10), allow_directed=True, **options)
+
+
+@pytest.mark.parametrize("options", OPTIONS)
+@pytest.mark.parametrize("n,fam,start,frontier", [
+    (13, "lrx", None, 1_000_000), (16, "star", None, 1_000_000), (24, "lrx", [0] * 12 + [1] * 12, None),
+    (14, "coxeter", [4, 4, 3, 3, 3, 2, 2, 2, 1, 1, 1, 0, 0, 0], 1_000_000)])
+def test_layers_by_hash_buckets(n, fam, start, frontier, options, monkeypatch):
+    _finishes_where_sorting_does(monkeypatch, n, I.family(fam, n), start=start, max_frontier=frontier, **options)
