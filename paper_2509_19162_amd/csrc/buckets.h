@@ -110,7 +110,7 @@ struct HashBufs {
 // for as many.)
 void launch_hash_partition(const HashPlan &p, const HashGens &g, const HashTags &t, const HashLayer &cur,
                            const HashBufs &b, PipeWork &w);
-// dst[i] = the whole key of the state src[i].
+// dst[i] = the whole key of the state src[i] (dst may be src).
 void launch_hash_strip(uint64_t *dst, const uint64_t *src, uint64_t n, const HashTags &t, hipStream_t s);
 // Buckets: new states to out[0..out_cap) (the count in counters[kHashCount]
 // goes on past out_cap), their buckets to out_bucket[0 .. 2^lg_q).

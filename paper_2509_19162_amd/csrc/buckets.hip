@@ -611,8 +611,7 @@ __global__ __launch_bounds__(kPartBlock) void hash_small_kernel(HashSmallArgs a,
 }  // namespace
 
 namespace {
-__global__ __launch_bounds__(256) void hash_strip_kernel(uint64_t *__restrict__ dst, const uint64_t *__restrict__ src,
-                                                         uint64_t n, HashTags t) {
+__global__ __launch_bounds__(256) void hash_strip_kernel(uint64_t *dst, const uint64_t *src, uint64_t n, HashTags t) {
     for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (uint64_t)gridDim.x * 256)
         dst[i] = tag_strip(src[i], t);
 }

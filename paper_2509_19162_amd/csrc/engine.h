@@ -80,6 +80,7 @@ private:
     void export_ranked(const JobSpec &spec, const uint64_t *sizes, int layers);
     void run_sorted(const JobSpec &spec, cg_result_t *res, uint64_t key0, Progress &p, bool resume);
     void hand_to_sort(const JobSpec &spec, const HashLayer &prev, const HashLayer &cur, const Progress &p);
+    uint64_t *sort_keys(const JobSpec &spec, uint64_t *keys, uint64_t *tmp, uint64_t n);
     uint64_t *sorted_copy(const JobSpec &spec, const uint64_t *keys, uint64_t n, DevBuf &a, DevBuf &b);
     // every device buffer beside the pipeline's own (w_)
     std::vector<DevBuf *> buffers();

@@ -100,44 +100,60 @@ HashTags make_tags(const JobSpec &spec) {
     return t;
 }
 
+// keys[0..n) sorted, there or in tmp.
+uint64_t *Engine::sort_keys(const JobSpec &spec, uint64_t *keys, uint64_t *tmp, uint64_t n) {
+    if (!w_.ready()) w_.init(stream_);
+    return radix_sort(keys, tmp, n, spec.binary ? 0 : 4, spec.binary ? spec.n : 4 * spec.n, w_, spec.binary);
+}
+
 // keys[0..n) sorted, whole keys, in a or b (each n keys); keys is left as it is.
 uint64_t *Engine::sorted_copy(const JobSpec &spec, const uint64_t *keys, uint64_t n, DevBuf &a, DevBuf &b) {
-    if (!w_.ready()) w_.init(stream_);
     a.ensure(std::max<uint64_t>(n, 1) * 8);
     b.ensure(std::max<uint64_t>(n, 1) * 8);
     if (tags_.on())
         launch_hash_strip(a.as<uint64_t>(), keys, n, tags_, stream_);
     else
         CG_HIP(hipMemcpyAsync(a.p, keys, n * 8, hipMemcpyDeviceToDevice, stream_));
-    return radix_sort(a.as<uint64_t>(), b.as<uint64_t>(), n, spec.binary ? 0 : 4, spec.binary ? spec.n : 4 * spec.n,
-                      w_, spec.binary);
+    return sort_keys(spec, a.as<uint64_t>(), b.as<uint64_t>(), n);
 }
 
+// Layers d-1 and d sorted, as whole keys, each in a buffer of its own (the
+// layers that stay resident: in their place). Sorted where they lie, with
+// one more copy of one layer at a time, after all else is freed: memory is
+// short when this runs.
 void Engine::hand_to_sort(const JobSpec &spec, const HashLayer &prev, const HashLayer &cur, const Progress &p) {
     CG_HIP(hipStreamSynchronize(stream_));
-    for (DevBuf *x : {&part_[0], &part_[1], &part_cnt_[0], &part_cnt_[1], &order_[0], &order_[1]}) x->release();
+    for (DevBuf *x : {&part_[0], &part_[1], &part_cnt_[0], &part_cnt_[1], &order_[0], &order_[1], &tab_[0], &tab_[1],
+                      &tab_[2]})
+        x->release();
     const bool keep_all = (spec.flags & CG_KEEP_ALL_LAYERS) != 0;
-    DevBuf out[2], tmp;
-    for (DevBuf *x : {&out[0], &out[1], &tmp}) x->stream = stream_;
+    DevBuf own[2], tmp;
+    for (DevBuf *x : {&own[0], &own[1], &tmp}) x->stream = stream_;
+    for (int i = 0; i < 2 && !keep_all; ++i) {
+        const HashLayer &l = i ? cur : prev;
+        for (DevBuf &x : lay_)
+            if (l.n && x.p == l.keys) own[i].swap(x);
+        if (own[i].p) continue;
+        own[i].ensure(std::max<uint64_t>(l.n * 8, 64));  // (one of a run of small layers, or none)
+        if (l.n) CG_HIP(hipMemcpyAsync(own[i].p, l.keys, l.n * 8, hipMemcpyDeviceToDevice, stream_));
+    }
+    for (DevBuf *x : {&small_[0], &small_[1], &small_[2], &lay_[0], &lay_[1], &lay_[2]}) x->release();
     for (int i = 0; i < 2; ++i) {
         const HashLayer &l = i ? cur : prev;
-        if (!l.n) {
-            out[i].ensure(64);
-            continue;
-        }
-        uint64_t *r = sorted_copy(spec, l.keys, l.n, out[i], tmp);
-        if (r == tmp.as<uint64_t>()) out[i].swap(tmp);
-        if (keep_all)
-            CG_HIP(hipMemcpyAsync(arena_.as<uint64_t>() + p.off[p.off.size() - 3 + i], out[i].p, l.n * 8,
-                                  hipMemcpyDeviceToDevice, stream_));
+        if (!l.n) continue;
+        uint64_t *at = keep_all ? arena_.as<uint64_t>() + p.off[p.off.size() - 3 + i] : own[i].as<uint64_t>();
+        if (tags_.on()) launch_hash_strip(at, at, l.n, tags_, stream_);
+        tmp.release();  // (it would grow with slack)
+        tmp.ensure(l.n * 8);
+        uint64_t *r = sort_keys(spec, at, tmp.as<uint64_t>(), l.n);
+        uint64_t *to = keep_all ? at : tmp.as<uint64_t>();  // (the layer's own buffer may be far larger)
+        if (r != to) CG_HIP(hipMemcpyAsync(to, r, l.n * 8, hipMemcpyDeviceToDevice, stream_));
+        if (!keep_all) own[i].swap(tmp);
     }
     CG_HIP(hipStreamSynchronize(stream_));
     tmp.release();
-    if (!keep_all)
-        for (int i = 0; i < 2; ++i) lay_[i].swap(out[i]);
-    for (DevBuf *x : {&small_[0], &small_[1], &small_[2], &tab_[0], &tab_[1], &tab_[2]}) x->release();
     if (keep_all) return;
-    lay_[2].release();
+    for (int i = 0; i < 2; ++i) lay_[i].swap(own[i]);
     // The sort path's chunks take the largest free block: a layer that lies
     // between two moves where a smaller one holds it.
     for (int pass = 0; pass < 2; ++pass)

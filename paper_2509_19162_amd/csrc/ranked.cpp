@@ -45,9 +45,8 @@ void Engine::export_ranked(const JobSpec &spec, const uint64_t *sizes, int layer
         } else {
             run = sizes[d];
             e = d + 1;
-            if (!w_.ready()) w_.init(stream_);
             order_[0].ensure(run * 8);
-            export_layer(spec, radix_sort(all + off, order_[0].as<uint64_t>(), run, 4, 4 * spec.n, w_), run, written);
+            export_layer(spec, sort_keys(spec, all + off, order_[0].as<uint64_t>(), run), run, written);
         }
         off += run;
         d = e;

@@ -67,3 +67,12 @@ def test_directed_permutations(options, monkeypatch):
     (14, "coxeter", [4, 4, 3, 3, 3, 2, 2, 2, 1, 1, 1, 0, 0, 0], 1_000_000)])
 def test_layers_by_hash_buckets(n, fam, start, frontier, options, monkeypatch):
     _finishes_where_sorting_does(monkeypatch, n, I.family(fam, n), start=start, max_frontier=frontier, **options)
+
+
+def test_hand_over_holds_one_copy_of_a_layer(monkeypatch):
+    """C(24, 12) = 2,704,156 binary states in some 200 layers: two of these,
+    one copy and the sort path's chunks fit 5 MiB."""
+    gens, start = I.lrx(24), [0] * 12 + [1] * 12
+    ref = api.growth_ex(24, gens, max_layers=512, start=start)
+    monkeypatch.setenv("CG_DEVICE_BYTES", str(api.memory_stats()["held_bytes"] + (5 << 20)))
+    _same(api.growth_ex(24, gens, max_layers=512, start=start), ref)
