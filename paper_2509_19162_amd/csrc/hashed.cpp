@@ -291,8 +291,15 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
             uint64_t *out;
             if (keep_all) {
                 // the kernel wants room for a whole table of states, also
-                // where the orbit has fewer left
-                arena_room(std::max<uint64_t>(kSmallStates, std::min<uint64_t>(room, kSmallRun)));
+                // where the orbit has fewer left; where memory has not, the
+                // layer takes a step of its own, which wants less
+                try {
+                    arena_room(std::max<uint64_t>(kSmallStates, std::min<uint64_t>(room, kSmallRun)));
+                } catch (const Error &e) {
+                    if (!is_nomem(e)) throw;
+                    small_ok = false;
+                    continue;
+                }
                 a.prev = prev.keys;
                 a.cur = cur.keys;
                 out = arena_.as<uint64_t>() + p.total;

@@ -76,3 +76,16 @@ def test_hand_over_holds_one_copy_of_a_layer(monkeypatch):
     ref = api.growth_ex(24, gens, max_layers=512, start=start)
     monkeypatch.setenv("CG_DEVICE_BYTES", str(api.memory_stats()["held_bytes"] + (5 << 20)))
     _same(api.growth_ex(24, gens, max_layers=512, start=start), ref)
+
+
+def test_last_small_layers_without_room_for_a_run(monkeypatch):
+    """All 2,704,156 states kept in 52 MiB: the last layers are small, but
+    not even 9216 more states fit; they are not paid for with a second
+    growth by sorting (its 209 layers)."""
+    gens, start = I.lrx(24), [0] * 12 + [1] * 12
+    kw = dict(max_layers=512, start=start, keep_all_layers=True, profile=True)
+    ref = api.growth_ex(24, gens, **kw)
+    monkeypatch.setenv("CG_DEVICE_BYTES", str(api.memory_stats()["held_bytes"] + (52 << 20)))
+    got = api.growth_ex(24, gens, **kw)
+    _same(got, ref)
+    assert got.kstats.get("dedup_compact", {"launches": 0})["launches"] < 100
