@@ -116,6 +116,13 @@ int cg_test_unrank64(int n, const uint64_t *h_ranks, uint64_t count, uint64_t *h
                      int on_device, void *stream);
 
 /*
+ * Raises the error flag that the engine's sort kernels raise on a failed
+ * bounds check. Every later run of the engine that sorts has to return
+ * CG_E_DEVICE.
+ */
+int cg_test_raise_error_flag(cg_engine_t *engine);
+
+/*
  * Plain device-to-device copy of `bytes` bytes (a multiple of 16, both
  * pointers 16-byte aligned), run `repeats` times. Not part of the method:
  * the known byte count calibrates hardware traffic counters against the

@@ -205,6 +205,7 @@ SIGNATURES = [
      [ctypes.c_int, u64p, ctypes.c_uint64, u64p, ctypes.c_int, ctypes.c_void_p]),
     ("cg_test_host_expand", ctypes.c_int, [ctypes.c_int, u8p, ctypes.c_int, u64p, ctypes.c_uint64, u64p]),
     ("cg_test_host_expand_bits", ctypes.c_int, [ctypes.c_int, u8p, ctypes.c_int, u64p, ctypes.c_uint64, u64p]),
+    ("cg_test_raise_error_flag", ctypes.c_int, [ctypes.c_void_p]),
     ("cg_test_copy", ctypes.c_int,
      [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_uint64, ctypes.c_int, ctypes.c_void_p]),
     ("cg_test_layer_step", ctypes.c_int,

@@ -177,6 +177,14 @@ void cg_engine_destroy(cg_engine_t *e) {
     });
 }
 
+int cg_test_raise_error_flag(cg_engine_t *e) {
+    return guarded([&]() -> int {
+        if (!e) throw cg::Error(CG_E_INVAL, "NULL engine");
+        e->eng.raise_error_flag();
+        return CG_OK;
+    });
+}
+
 // ---- kernel-level test entry points -------------------------------------------
 
 int cg_test_pack(int n, const uint8_t *h_states, uint64_t count, uint64_t *d_keys, void *stream) {

@@ -156,6 +156,13 @@ void Engine::release_buffers() {
     w_.epoch = 0;
 }
 
+void Engine::raise_error_flag() {
+    if (!w_.ready()) w_.init(stream_);
+    *host_small_ = 1;
+    CG_HIP(hipMemcpyAsync(w_.err(), host_small_, sizeof(uint32_t), hipMemcpyHostToDevice, stream_));
+    CG_HIP(hipStreamSynchronize(stream_));
+}
+
 uint64_t Engine::read_counter() {
     // the error flag and the counter lie in one small device buffer: one
     // copy brings both
@@ -373,6 +380,7 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
     const uint64_t key0 = binary ? pack_bits_host(n, spec.start) : pack_host(n, spec.start);
     Progress pg;
     tags_ = HashTags();
+    sorted_ = false;
     const bool ranked = rank_layers(spec), hashed = hash_layers(spec);
     bool finished = false, by_sort = !ranked && !hashed;
     if (!by_sort) {
@@ -396,7 +404,9 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
 
     CG_HIP(hipEventRecord(ev1, stream_));
     CG_HIP(hipEventSynchronize(ev1));
-    if (!finished) (void)read_counter();  // surfaces an error flag raised by the last gather
+    // surfaces an error flag raised by the last gather, or by a sort of layers
+    // that were read back
+    if (!finished || sorted_) (void)read_counter();
     float ms = 0;
     CG_HIP(hipEventElapsedTime(&ms, ev0, ev1));
     (void)hipEventDestroy(ev0);

@@ -64,6 +64,8 @@ public:
     // Device bytes the engine's buffers hold now (they are kept between
     // runs); release_buffers() frees them.
     uint64_t device_bytes();
+    // Raises the error flag of the sort kernels (tests).
+    void raise_error_flag();
     void release_buffers();
 
 private:
@@ -104,6 +106,7 @@ private:
     DevBuf part_[2], part_cnt_[2], tab_[3], small_[3], hctr_, ssz_, order_[2];
     class WgRunner *wg_ = nullptr;  // small-job engine (created on first use)
     static constexpr size_t kHostSmallBytes = 16384;
+    bool sorted_ = false;             // a layer of the current run was sorted beside the sort path
     HashTags tags_;                   // of the layers that hash buckets hold now
     HostKit kit_;
     uint64_t *host_small_ = nullptr;  // of the kit: counters read back, inputs uploaded

@@ -103,6 +103,7 @@ HashTags make_tags(const JobSpec &spec) {
 // keys[0..n) sorted, there or in tmp.
 uint64_t *Engine::sort_keys(const JobSpec &spec, uint64_t *keys, uint64_t *tmp, uint64_t n) {
     if (!w_.ready()) w_.init(stream_);
+    sorted_ = true;
     return radix_sort(keys, tmp, n, spec.binary ? 0 : 4, spec.binary ? spec.n : 4 * spec.n, w_, spec.binary);
 }
 
