@@ -92,8 +92,9 @@ void run_batch_noalloc(int n_jobs, const cg_job_t *jobs, cg_result_t *results, h
 void *noalloc_scratch(int dev);
 
 // The bitmask engine: whole-device growth of one job (n <= 14, start a
-// permutation). Fills res like Engine::run. Layers are not exported.
-void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s);
+// permutation). Fills res like Engine::run. Layers are not exported. Its
+// buffers are counted in `held`.
+void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s, HeldBytes *held);
 // Device bytes it may take beyond its bitmaps (lists of neighbours).
 uint64_t bitmask_list_bytes(const JobSpec &spec);
 

@@ -1500,7 +1500,7 @@ uint64_t bitmask_list_bytes(const JobSpec &spec) {
     return l.per_piece ? (l.words() + kBmCursors) * sizeof(uint32_t) : 0;
 }
 
-void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
+void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s, HeldBytes *held) {
     const std::string why = bitmask_unsupported(spec);
     if (!why.empty()) throw Error(CG_E_INVAL, why);
     const double t0 = now_seconds();
@@ -1519,7 +1519,10 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s) {
     const uint64_t nchunks = (W + kChunkWords - 1) / kChunkWords;
     const uint64_t sw = (nchunks + 31) / 32;
     DevBuf vis, cur, nxt, scur, snxt, gsel, cnt, lists, list_cnt;
-    for (DevBuf *b : {&vis, &cur, &nxt, &scur, &snxt, &gsel, &cnt, &lists, &list_cnt}) b->stream = s;
+    for (DevBuf *b : {&vis, &cur, &nxt, &scur, &snxt, &gsel, &cnt, &lists, &list_cnt}) {
+        b->stream = s;
+        b->held = held;
+    }
     vis.ensure(W * 4);
     cur.ensure(W * 4);
     nxt.ensure(W * 4);

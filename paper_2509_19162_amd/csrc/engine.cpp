@@ -119,7 +119,8 @@ Engine::Engine(hipStream_t user_stream) {
     stream_ = user_stream ? user_stream : kit_.stream;
     host_small_ = static_cast<uint64_t *>(kit_.host);
     w_.attach(stream_);
-    for (DevBuf *b : buffers()) b->stream = stream_;
+    for (DevBuf *b : buffers()) adopt(*b);
+    for (DevBuf *b : w_.buffers()) adopt(*b);
     prof_.stream = stream_;
 }
 
@@ -283,7 +284,7 @@ uint64_t Engine::run_chunked(bool ranked, int n, const uint64_t *Ld, uint64_t F,
                                  cursor, w_);
         uint64_t nj = 0;
         auto part = std::make_unique<DevBuf>();
-        part->stream = stream_;
+        adopt(*part);
         if (ranked) {
             uint32_t *c0 = cand0_.as<uint32_t>(), *c1 = cand1_.as<uint32_t>();
             uint32_t *sorted = radix_sort32(c0, c1, c.count, 0, rank_bits, w_);
@@ -346,6 +347,7 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
     res->device_ms = 0;
     res->n_kstats = 0;
     sizes[0] = 1;
+    held_.peak = held_.now;
 
     prof_.on = (spec.flags & CG_PROFILE) != 0;
     for (int i = 0; i < K_NUM; ++i) {
@@ -355,7 +357,7 @@ void Engine::run(const JobSpec &spec, cg_result_t *res) {
     w_.prof = prof_.on ? &prof_ : nullptr;
 
     if (spec.flags & CG_BITMASK) {
-        run_bitmask(spec, res, stream_);
+        run_bitmask(spec, res, stream_, &held_);
         return;
     }
     if (spec.flags & CG_SMALL_JOB) {
@@ -612,7 +614,7 @@ void Engine::run_sorted(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
                 size_t want = std::max<size_t>(need, (size_t)(arena_.bytes * 1.5));
                 want = std::min<size_t>(want, std::max<size_t>(need, spec.orbit_bound * 8));
                 DevBuf bigger;
-                bigger.stream = stream_;
+                adopt(bigger);
                 bigger.ensure(want);
                 CG_HIP(hipMemcpyAsync(bigger.p, arena_.p, total * sizeof(uint64_t),
                                       hipMemcpyDeviceToDevice, stream_));

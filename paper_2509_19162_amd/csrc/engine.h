@@ -62,8 +62,10 @@ public:
     // Reads back one u64 counter and the kernel error flag (synchronises).
     uint64_t read_counter();
     // Device bytes the engine's buffers hold now (they are kept between
-    // runs); release_buffers() frees them.
+    // runs; release_buffers() frees them), and the most they held at once in
+    // the last run.
     uint64_t device_bytes();
+    uint64_t peak_bytes() const { return held_.peak; }
     // Raises the error flag of the sort kernels (tests).
     void raise_error_flag();
     void release_buffers();
@@ -84,6 +86,11 @@ private:
     void hand_to_sort(const JobSpec &spec, const HashLayer &prev, const HashLayer &cur, const Progress &p);
     uint64_t *sort_keys(const JobSpec &spec, uint64_t *keys, uint64_t *tmp, uint64_t n);
     uint64_t *sorted_copy(const JobSpec &spec, const uint64_t *keys, uint64_t n, DevBuf &a, DevBuf &b);
+    // a buffer of this engine: its stream, counted
+    void adopt(DevBuf &b) {
+        b.stream = stream_;
+        b.held = &held_;
+    }
     // every device buffer beside the pipeline's own (w_)
     std::vector<DevBuf *> buffers();
     void export_layer(const JobSpec &spec, const uint64_t *d_keys, uint64_t count,
@@ -96,6 +103,7 @@ private:
                          uint64_t *dst, uint64_t out_cap, uint64_t room, int in);
 
     hipStream_t stream_ = nullptr;
+    HeldBytes held_;
     PipeWork w_;
     Profiler prof_;
     DevBuf gsel_, cand0_, cand1_, lay_[3], arena_, stage_, chunk_hist_, vis_[2];

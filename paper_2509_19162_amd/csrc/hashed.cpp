@@ -129,7 +129,7 @@ void Engine::hand_to_sort(const JobSpec &spec, const HashLayer &prev, const Hash
         x->release();
     const bool keep_all = (spec.flags & CG_KEEP_ALL_LAYERS) != 0;
     DevBuf own[2], tmp;
-    for (DevBuf *x : {&own[0], &own[1], &tmp}) x->stream = stream_;
+    for (DevBuf *x : {&own[0], &own[1], &tmp}) adopt(*x);
     for (int i = 0; i < 2 && !keep_all; ++i) {
         const HashLayer &l = i ? cur : prev;
         for (DevBuf &x : lay_)
@@ -162,7 +162,7 @@ void Engine::hand_to_sort(const JobSpec &spec, const HashLayer &prev, const Hash
             const size_t bytes = lay_[i].bytes, largest = device_bytes_available();
             if (bytes < (1u << 30)) continue;
             DevBuf moved;
-            moved.stream = stream_;
+            adopt(moved);
             try {
                 moved.ensure(bytes);
             } catch (const Error &e) {
@@ -254,7 +254,7 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
         size_t want = std::max<size_t>(need, (size_t)(arena_.bytes * 1.5));
         want = std::min<size_t>(want, std::max<size_t>(need, spec.orbit_bound * 8));
         DevBuf bigger;
-        bigger.stream = stream_;
+        adopt(bigger);
         bigger.ensure(want);
         CG_HIP(hipMemcpyAsync(bigger.p, arena_.p, p.total * 8, hipMemcpyDeviceToDevice, stream_));
         CG_HIP(hipStreamSynchronize(stream_));

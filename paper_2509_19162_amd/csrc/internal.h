@@ -106,12 +106,21 @@ struct Profiler {
 // ---------------------------------------------------------------------------
 // Device scratch of the layer pipeline (owned by an Engine, grown on demand).
 // ---------------------------------------------------------------------------
+// Bytes held now by one owner's buffers, and at most since `peak` was set.
+struct HeldBytes {
+    uint64_t now = 0, peak = 0;
+    void add(uint64_t b) {
+        now += b;
+        if (now > peak) peak = now;
+    }
+};
 struct DevBuf {
     void *p = nullptr;
     size_t bytes = 0;
     int dev = 0;
     bool in_arena = false;
     hipStream_t stream = nullptr;  // the stream the owner uses the buffer on
+    HeldBytes *held = nullptr;     // the owner's count, if it keeps one
     // Grow to at least `need` bytes (contents are not kept). Returns true if
     // the buffer was reallocated. Memory comes from the device arena.
     bool ensure(size_t need, double slack = 1.0);
@@ -123,8 +132,8 @@ struct DevBuf {
     }
     void release();
     bool holds(const void *x) const { return p && x >= p && x < (const char *)p + bytes; }
-    // Exchanges the memory of two buffers (with where it came from; the
-    // streams stay with their owners).
+    // Exchanges the memory of two buffers of one owner (with where it came
+    // from; the streams stay).
     void swap(DevBuf &o) {
         std::swap(p, o.p);
         std::swap(bytes, o.bytes);

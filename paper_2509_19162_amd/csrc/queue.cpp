@@ -309,10 +309,11 @@ void cg_queue::big_loop(int lane) {
             if (!eng) eng.reset(new cg::Engine(nullptr));
             eng->run(r->spec, r->res);
             status = r->res->status;
-            held_end = eng->device_bytes();  // buffers only grow during a run
+            held_end = eng->peak_bytes();
             eng->release_buffers();
         } catch (const cg::Error &e) {
             status = e.code;
+            held_end = eng ? eng->peak_bytes() : 0;
             eng.reset();  // frees whatever the failed run held
         } catch (...) {
             status = CG_E_DEVICE;

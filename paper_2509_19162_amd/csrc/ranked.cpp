@@ -88,7 +88,7 @@ void Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
         states = std::min(states, orbit) + kSmallStates;
         if (states * 8 > arena_.bytes) {
             DevBuf bigger;
-            bigger.stream = stream_;
+            adopt(bigger);
             bigger.ensure(std::max<uint64_t>(states * 8, std::min<uint64_t>((orbit + kSmallStates) * 8,
                                                                            arena_.bytes + arena_.bytes / 2)));
             if (p.total > 1 || a.all) {

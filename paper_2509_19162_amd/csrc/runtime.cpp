@@ -272,6 +272,7 @@ bool DevBuf::ensure(size_t need, double slack) {
     p = q;
     bytes = want;
     count_held(want);
+    if (held) held->add(want);
     return true;
 }
 
@@ -290,6 +291,7 @@ void DevBuf::release() {
             (void)hipFree(p);  // a block of its own; synchronises the device
         }
         g_held.fetch_sub(bytes);
+        if (held) held->now -= bytes;
     }
     p = nullptr;
     bytes = 0;
