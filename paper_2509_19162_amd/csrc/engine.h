@@ -32,7 +32,8 @@ JobSpec canonicalize(const cg_job_t &job, bool batch);
 bool hash_layers(const JobSpec &spec);
 // Whether they go over a rank bitmap (Engine::run_ranked).
 bool rank_layers(const JobSpec &spec);
-// Upper bound of the device bytes a job by hash buckets makes an engine hold.
+// Upper bounds of the device bytes a job by either makes an engine hold.
+uint64_t rank_layers_bytes(const JobSpec &spec);
 uint64_t hash_layers_bytes(const JobSpec &spec);
 
 double now_seconds();

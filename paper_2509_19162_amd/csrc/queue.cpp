@@ -60,7 +60,8 @@ uint64_t factorial_u64(int n) {
 // states and an expanded one at most min(orbit, max_frontier), so the
 // candidates of one step are at most k * F. Buffers may grow with 50%
 // slack; 64 MiB covers the fixed ones. Bitmask engine: its three bitmaps
-// and their summaries, and the lists of its large layers.
+// and their summaries, and the lists of its large layers. (The rank bitmap
+// and the hash buckets have bounds of their own.)
 uint64_t job_bound(const JobSpec &s) {
     const double k = (double)std::max(1, s.k);
     const double orbit = (double)s.orbit_bound;
@@ -491,8 +492,10 @@ int cg_queue_submit(cg_queue_t *q, const cg_job_t *job, cg_result_t *res_slot, u
     if (r->big && r->spec.n >= 12 && !(r->spec.flags & CG_PACKED_SORT) && cg::bitmask_unsupported(r->spec).empty()) {
         r->spec.flags |= CG_BITMASK;
         r->bound = cg::job_bound(r->spec);
-    } else if (r->big && !cg::rank_layers(r->spec) && cg::hash_layers(r->spec)) {
-        // partitions and tables on top of what the sort path may still need
+    } else if (r->big && cg::rank_layers(r->spec)) {
+        // (the sort path may take over in either)
+        r->bound = std::max(r->bound, cg::rank_layers_bytes(r->spec));
+    } else if (r->big && cg::hash_layers(r->spec)) {
         r->bound = std::max(r->bound, cg::hash_layers_bytes(r->spec));
     }
     *ticket = r->ticket;

@@ -18,9 +18,51 @@ namespace {
 // launches and a read-back of their own cost about 30 us.
 constexpr uint64_t kRbLargeCandidates = 1u << 20;
 // States a chain of steps may add where the layer array grows on demand.
-constexpr uint64_t kRbChainStates = 1u << 24;
+constexpr uint64_t kRbChainStates = 1u << 22;
+// Room the layer array starts with (whole orbits up to n = 10).
+constexpr uint64_t kRbFirstStates = 1u << 22, kRbFirstStates12 = 1u << 20;
+// States from which a growth on S_11 that no stop rule cuts is taken to reach
+// the whole group: the array is reserved at once (319 MB), chains need not
+// heed its length.
+constexpr uint64_t kRbWholeFrom = 4096;
+
+// States a growth can record before a stop rule ends it.
+uint64_t most_states(const JobSpec &spec) {
+    const uint64_t orbit = spec.orbit_bound, k = (uint64_t)spec.k;
+    uint64_t total = 1, F = 1;
+    for (uint64_t left = (uint64_t)spec.max_layers - 1; left && total < orbit; --left) {
+        const uint64_t next = std::min(orbit, k * (spec.max_frontier ? std::min(F, spec.max_frontier) : F));
+        if (next == F) return std::min(orbit, total + left * next);
+        total += next;
+        F = next;
+    }
+    return std::min(total, orbit);
+}
+bool takes_whole(const JobSpec &spec) {
+    return spec.n <= 11 && !spec.max_frontier && most_states(spec) == spec.orbit_bound;
+}
 
 }  // namespace
+
+// The layer array (while it grows: the old one beside the new), the bitmaps,
+// the partition at every frontier size, one layer's copy and rows to read
+// states back.
+uint64_t rank_layers_bytes(const JobSpec &spec) {
+    const uint64_t orbit = spec.orbit_bound, k = (uint64_t)std::max(1, spec.k), most = most_states(spec);
+    const uint64_t fmax = spec.max_frontier ? std::min(orbit, spec.max_frontier) : orbit;
+    const uint64_t layer = std::min(most, k * fmax), room = most + kSmallStates;
+    uint64_t b = 8 * room;
+    if (spec.n > 10) b += takes_whole(spec) ? 8 * (kRbFirstStates + kSmallStates) : 8 * room;
+    b += (spec.n >= kRbLargeMinN ? 2 : 1) * 4 * rb_bitmap_words(spec.n);
+    uint64_t parts = 0;
+    for (uint64_t F = std::min(fmax, most); spec.n >= kRbLargeMinN && F * k >= kRbLargeCandidates; F /= 2) {
+        const RbPlan p = rb_plan(F, (uint32_t)k);
+        parts = std::max(parts, p.bytes() + 4 * p.parts());
+    }
+    b += parts + parts / 2;
+    if (spec.layers_out) b += 8 * layer + 2 * (uint64_t)spec.n * std::min(layer, spec.layers_out_cap);
+    return b + (64ull << 20);
+}
 
 bool rank_layers(const JobSpec &spec) {
     if (spec.k == 0 || spec.binary || spec.n > kRbMaxN || !start_is_permutation(spec)) return false;
@@ -84,12 +126,14 @@ void Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
     a.k = k;
     a.max_frontier = spec.max_frontier;
     // room for `states` states in all; what is there is kept
+    const uint64_t cut = most_states(spec);
+    const bool whole_ok = takes_whole(spec);
     auto room_for = [&](uint64_t states) {
-        states = std::min(states, orbit) + kSmallStates;
+        states = std::min(states, cut) + kSmallStates;
         if (states * 8 > arena_.bytes) {
             DevBuf bigger;
             adopt(bigger);
-            bigger.ensure(std::max<uint64_t>(states * 8, std::min<uint64_t>((orbit + kSmallStates) * 8,
+            bigger.ensure(std::max<uint64_t>(states * 8, std::min<uint64_t>((cut + kSmallStates) * 8,
                                                                            arena_.bytes + arena_.bytes / 2)));
             if (p.total > 1 || a.all) {
                 CG_HIP(hipMemcpyAsync(bigger.p, arena_.p, p.total * 8, hipMemcpyDeviceToDevice, stream_));
@@ -104,7 +148,7 @@ void Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
     bool unused_marked = false;  // bit numbers of no rank are marked in it
     const uint64_t words = rb_bitmap_words(n);
     bool large_ok = n >= kRbLargeMinN;
-    room_for(n <= 10 ? orbit : std::min<uint64_t>(orbit, 1u << 20));
+    room_for(n <= 10 ? kRbFirstStates : kRbFirstStates12);
     CG_HIP(hipMemcpyAsync(a.all, gsel_.p, 8, hipMemcpyDeviceToDevice, stream_));
     bool small_ok = spec.inverse_closed;
     for (;;) {
@@ -120,7 +164,7 @@ void Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
         if (small_ok && p.np + p.F <= kSmallStates && C <= kSmallMaxCand) {
             // small layers in one workgroup, straight behind the last one
             ssz_.ensure(8 + kSmallMaxLayers * 8);
-            room_for(p.total + (n <= 10 ? orbit : (1u << 18)));
+            room_for(p.total + (1u << 18));
             HashSmallArgs s{};
             s.cur = a.all + p.total - p.F;
             s.prev = a.all + p.total - p.F - p.np;
@@ -162,15 +206,18 @@ void Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
         RbPlan plan;
         uint32_t chain = 1;
         uint64_t most = p.F, sum = std::min(orbit, C);
+        const bool whole = n <= 10 || (whole_ok && p.total >= kRbWholeFrom);
         if (!large) {
             const uint32_t longest = (uint32_t)std::min<int>(kRbChain, spec.max_layers - p.layers);
             const double grow = std::min((double)k, p.np ? 1.25 * (double)p.F / (double)p.np : (double)k);
             double c = (double)C * grow;
             // a shrinking growth is about to end
             const uint32_t enough = p.F < p.np ? 4 : longest;
-            while (chain < std::min(longest, enough) && (!large_ok || c < (double)kRbLargeCandidates) &&
-                   (n <= 11 || sum < kRbChainStates)) {
-                sum = std::min(orbit, sum + sum * k);
+            uint64_t last = sum;  // states of the chain's last layer at most
+            while (chain < std::min(longest, enough) && (!large_ok || c < (double)kRbLargeCandidates)) {
+                last = std::min(orbit, k * (spec.max_frontier ? std::min(last, spec.max_frontier) : last));
+                if (!whole && sum + last > kRbChainStates) break;
+                sum = std::min(orbit, sum + last);
                 c *= std::max(grow, 0.5);
                 ++chain;
             }
@@ -185,7 +232,7 @@ void Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
                 large = large_ok = false;
             }
         }
-        room_for(n <= 11 ? orbit : p.total + sum);
+        room_for(whole ? orbit : p.total + sum);
         if (!marked) {
             vis_[0].ensure(words * 4);
             hctr_.ensure((2 * kRbWindow * kRbStride + 16) * 8);

@@ -28,3 +28,19 @@ def test_peak_held_is_what_was_held(n, fam, frontier, candidates, monkeypatch):
     # (the lanes make their fixed buffers before or after `base` is read)
     assert abs(st["peak_held_bytes"] - held) <= FIXED
     assert st["over_bound"] == 0
+
+
+@pytest.mark.parametrize("n,fam,kw", [
+    (11, "lrx", {"max_frontier": 100_000}), (11, "lrx", {"max_frontier": 20_000}), (11, "star", {"max_frontier": 5_000}),
+    (11, "coxeter", {"max_layers": 20}), (11, "pancake", {}), (10, "star", {"max_frontier": 1_000}), (10, "reversals", {}),
+    (11, "lx", {"allow_directed": True, "max_frontier": 50_000})])
+def test_rank_bitmap_jobs_stay_within_their_charge(n, fam, kw):
+    gens = I.lx(n) if fam == "lx" else I.family(fam, n)
+    kw = dict({"max_layers": 256}, **kw)
+    with api.GrowthQueue() as q:
+        r = q.wait(q.submit(n, gens, **kw), timeout_s=120)
+        st = q.stats()
+    assert st["over_bound"] == 0
+    assert st["peak_held_bytes"] <= st["peak_charged_bytes"] + FIXED
+    ref = api.growth_ex(n, gens, packed_sort=True, **kw)
+    assert (r.sizes, r.status) == (ref.sizes, ref.status)
