@@ -24,10 +24,13 @@ void hip_check(hipError_t e, const char *what, const char *file, int line) {
 
 // ---------------------------------------------------------------------------
 // Device arena. On this HIP runtime a hipMalloc is fast while little memory is
-// held, but a large one takes seconds once tens of GB are already held. So
-// the first large request reserves one big region (CG_ARENA_FRACTION of the
-// free memory, default 0.85; 0 disables it) and every buffer is carved out
-// of it: best fit, split on allocation, coalesced on free. A range is
+// held, but a large one takes seconds (245 GB: 1.3 to 6 s), and so do later
+// ones once tens of GB are held. So buffers are carved out of regions that
+// the library reserves: a first one of 4 GiB (0.3 ms), with the first request
+// of 16 MiB or more, and one of most of the device's memory
+// (CG_ARENA_FRACTION of what is free, default 0.85; 0 disables both) once
+// something does not fit there. Best fit, split on allocation, coalesced on
+// free. A range is
 // freed only after its owner's stream has drained, so work still queued on
 // the old stream never races with a new owner. Requests the arena cannot
 // hold fall back to plain hipMalloc/hipFree.
@@ -35,54 +38,85 @@ void hip_check(hipError_t e, const char *what, const char *file, int line) {
 namespace {
 
 constexpr size_t kAlign = 1u << 16;
-constexpr size_t kArenaMinRequest = 64u << 20;  // smaller buffers also use it once it exists
+constexpr size_t kArenaMinRequest = 16u << 20;  // smaller buffers also use it once it exists
+constexpr size_t kArenaFirst = 4ull << 30;
 
 struct Arena {
-    char *base = nullptr;
-    size_t size = 0;
-    bool tried = false;
+    struct Region {
+        char *base;
+        size_t size;
+    };
+    std::vector<Region> regions;
+    bool tried = false;     // the large region was asked for
     bool external = false;  // the caller's memory (cg_set_workspace): never freed here
-    std::map<size_t, size_t> by_off;            // free ranges: offset -> length
-    std::multimap<size_t, size_t> by_len;       // free ranges: length -> offset
+    std::map<char *, size_t> by_place;       // free ranges: start -> length
+    std::multimap<size_t, char *> by_len;    // free ranges: length -> start
     size_t used = 0;
 
-    void insert_free(size_t off, size_t len) {
-        auto nx = by_off.lower_bound(off);
-        if (nx != by_off.end() && off + len == nx->first) {  // merge with the next range
+    bool active() const { return !regions.empty(); }
+    size_t reserved() const {
+        size_t n = 0;
+        for (const Region &r : regions) n += r.size;
+        return n;
+    }
+    bool holds(const char *p) const {
+        for (const Region &r : regions)
+            if (p >= r.base && p < r.base + r.size) return true;
+        return false;
+    }
+    // (ranges of neighbouring regions stay apart)
+    bool starts_region(const char *p) const {
+        for (const Region &r : regions)
+            if (p == r.base) return true;
+        return false;
+    }
+    void add_region(char *base, size_t size) {
+        regions.push_back({base, size});
+        insert_free(base, size);
+    }
+    void insert_free(char *at, size_t len) {
+        auto nx = by_place.lower_bound(at);
+        if (nx != by_place.end() && at + len == nx->first && !starts_region(nx->first)) {  // merge with the next range
             erase_len(nx->second, nx->first);
             len += nx->second;
-            nx = by_off.erase(nx);
+            nx = by_place.erase(nx);
         }
-        if (nx != by_off.begin()) {
+        if (nx != by_place.begin()) {
             auto pv = std::prev(nx);
-            if (pv->first + pv->second == off) {  // merge with the previous range
+            if (pv->first + pv->second == at && !starts_region(at)) {  // merge with the previous range
                 erase_len(pv->second, pv->first);
-                off = pv->first;
+                at = pv->first;
                 len += pv->second;
-                by_off.erase(pv);
+                by_place.erase(pv);
             }
         }
-        by_off[off] = len;
-        by_len.emplace(len, off);
+        by_place[at] = len;
+        by_len.emplace(len, at);
     }
-    void erase_len(size_t len, size_t off) {
+    void erase_len(size_t len, char *at) {
         auto r = by_len.equal_range(len);
         for (auto it = r.first; it != r.second; ++it)
-            if (it->second == off) {
+            if (it->second == at) {
                 by_len.erase(it);
                 return;
             }
     }
-    bool take(size_t len, size_t &off) {
+    char *take(size_t len) {
         auto it = by_len.lower_bound(len);
-        if (it == by_len.end()) return false;
-        const size_t flen = it->first, foff = it->second;
+        if (it == by_len.end()) return nullptr;
+        const size_t flen = it->first;
+        char *const at = it->second;
         by_len.erase(it);
-        by_off.erase(foff);
-        if (flen > len) insert_free(foff + len, flen - len);
-        off = foff;
+        by_place.erase(at);
+        if (flen > len) insert_free(at + len, flen - len);
         used += len;
-        return true;
+        return at;
+    }
+    // hipFree of every region; none may be in use
+    void free_regions() {
+        if (!external)
+            for (const Region &r : regions) (void)hipFree(r.base);
+        *this = Arena{};
     }
 };
 
@@ -113,36 +147,37 @@ double arena_fraction() {
 void *arena_alloc(int dev, size_t len) {
     std::lock_guard<std::mutex> lk(arenas().mu);
     Arena &A = arenas().arena[dev];
-    if (!A.base) {
-        if (A.tried || len < kArenaMinRequest) return nullptr;
+    if (char *p = A.take(len)) return p;
+    if (A.tried || (!A.active() && len < kArenaMinRequest)) return nullptr;
+    const double frac = arena_fraction();
+    size_t free_b = 0, total_b = 0;
+    if (frac <= 0 || hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
         A.tried = true;
-        const double frac = arena_fraction();
-        size_t free_b = 0, total_b = 0;
-        if (frac <= 0 || hipMemGetInfo(&free_b, &total_b) != hipSuccess) return nullptr;
-        size_t want = (size_t)((double)free_b * frac) / kAlign * kAlign;
-        void *p = nullptr;
-        if (want < len || hipMalloc(&p, want) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        A.base = (char *)p;
-        A.size = want;
-        A.insert_free(0, want);
+        return nullptr;
     }
-    size_t off = 0;
-    if (!A.take(len, off)) return nullptr;
-    return A.base + off;
+    // of the large region: its share of what is free, the first one included
+    const size_t first = A.reserved(), share = (size_t)((double)(free_b + first) * frac);
+    size_t want = (share > first ? share - first : 0) / kAlign * kAlign;
+    if (!A.active() && len <= kArenaFirst / 4 && want > kArenaFirst)
+        want = kArenaFirst;
+    else
+        A.tried = true;
+    void *p = nullptr;
+    if (want < len || hipMalloc(&p, want) != hipSuccess) {
+        (void)hipGetLastError();
+        A.tried = true;
+        return nullptr;
+    }
+    A.add_region((char *)p, want);
+    return A.take(len);
 }
 
 bool arena_free(int dev, void *p, size_t len) {
     std::lock_guard<std::mutex> lk(arenas().mu);
     auto it = arenas().arena.find(dev);
-    if (it == arenas().arena.end() || !it->second.base) return false;
-    Arena &A = it->second;
-    char *c = (char *)p;
-    if (c < A.base || c >= A.base + A.size) return false;
-    A.insert_free((size_t)(c - A.base), len);
-    A.used -= len;
+    if (it == arenas().arena.end() || !it->second.holds((char *)p)) return false;
+    it->second.insert_free((char *)p, len);
+    it->second.used -= len;
     return true;
 }
 
@@ -152,9 +187,8 @@ void release_cached_device_memory() {
     std::lock_guard<std::mutex> lk(arenas().mu);
     for (auto &kv : arenas().arena) {
         Arena &A = kv.second;
-        if (!A.base || A.used || A.external) continue;  // in use, or the caller's
-        (void)hipFree(A.base);
-        A = Arena{};
+        if (!A.active() || A.used || A.external) continue;  // in use, or the caller's
+        A.free_regions();
     }
 }
 
@@ -162,26 +196,23 @@ void set_workspace(void *p, size_t bytes) {
     const int dev = current_device();
     std::lock_guard<std::mutex> lk(arenas().mu);
     Arena &A = arenas().arena[dev];
-    if (A.base && A.used) throw Error(CG_E_BUSY, "device buffers still live in the current workspace");
-    if (A.base && !A.external) (void)hipFree(A.base);
-    A = Arena{};
+    if (A.used) throw Error(CG_E_BUSY, "device buffers still live in the current workspace");
+    A.free_regions();
     if (!p) return;  // back to memory the library reserves itself
     const uintptr_t lo = ((uintptr_t)p + 255) & ~(uintptr_t)255;
     const size_t skip = (size_t)(lo - (uintptr_t)p);
     if (bytes <= skip + kAlign) throw Error(CG_E_INVAL, "workspace smaller than 64 KiB");
     const size_t size = (bytes - skip) / kAlign * kAlign;
-    A.base = (char *)lo;
-    A.size = size;
     A.external = true;
     A.tried = true;
-    A.insert_free(0, size);
+    A.add_region((char *)lo, size);
 }
 
 bool arena_active() {
     const int dev = current_device();
     std::lock_guard<std::mutex> lk(arenas().mu);
     auto it = arenas().arena.find(dev);
-    return it != arenas().arena.end() && it->second.base;
+    return it != arenas().arena.end() && it->second.active();
 }
 
 namespace {
@@ -210,20 +241,26 @@ size_t under_limit(size_t avail) {
 
 size_t device_bytes_available() {
     const int dev = current_device();
+    size_t free_b = 0, total_b = 0, largest = 0;
+    bool tried = false, active = false;
     {
         std::lock_guard<std::mutex> lk(arenas().mu);
         auto it = arenas().arena.find(dev);
-        if (it != arenas().arena.end() && it->second.base) {
-            const auto &by_len = it->second.by_len;
-            return by_len.empty() ? 0 : under_limit(by_len.rbegin()->first);
+        if (it != arenas().arena.end() && it->second.active()) {
+            const Arena &A = it->second;
+            largest = A.by_len.empty() ? 0 : A.by_len.rbegin()->first;
+            tried = A.tried;
+            active = true;
         }
     }
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
-        (void)hipGetLastError();
-        return 0;
+    if (!tried) {
+        if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+            (void)hipGetLastError();
+            free_b = 0;
+        }
+        largest = std::max(largest, active ? (size_t)((double)free_b * arena_fraction()) : free_b);
     }
-    return under_limit(free_b);
+    return under_limit(largest);
 }
 
 void memory_stats(cg_memory_stats_t *out, bool reset_peak) {
@@ -233,7 +270,7 @@ void memory_stats(cg_memory_stats_t *out, bool reset_peak) {
     {
         std::lock_guard<std::mutex> lk(arenas().mu);
         for (auto &kv : arenas().arena)
-            if (kv.second.base && !kv.second.external) reserved += kv.second.size;
+            if (!kv.second.external) reserved += kv.second.reserved();
     }
     out->arena_bytes = reserved;
     if (reset_peak) g_peak_held.store(g_held.load());
