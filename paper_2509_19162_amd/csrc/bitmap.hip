@@ -84,7 +84,26 @@ static_assert((uint64_t)kWgParts << kWgLgPart >= factorial(10), "parts cover the
 // is divided among the waves and parts).
 constexpr uint64_t kWgSlotBits = (wg_words(10) + 63) / 64 * 64;
 constexpr uint64_t kWgListWords = 1u << 20;
-constexpr uint64_t kWgListWordsNoAlloc = 64u << 10;
+constexpr uint64_t kWgListWordsLeast = 24u << 10;
+// Slots for `jobs` of n = 10 in `words` words: as many as short lists leave
+// room for, the jobs in rounds of equal length, and the lists as long as
+// these slots leave room for. (In 64 MiB, S_10 by two random generators and
+// their inverses: 35 jobs 44 ms in two rounds of 29 slots with 65536 words of
+// lists, 25 in one round; 46 jobs 48 ms in one round with 16384 words, 42 in
+// two.)
+struct WgSlots {
+    uint32_t slots = 0;
+    uint64_t words = 0;  // of a slot
+};
+WgSlots wg_slots(uint64_t words, uint32_t jobs, uint32_t blocks) {
+    WgSlots s;
+    const uint64_t fit = std::min<uint64_t>({words / (3 * kWgSlotBits + kWgListWordsLeast), jobs, blocks});
+    if (!fit) return s;
+    const uint64_t rounds = (jobs + fit - 1) / fit;
+    s.slots = (uint32_t)((jobs + rounds - 1) / rounds);
+    s.words = std::min(words / s.slots / 64 * 64, 3 * kWgSlotBits + kWgListWords);
+    return s;
+}
 
 // ---- states of n <= 8 ------------------------------------------------------------
 // A state is eight bytes, entry i in byte i (of fewer than eight entries the
@@ -1361,17 +1380,23 @@ WgTuning tune_wg(std::vector<WgItem> &sample, WgRunner &r, double *best_ms_out) 
 namespace {
 
 constexpr size_t na_align(size_t x) { return (x + 255) & ~(size_t)255; }
-// layout of the scratch array
-constexpr size_t kNaOffTicket = 0;  // three uint32 queue tickets
-constexpr size_t kNaOffOuts = 256;
-constexpr size_t kNaOffJobs = na_align(kNaOffOuts + sizeof(WgOutDev) * kNoAllocMaxJobs);
-constexpr size_t kNaOffGsel = na_align(kNaOffJobs + sizeof(WgJobDev) * kNoAllocMaxJobs);
-constexpr size_t kNaOffSizes = na_align(kNaOffGsel + sizeof(GenSel) * 2 * kNoAllocMaxGens);
-constexpr size_t kNaOffSlots = na_align(kNaOffSizes + sizeof(uint64_t) * kNoAllocMaxSizes);
-// one n = 10 slot: shorter lists than with memory of its own, for more slots
-constexpr size_t kNaSlotWords = 3 * kWgSlotBits + kWgListWordsNoAlloc;
-constexpr size_t kNaSlot10 = kNaSlotWords * sizeof(uint32_t);
-static_assert(kNaOffSlots + 16 * kNaSlot10 <= kNoAllocScratchBytes, "room for at least 16 slots of n = 10");
+// layout of the scratch array: three uint32 queue tickets, then what this
+// call's jobs need; the slots of n = 10 take the rest
+struct NaLayout {
+    size_t outs, jobs, gsel, sizes, slots;
+};
+constexpr NaLayout na_layout(size_t n_jobs, size_t n_gsel, size_t n_sizes) {
+    NaLayout l{};
+    l.outs = 256;
+    l.jobs = na_align(l.outs + sizeof(WgOutDev) * n_jobs);
+    l.gsel = na_align(l.jobs + sizeof(WgJobDev) * n_jobs);
+    l.sizes = na_align(l.gsel + sizeof(GenSel) * n_gsel);
+    l.slots = na_align(l.sizes + sizeof(uint64_t) * n_sizes);
+    return l;
+}
+static_assert(na_layout(kNoAllocMaxJobs, 2 * kNoAllocMaxGens, kNoAllocMaxSizes).slots +
+                      16 * (3 * kWgSlotBits + kWgListWordsLeast) * sizeof(uint32_t) <= kNoAllocScratchBytes,
+              "room for at least 16 slots of n = 10");
 
 constexpr int kNaMaxDevices = 64;
 struct NaDevice {
@@ -1441,23 +1466,22 @@ void run_batch_noalloc(int n_jobs, const cg_job_t *jobs, cg_result_t *results, h
     unsigned char *base = static_cast<unsigned char *>(noalloc_scratch(dev));
     std::lock_guard<std::mutex> lk(g_na[dev].mu);
 
-    uint32_t *ticket = reinterpret_cast<uint32_t *>(base + kNaOffTicket);
-    WgOutDev *outs = reinterpret_cast<WgOutDev *>(base + kNaOffOuts);
-    WgJobDev *djobs = reinterpret_cast<WgJobDev *>(base + kNaOffJobs);
-    GenSel *dgsel = reinterpret_cast<GenSel *>(base + kNaOffGsel);
-    uint64_t *dsizes = reinterpret_cast<uint64_t *>(base + kNaOffSizes);
-    uint32_t *gbits = T.n10 ? reinterpret_cast<uint32_t *>(base + kNaOffSlots) : nullptr;
+    const NaLayout at = na_layout(nj, T.gsel.size(), T.sizes_total);
+    uint32_t *ticket = reinterpret_cast<uint32_t *>(base);
+    WgOutDev *outs = reinterpret_cast<WgOutDev *>(base + at.outs);
+    WgJobDev *djobs = reinterpret_cast<WgJobDev *>(base + at.jobs);
+    GenSel *dgsel = reinterpret_cast<GenSel *>(base + at.gsel);
+    uint64_t *dsizes = reinterpret_cast<uint64_t *>(base + at.sizes);
+    uint32_t *gbits = T.n10 ? reinterpret_cast<uint32_t *>(base + at.slots) : nullptr;
 
     // the launch shape of cg_growth_batch for the batch's largest n
     const int block = wg_block(T.n_max);
     const WgGrid grid = wg_grid(T, block);
-    // workgroups that own a slot: as many as the slot area holds, at most
-    // one per job that needs one
-    uint32_t n_slot_blocks = 0;
+    // workgroups that own a slot
+    WgSlots slots;
     if (gbits) {
-        const uint64_t fit = (kNoAllocScratchBytes - kNaOffSlots) / kNaSlot10;
-        n_slot_blocks = (uint32_t)std::min<uint64_t>({fit, (uint64_t)grid.big, (uint64_t)T.n10});
-        if (n_slot_blocks < 1 || kNaOffSlots + (uint64_t)n_slot_blocks * kNaSlot10 > kNoAllocScratchBytes)
+        slots = wg_slots((kNoAllocScratchBytes - at.slots) / sizeof(uint32_t), T.n10, grid.big);
+        if (!slots.slots || at.slots + slots.slots * slots.words * sizeof(uint32_t) > kNoAllocScratchBytes)
             throw Error(CG_E_DEVICE, "no-allocation slot layout");
     }
     CG_HIP(hipMemcpyAsync(djobs, T.jobs.data(), sizeof(WgJobDev) * nj, hipMemcpyHostToDevice, stream));
@@ -1466,7 +1490,7 @@ void run_batch_noalloc(int n_jobs, const cg_job_t *jobs, cg_result_t *results, h
     hipLaunchKernelGGL(clear_u32_kernel, dim3(1), dim3(64), 0, stream, ticket, 3u);
     CG_HIP(hipGetLastError());
     const double t_admit = now_seconds();
-    const WgLaunch args{djobs, T.n10, T.n9, nj, n_slot_blocks, dgsel, dsizes, outs, ticket, gbits, kNaSlotWords};
+    const WgLaunch args{djobs, T.n10, T.n9, nj, slots.slots, dgsel, dsizes, outs, ticket, gbits, slots.words};
     if (grid.big) hipLaunchKernelGGL(wg_growth_kernel<true>, dim3(grid.big), dim3(block), 0, stream, args);
     CG_HIP(hipGetLastError());
     if (grid.small) hipLaunchKernelGGL(wg_growth_kernel<false>, dim3(grid.small), dim3(block), 0, stream, args);
