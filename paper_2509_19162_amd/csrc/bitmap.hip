@@ -1099,6 +1099,7 @@ struct WgTables {
     std::vector<GenSel> gsel;
     uint64_t sizes_total = 0;     // layer-size entries of all jobs
     uint32_t n10 = 0, n9 = 0;     // jobs of n = 10 (first) and n = 9 (next)
+    uint32_t k10 = 0;             // most generators of a job of n = 10
     int n_max = 0;
 };
 
@@ -1157,6 +1158,7 @@ WgTables wg_tables(const std::vector<WgItem> &items) {
         // the generators, then their inverses
         for (int g = 0; g < 2 * s.k; ++g) T.gsel.push_back(wg_gensel(s, g < s.k ? g : g - s.k, g >= s.k));
         T.n10 += s.n > (int)kWgLdsN;
+        if (s.n > (int)kWgLdsN) T.k10 = std::max(T.k10, (uint32_t)s.k);
         T.n9 += s.n == 9;
         T.n_max = std::max(T.n_max, s.n);
     }
@@ -1206,7 +1208,9 @@ static WgGrid wg_grid(const WgTables &T, int block) {
     }
     return g;
 }
-constexpr uint64_t kWgSlotWords = 3 * kWgSlotBits + kWgListWords;
+// Words of a slot where there is memory for all. (One generator makes layers
+// of one state, or two.)
+uint64_t wg_slot_words(const WgTables &T) { return 3 * kWgSlotBits + (T.k10 > 1 ? kWgListWords : kWgListWordsLeast); }
 
 uint64_t WgRunner::launch_bytes(const std::vector<WgItem> &items, const WgTuning &t) {
     if (items.empty()) return 0;
@@ -1216,7 +1220,7 @@ uint64_t WgRunner::launch_bytes(const std::vector<WgItem> &items, const WgTuning
     // every buffer as DevBuf rounds it (64 KiB) with its growth slack
     auto r = [](uint64_t b) { return ((uint64_t)(1.5 * (double)b) + (64u << 10) - 1) / (64u << 10) * (64u << 10); };
     return r(sizeof(WgJobDev) * nj) + r(sizeof(GenSel) * T.gsel.size()) +
-           r(sizeof(WgOutDev) * nj + sizeof(uint64_t) * T.sizes_total) + r(256) + r(slots * kWgSlotWords * sizeof(uint32_t));
+           r(sizeof(WgOutDev) * nj + sizeof(uint64_t) * T.sizes_total) + r(256) + r(slots * wg_slot_words(T) * sizeof(uint32_t));
 }
 
 uint64_t WgRunner::device_bytes() const {
@@ -1242,7 +1246,6 @@ double WgRunner::run(std::vector<WgItem> &items, const WgTuning &t, double t_sub
     const WgTables T = wg_tables(items);
     const uint64_t sizes_total = T.sizes_total;
     const WgGrid grid = wg_grid(T, t.block);
-    const uint32_t n_slot_blocks = std::min(grid.big, T.n10);
 
     jobs_.ensure(sizeof(WgJobDev) * nj, 1.25);
     gsel_.ensure(sizeof(GenSel) * T.gsel.size(), 1.25);
@@ -1251,18 +1254,32 @@ double WgRunner::run(std::vector<WgItem> &items, const WgTuning &t, double t_sub
     outs_.ensure(back, 1.25);
     uint64_t *const d_sizes = reinterpret_cast<uint64_t *>(outs_.as<char>() + outs_bytes);
     ticket_.ensure(256);
-    if (n_slot_blocks) ws_.ensure((size_t)n_slot_blocks * kWgSlotWords * sizeof(uint32_t));
+    // a slot for every workgroup with a job of n = 10, or as many as there is
+    // memory for
+    WgSlots slots{std::min(grid.big, T.n10), wg_slot_words(T)};
+    for (uint64_t words = slots.slots * slots.words; words;) {
+        try {
+            ws_.ensure(slots.slots * slots.words * sizeof(uint32_t));
+            break;
+        } catch (const Error &e) {
+            if (e.code != CG_E_NOMEM) throw;
+            words = words / 4 * 3;
+            slots = wg_slots(words, T.n10, grid.big);
+            if (!slots.slots) throw;
+        }
+    }
     CG_HIP(hipMemcpyAsync(jobs_.p, T.jobs.data(), sizeof(WgJobDev) * nj, hipMemcpyHostToDevice, stream_));
     CG_HIP(hipMemcpyAsync(gsel_.p, T.gsel.data(), sizeof(GenSel) * T.gsel.size(), hipMemcpyHostToDevice, stream_));
 
-    uint32_t *gbits = n_slot_blocks ? ws_.as<uint32_t>() : nullptr;
-    WgLaunch args{jobs_.as<const WgJobDev>(), T.n10, T.n9, nj, n_slot_blocks, gsel_.as<const GenSel>(),
-                  d_sizes, outs_.as<WgOutDev>(), ticket_.as<uint32_t>(), gbits, kWgSlotWords};
+    uint32_t *gbits = slots.slots ? ws_.as<uint32_t>() : nullptr;
+    WgLaunch args{jobs_.as<const WgJobDev>(), T.n10, T.n9, nj, slots.slots, gsel_.as<const GenSel>(),
+                  d_sizes, outs_.as<WgOutDev>(), ticket_.as<uint32_t>(), gbits, slots.words};
     const std::vector<uint64_t> key = {(uint64_t)(uintptr_t)jobs_.p,   nj,
                                        (uint64_t)(uintptr_t)gsel_.p,   (uint64_t)(uintptr_t)d_sizes,
                                        (uint64_t)(uintptr_t)outs_.p,   (uint64_t)(uintptr_t)ticket_.p,
                                        (uint64_t)(uintptr_t)gbits,     (uint64_t)t.block,
                                        T.n10,                          T.n9,
+                                       slots.slots,                    slots.words,
                                        grid.big,                       grid.small};
     auto enqueue = [&]() {
         hipLaunchKernelGGL(clear_u32_kernel, dim3(1), dim3(64), 0, stream_, ticket_.as<uint32_t>(), 3u);

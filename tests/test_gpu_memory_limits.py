@@ -89,3 +89,18 @@ def test_last_small_layers_without_room_for_a_run(monkeypatch):
     got = api.growth_ex(24, gens, **kw)
     _same(got, ref)
     assert got.kstats.get("dedup_compact", {"launches": 0})["launches"] < 100
+
+
+@pytest.mark.parametrize("mib", [4, 24, 140, 300])
+def test_batches_of_n_10_with_few_slots(mib, monkeypatch):
+    """100 jobs (one workgroup each) whose bitmaps alone take 130 MiB: with
+    less, they take turns."""
+    jobs = [(10, I.random_perms_with_inverses(10, 2, I.rng_for(i, seed=22))) for i in range(100)]
+    ref = api.growth_batch_noalloc(jobs)
+    api.release_cached_memory()
+    monkeypatch.setenv("CG_DEVICE_BYTES", str(api.memory_stats()["held_bytes"] + (mib << 20)))
+    for _ in range(2):
+        got = api.growth_batch(jobs)
+        assert [(r.status, r.sizes, r.states_expanded) for r in got] == [(r.status, r.sizes, r.states_expanded) for r in ref]
+    monkeypatch.delenv("CG_DEVICE_BYTES")
+    assert [r.sizes for r in api.growth_batch(jobs)] == [r.sizes for r in ref]
