@@ -355,10 +355,17 @@ __device__ __forceinline__ void wg_run(const WgJobDev &J, const C &codec, uint32
 // the unseen states look for a seen predecessor in the bitmap in memory; such
 // a test weighs four neighbours here.
 // A batch of 4096 jobs (1365 of n = 10, four or more generators): this launch
-// 86 ms, 222 ms with tests and ORs in the bitmaps in memory; bound by the
+// 75 ms, 222 ms with tests and ORs in the bitmaps in memory; bound by the
 // instructions that form the neighbours' ranks.
+// A layer goes over whole bitmaps then, 285 us in a job alone on the chip
+// however few its states are. So until a layer has more than kWgThin
+// neighbours its states are two lists in the LDS of the part: a wave maps 64
+// of them under one generator, and a neighbour is claimed in the visited
+// bitmap. (One directed generator of order 30: 2.8 us a layer; LRX up to a
+// layer of 4000 states 0.10 ms, 3.84 over bitmaps, 1.33 with tests in memory.)
 constexpr uint32_t kWgSpan = 8;                            // words listed at a time
 constexpr uint32_t kWgQueue = kWgSpan * 32 + kWave;        // states a wave holds
+constexpr uint32_t kWgThin = kWgPartWords / 2;             // neighbours of a thin layer: a list's room
 template <class C>
 __device__ __forceinline__ void wg_run_parts(const WgJobDev &J, const C &codec, uint32_t *vis, uint32_t *cur,
                                              uint32_t *nxt, uint32_t *lists, uint32_t cap, uint32_t *part,
@@ -374,19 +381,56 @@ __device__ __forceinline__ void wg_run_parts(const WgJobDev &J, const C &codec, 
         vis[w] = 0u;
         cur[w] = 0u;
     }
-    for (uint32_t w = tid; w < kWgPartWords; w += nt) part[w] = 0u;
     if (tid == 0) *s_acc = *s_more = 0;
     if (lane < kWgChunk) fresh[lane] = 0;
     __syncthreads();
+    uint32_t *from = part, *to = part + kWgThin;  // states of a thin layer and of the next
     if (tid == 0) {
         const uint32_t r = J.start_rank;
         vis[r >> 5] = 1u << (r & 31u);
-        cur[r >> 5] = 1u << (r & 31u);
+        from[0] = r;
         sizes[0] = 1;
     }
     __syncthreads();
     WgLayers L;
+    bool thin = true;
     while (!L.done(J)) {
+        if (thin && L.F * k <= kWgThin) {
+            const uint32_t F = (uint32_t)L.F, items = (F + kWave - 1) / kWave * k;
+            for (uint32_t it = wave; it < items; it += waves) {
+                const uint32_t c = it / k, i = c * kWave + lane;
+                const typename C::State s = codec.unrank(from[i < F ? i : 0u]);
+                const uint32_t q = codec.neighbour(s, it - c * k), m = 1u << (q & 31u);
+                // (a word read from a stale line costs an atomic, no more)
+                bool won = i < F && !(vis[q >> 5] & m);
+                if (won) won = !(atomicOr(&vis[q >> 5], m) & m);
+                const uint64_t b = __ballot(won);
+                if (!b) continue;
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(s_acc, (uint32_t)__popcll(b));
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + mask_rank(b);
+                if (won) to[at] = q;
+            }
+            __syncthreads();
+            const uint32_t n1 = *s_acc;
+            uint32_t *t = from;
+            from = to;
+            to = t;
+            if (!L.next(n1, sizes)) break;
+            __syncthreads();  // every thread has read s_acc before it is reset
+            if (tid == 0) *s_acc = 0;
+            __syncthreads();
+            continue;
+        }
+        if (thin) {
+            // the layer's states as bits of `cur`; the part is empty again
+            thin = false;
+            for (uint32_t i = tid; i < (uint32_t)L.F; i += nt) atomicOr(&cur[from[i] >> 5], 1u << (from[i] & 31u));
+            __syncthreads();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // no line of the bitmaps from before the atomics
+            for (uint32_t w = tid; w < kWgPartWords; w += nt) part[w] = 0u;
+            __syncthreads();
+        }
         uint32_t cnt = 0;
         if (pull_is_less(factorial(10) - L.seen, L.F, L.before, k, 4.0)) {
             for (uint32_t c = wave; c * kWgChunk < W; c += waves) {
