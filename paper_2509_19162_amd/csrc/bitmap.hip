@@ -84,24 +84,29 @@ static_assert((uint64_t)kWgParts << kWgLgPart >= factorial(10), "parts cover the
 // is divided among the waves and parts).
 constexpr uint64_t kWgSlotBits = (wg_words(10) + 63) / 64 * 64;
 constexpr uint64_t kWgListWords = 1u << 20;
-constexpr uint64_t kWgListWordsLeast = 24u << 10;
-// Slots for `jobs` of n = 10 in `words` words: as many as short lists leave
-// room for, the jobs in rounds of equal length, and the lists as long as
-// these slots leave room for. (In 64 MiB, S_10 by two random generators and
-// their inverses: 35 jobs 44 ms in two rounds of 29 slots with 65536 words of
-// lists, 25 in one round; 46 jobs 48 ms in one round with 16384 words, 42 in
-// two.)
+constexpr uint64_t kWgListWordsLeast = 16u << 10;
+// Slots for `jobs` of n = 10 in `words` words: the fewer, the longer their
+// lists and the fewer passes over a job's bitmaps. A round of S_10 growths by
+// two random generators and their inverses takes 21 ms times 1 + 28600 /
+// (words of a slot's lists), measured from 23000 to 250000 of these. (35 jobs
+// 44 ms in two rounds of 29 slots, 25 in one; 46 jobs 48 ms in one round, 43
+// in two; a batch with 1365 in 48 MB 846 ms with 32 slots, 669 with 28.)
 struct WgSlots {
     uint32_t slots = 0;
     uint64_t words = 0;  // of a slot
 };
 WgSlots wg_slots(uint64_t words, uint32_t jobs, uint32_t blocks) {
     WgSlots s;
-    const uint64_t fit = std::min<uint64_t>({words / (3 * kWgSlotBits + kWgListWordsLeast), jobs, blocks});
-    if (!fit) return s;
-    const uint64_t rounds = (jobs + fit - 1) / fit;
-    s.slots = (uint32_t)((jobs + rounds - 1) / rounds);
-    s.words = std::min(words / s.slots / 64 * 64, 3 * kWgSlotBits + kWgListWords);
+    double least = 0;
+    for (uint32_t n = 1; n <= std::min(jobs, blocks); ++n) {
+        const uint64_t w = std::min(words / n / 64 * 64, 3 * kWgSlotBits + kWgListWords);
+        if (w < 3 * kWgSlotBits + kWgListWordsLeast) break;
+        const double t = (double)((jobs + n - 1) / n) * (1.0 + 28600.0 / (double)(w - 3 * kWgSlotBits));
+        if (!s.slots || t <= least) {
+            least = t;
+            s = WgSlots{n, w};
+        }
+    }
     return s;
 }
 
