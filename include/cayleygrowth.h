@@ -367,7 +367,7 @@ int cg_queue_stats(cg_queue_t *q, cg_queue_stats_t *out);
 
 /*
  * Device memory: with the first request of 16 MiB or more the library
- * reserves a device arena of 4 GiB, and once something does not fit there
+ * reserves a device arena of 16 GiB, and once something does not fit there
  * the fraction CG_ARENA_FRACTION of the free memory (default 0.85; 0
  * disables both), and carves every buffer out of it; a freed range is
  * reused only after the work queued on its last stream has finished. This

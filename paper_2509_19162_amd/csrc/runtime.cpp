@@ -26,8 +26,9 @@ void hip_check(hipError_t e, const char *what, const char *file, int line) {
 // Device arena. On this HIP runtime a hipMalloc is fast while little memory is
 // held, but a large one takes seconds (245 GB: 1.3 to 6 s), and so do later
 // ones once tens of GB are held. So buffers are carved out of regions that
-// the library reserves: a first one of 4 GiB (0.3 ms), with the first request
-// of 16 MiB or more, and one of most of the device's memory
+// the library reserves: a first one of 16 GiB (0.3 ms; it holds the bitmask
+// engine's S_13 and S_12 with every layer kept), with the first request of 16
+// MiB or more, and one of most of the device's memory
 // (CG_ARENA_FRACTION of what is free, default 0.85; 0 disables both) once
 // something does not fit there. Best fit, split on allocation, coalesced on
 // free. A range is
@@ -39,7 +40,7 @@ namespace {
 
 constexpr size_t kAlign = 1u << 16;
 constexpr size_t kArenaMinRequest = 16u << 20;  // smaller buffers also use it once it exists
-constexpr size_t kArenaFirst = 4ull << 30;
+constexpr size_t kArenaFirst = 16ull << 30;
 
 struct Arena {
     struct Region {
