@@ -7,6 +7,7 @@
 // "every earlier layer", so no closure under inverses is assumed.
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -716,7 +717,8 @@ __global__ __launch_bounds__(kBmBlock) void bm_expand_kernel(const uint32_t *__r
 // so the workgroups share the digits' parts (with parts of their own, of
 // 2000 words, one in ten overran).
 // OR may be repeated, so a piece whose lists overran goes through
-// bm_expand_kernel as if nothing had happened.
+// bm_expand_kernel as if nothing had happened (on S_11, whose bitmaps fit the
+// caches, even that is faster: most bits are set by then).
 // S_13 by two random generators and their inverses: 617 -> 260 ms, of which
 // the split takes 60% (8.9 ps a neighbour: ranks, ring slots and barriers)
 // and the ORs 30% (4.4).
@@ -922,34 +924,45 @@ void with_bm_lists_n(int n, F &&f) {
 // place, or moves late ones only, the neighbours of states with nearby ranks
 // lie in a few lines, and testing them directly takes 3 to 6 ps (S_12 under
 // all 66 transpositions 230 ms, through lists 2100; S_13 2.9 s and 7.7),
-// where scattered ones take 31 and the lists 9 to 13 (by this rule 167 ms and
-// 1.9 s; star S_13 673 -> 492, pancake 1046 -> 618, LRX 762 -> 592, against
-// direct tests of all). It depends on how near
+// where scattered ones take 31 and the lists 9 to 13 (by the rules here 160 ms
+// and 1.9 s; star S_13 690 -> 484, pancake 1046 -> 525, LRX 760 to 830 -> 597,
+// against direct tests of all). It depends on how near
 // the layer's ranks are: lines that 64 of them come to under g, per rank, in
 // two places, for one in 1, 4, 16 or 64 ranks in the layer.
 constexpr int kBmDensities = 4;
 struct BmSpread {
     double at[kBmDensities];
 };
+constexpr uint32_t kBmSpreadRanks = 64, kBmSpreadPlaces = 2;
+constexpr uint32_t kBmSpreadKeys = kBmDensities * kBmSpreadPlaces * kBmSpreadRanks;
+// The permutations looked at, the same for every generator.
 template <int N>
-BmSpread bm_spread(const uint8_t *row) {
-    constexpr uint32_t kRanks = 64, kLgLine = 10;
+void bm_spread_keys(uint64_t *key) {
+    for (int d = 0; d < kBmDensities; ++d)
+        for (uint64_t place = 0; place < kBmSpreadPlaces; ++place) {
+            const uint64_t r0 = (factorial(N) / 5 * (2 * place + 1)) / 4096 * 4096;
+            for (uint32_t i = 0; i < kBmSpreadRanks; ++i)
+                *key++ = perm_unrank_t<N, RankOf<N>>((RankOf<N>)(r0 + ((uint64_t)i << (2 * d))));
+        }
+}
+template <int N>
+BmSpread bm_spread(const uint8_t *row, const uint64_t *key) {
+    constexpr uint32_t kLgLine = 10;
     BmSpread out;
     for (int d = 0; d < kBmDensities; ++d) {
         uint32_t lines = 0;
-        for (uint64_t place = 0; place < 2; ++place) {
-            const uint64_t r0 = (factorial(N) / 5 * (2 * place + 1)) / 4096 * 4096;
-            uint64_t line[kRanks];
-            for (uint32_t i = 0; i < kRanks; ++i) {
-                const uint64_t key = perm_unrank_t<N, RankOf<N>>((RankOf<N>)(r0 + ((uint64_t)i << (2 * d))));
+        for (uint32_t place = 0; place < kBmSpreadPlaces; ++place) {
+            uint64_t line[kBmSpreadRanks];
+            for (uint64_t &x : line) {
                 uint64_t t = 0;
-                for (int j = 0; j < N; ++j) t = t << 4 | ((key >> (4 * (N - 1 - row[j]))) & 15u);
-                line[i] = (uint64_t)perm_rank_t<N, RankOf<N>>(t) >> kLgLine;
+                for (int j = 0; j < N; ++j) t = t << 4 | ((*key >> (4 * (N - 1 - row[j]))) & 15u);
+                ++key;
+                x = (uint64_t)perm_rank_t<N, RankOf<N>>(t) >> kLgLine;
             }
-            std::sort(line, line + kRanks);
-            lines += (uint32_t)(std::unique(line, line + kRanks) - line);
+            std::sort(line, line + kBmSpreadRanks);
+            lines += (uint32_t)(std::unique(line, line + kBmSpreadRanks) - line);
         }
-        out.at[d] = (double)lines / (2.0 * kRanks);
+        out.at[d] = (double)lines / (2.0 * kBmSpreadRanks);
     }
     return out;
 }
@@ -964,8 +977,34 @@ double bm_scattered(int density, int k) {
 }
 
 // From this many neighbours on a layer goes through lists: below, clearing
-// and writing back every segment (0.3 ms at n = 13) is more than the tests.
-constexpr uint64_t kBmListsMin = 1ull << 23;
+// and writing back every segment is more than the tests (at n = 13, 2.5 ms; by
+// two random generators and their inverses 8e6 neighbours 3.5 ms and 3.2
+// directly, 2.5e7 3.8 and 5.1).
+constexpr uint64_t kBmListsMin = 1ull << 23, kBmListsMin13 = 1ull << 24;
+uint64_t bm_lists_min(int n) { return n >= 13 ? kBmListsMin13 : kBmListsMin; }
+// Early layers crowd near the start state, and late ones at the other end.
+// There direct tests are cheap, as neighbours share lines (S_13 Coxeter, 8e5
+// to 2e8 states, 82 to 15 ps), and a digit's list overruns (lists 900 to 62
+// ps). So a layer goes through lists up to this many times its even share in
+// the fullest digit. One segment to a digit (n = 11, 12): lists are faster on
+// S_11 up to 3.8 (pancake 320 ps directly, 116 through lists, transpositions
+// 46 and 22), slower for reversals at 4.4 (40, 118) and for Coxeter, none of
+// whose generators goes far, at 3.7 (136, 200); on S_12 faster up to 2.2 (LRX
+// 175, 70), slower for Coxeter at 2.7 (42, 146) and reversals at 2.9 (11, 53).
+// A digit of n = 13 holds 12 segments: faster up to 1.43 (LRX 74, 45), slower
+// at 1.51 (Coxeter 15, 62) and 1.61 (pancake 19, 28). Where every generator
+// takes ranks as near as the layer's to a quarter of a line each or more, no
+// neighbours share lines, whatever part of the ranks the orbit lies in: up to
+// 3 (S_12 as a subgroup of S_13, at 2.2: 34 to 207 ps, 16 to 133).
+constexpr double kBmFar = 0.25, kBmCrowdedMost = 4.0;
+double bm_crowded(int n, bool all_far, bool some_far) {
+    if (n <= 11) return some_far ? kBmCrowdedMost : 3.5;
+    return all_far ? 3.0 : (n == 12 ? 2.4 : 1.45);
+}
+// From this many states on a layer is worth finding out which generators
+// scatter: up to 17 us of host time per generator, and lists save 100 ps and
+// more of a neighbour's time in the first layers that take them.
+constexpr uint64_t kBmSpreadMin = 1ull << 18;
 
 // The step from the other side, late in a growth: every unseen state looks
 // for a seen predecessor (its images under the inverse generators) and is in
@@ -1032,14 +1071,18 @@ __global__ __launch_bounds__(kBmBlock) void bm_pull_kernel(const uint32_t *__res
 }
 
 // visited |= next (counted), and the expanded layer is cleared, over the
-// chunks that either touches.
+// chunks that either touches. digits (or null): new states by the digit of
+// their segment, of 2^lg bits.
 __global__ __launch_bounds__(kBmBlock) void bm_fold_kernel(uint32_t *__restrict__ vis, uint32_t *__restrict__ cur,
                                                            const uint32_t *__restrict__ scur,
                                                            const uint32_t *__restrict__ nxt,
                                                            const uint32_t *__restrict__ snxt, uint64_t W,
-                                                           uint64_t nchunks, unsigned long long *count) {
-    __shared__ uint32_t s_acc;
+                                                           uint64_t nchunks, unsigned long long *count,
+                                                           uint32_t *digits, uint32_t lg) {
+    __shared__ uint32_t s_acc, s_digit[1u << kBmLgDigits];
     if (threadIdx.x == 0) s_acc = 0;
+    if (digits)
+        for (uint32_t d = threadIdx.x; d < (1u << kBmLgDigits); d += kBmBlock) s_digit[d] = 0;
     __syncthreads();
     uint32_t cnt = 0;
     for (uint64_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
@@ -1047,21 +1090,31 @@ __global__ __launch_bounds__(kBmBlock) void bm_fold_kernel(uint32_t *__restrict_
         const bool in_cur = (scur[c >> 5] >> (c & 31u)) & 1u;
         if (!in_next && !in_cur) continue;
         const uint64_t w_end = (c + 1) * kChunkWords < W ? (c + 1) * kChunkWords : W;
+        uint32_t here = 0;
         for (uint64_t w = c * kChunkWords + threadIdx.x; w < w_end; w += kBmBlock) {
             if (in_next) {
                 const uint32_t x = nxt[w];
                 if (x) {
                     vis[w] |= x;
-                    cnt += (uint32_t)__popc(x);
+                    here += (uint32_t)__popc(x);
                 }
             }
             if (in_cur) cur[w] = 0u;
+        }
+        cnt += here;
+        if (digits && in_next) {
+            here = wave_sum(here);
+            const uint32_t d = (uint32_t)(c * kChunkWords * 32 >> lg) & ((1u << kBmLgDigits) - 1u);
+            if ((threadIdx.x & (kWave - 1)) == 0 && here) atomicAdd(&s_digit[d], here);
         }
     }
     cnt = wave_sum(cnt);
     if ((threadIdx.x & (kWave - 1)) == 0 && cnt) atomicAdd(&s_acc, cnt);
     __syncthreads();
     if (threadIdx.x == 0 && s_acc) atomicAdd(count, (unsigned long long)s_acc);
+    if (digits)
+        for (uint32_t d = threadIdx.x; d < (1u << kBmLgDigits); d += kBmBlock)
+            if (s_digit[d]) atomicAdd(&digits[d], s_digit[d]);
 }
 
 __global__ void bm_seed_kernel(uint32_t *vis, uint32_t *cur, uint32_t *scur, uint64_t r,
@@ -1072,7 +1125,7 @@ __global__ void bm_seed_kernel(uint32_t *vis, uint32_t *cur, uint32_t *scur, uin
     cur[w] = m;
     const uint64_t c = w / kChunkWords;
     scur[c >> 5] = 1u << (uint32_t)(c & 31u);
-    count[0] = count[1] = 0;  // and the lists' flag
+    count[0] = 0;
 }
 
 __global__ void bm_clear_kernel(uint32_t *a, uint64_t na, unsigned long long *count) {
@@ -1585,7 +1638,7 @@ std::string bitmask_unsupported(const JobSpec &spec) {
 
 uint64_t bitmask_list_bytes(const JobSpec &spec) {
     const uint64_t k = (uint64_t)spec.k;
-    if (spec.max_frontier && spec.max_frontier < kBmListsMin / std::max<uint64_t>(1, k)) return 0;
+    if (spec.max_frontier && spec.max_frontier < bm_lists_min(spec.n) / std::max<uint64_t>(1, k)) return 0;
     const BmLists l = bm_lists(spec.n, (uint32_t)spec.k);
     return l.per_piece ? (l.words() + kBmCursors) * sizeof(uint32_t) : 0;
 }
@@ -1618,35 +1671,50 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s, HeldBytes
     nxt.ensure(W * 4);
     scur.ensure(sw * 4);
     snxt.ensure(sw * 4);
-    cnt.ensure(64);
-    // the generators, those that scatter most first, then the inverses
+    // the layer's count, the lists' flag, and states by digit
+    constexpr uint32_t kFlagAt = 2, kDigitsAt = 16, kCounts = kDigitsAt + (1u << kBmLgDigits);
+    cnt.ensure(kCounts * sizeof(uint32_t));
+    // the generators, then the inverses
     std::vector<GenSel> hs(std::max(1, 2 * k));
     std::vector<int> order(k);
-    std::vector<BmSpread> spread(k, BmSpread{});
-    for (int g = 0; g < k; ++g) {
-        order[g] = g;
-        if (bm_lists(n, (uint32_t)k).per_piece)
-            with_bm_lists_n(n, [&](auto NN) {
-                spread[g] = bm_spread<decltype(NN)::value>(spec.gens.data() + (size_t)g * n);
-            });
-    }
-    auto sum = [&](int g) { return spread[g].at[0] + spread[g].at[1] + spread[g].at[2] + spread[g].at[3]; };
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return sum(a) > sum(b); });
-    // how many go through lists, by the layer's density
-    int scattered[kBmDensities] = {0};
-    for (int d = 0; d < kBmDensities; ++d) {
-        for (int g = 0; g < k; ++g) scattered[d] += spread[g].at[d] >= bm_scattered(d, k);
-        scattered[d] = std::min(k, (scattered[d] + 3) / 4 * 4);  // (a round takes four)
-    }
-    for (int g = 0; g < k; ++g) {
-        const uint8_t *row = spec.gens.data() + (size_t)order[g] * n;
-        uint8_t inv[16] = {0};
-        for (int i = 0; i < n; ++i) inv[row[i]] = (uint8_t)i;
-        hs[g] = make_gensel(n, row);
-        hs[k + g] = make_gensel(n, inv);
-    }
+    for (int g = 0; g < k; ++g) order[g] = g;
+    auto upload = [&]() {
+        for (int g = 0; g < k; ++g) {
+            const uint8_t *row = spec.gens.data() + (size_t)order[g] * n;
+            uint8_t inv[16] = {0};
+            for (int i = 0; i < n; ++i) inv[row[i]] = (uint8_t)i;
+            hs[g] = make_gensel(n, row);
+            hs[k + g] = make_gensel(n, inv);
+        }
+        CG_HIP(hipMemcpyAsync(gsel.p, hs.data(), sizeof(GenSel) * hs.size(), hipMemcpyHostToDevice, s));
+    };
     gsel.ensure(sizeof(GenSel) * hs.size());
-    CG_HIP(hipMemcpyAsync(gsel.p, hs.data(), sizeof(GenSel) * hs.size(), hipMemcpyHostToDevice, s));
+    upload();
+    // how many generators go through lists, by the layer's density; these
+    // come first then (nothing is under way between two layers)
+    int scattered[kBmDensities] = {0};
+    bool looked = false, all_far[kBmDensities] = {false}, some_far[kBmDensities] = {false};
+    double crowd = 1e9;  // the fullest digit of the layer, in even shares
+    auto look_for_scattered = [&]() {
+        looked = true;
+        std::vector<BmSpread> spread(k, BmSpread{});
+        with_bm_lists_n(n, [&](auto NN) {
+            constexpr int N = decltype(NN)::value;
+            uint64_t keys[kBmSpreadKeys];
+            bm_spread_keys<N>(keys);
+            for (int g = 0; g < k; ++g) spread[g] = bm_spread<N>(spec.gens.data() + (size_t)g * n, keys);
+        });
+        auto sum = [&](int g) { return spread[g].at[0] + spread[g].at[1] + spread[g].at[2] + spread[g].at[3]; };
+        std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return sum(a) > sum(b); });
+        for (int d = 0; d < kBmDensities; ++d) {
+            for (int g = 0; g < k; ++g) scattered[d] += spread[g].at[d] >= bm_scattered(d, k);
+            scattered[d] = std::min(k, (scattered[d] + 3) / 4 * 4);  // (a round takes four)
+            auto far = [&](const BmSpread &x) { return x.at[d] >= kBmFar; };
+            all_far[d] = std::all_of(spread.begin(), spread.end(), far);
+            some_far[d] = std::any_of(spread.begin(), spread.end(), far);
+        }
+        upload();
+    };
     CG_HIP(hipMemsetAsync(vis.p, 0, W * 4, s));
     CG_HIP(hipMemsetAsync(cur.p, 0, W * 4, s));
     CG_HIP(hipMemsetAsync(nxt.p, 0, W * 4, s));
@@ -1657,14 +1725,17 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s, HeldBytes
     hipLaunchKernelGGL(bm_seed_kernel, dim3(1), dim3(1), 0, s, vis.as<uint32_t>(), cur.as<uint32_t>(),
                        scur.as<uint32_t>(), host_rank64(key0, n), cnt.as<unsigned long long>());
     CG_HIP(hipGetLastError());
+    hipLaunchKernelGGL(bm_clear_kernel, dim3(1), dim3(256), 0, s, cnt.as<uint32_t>() + kFlagAt,
+                       (uint64_t)(kCounts - kFlagAt), (unsigned long long *)nullptr);
+    CG_HIP(hipGetLastError());
 
     hipEvent_t e0, e1;
     CG_HIP(hipEventCreate(&e0));
     CG_HIP(hipEventCreate(&e1));
     CG_HIP(hipEventRecord(e0, s));
     const uint32_t grid = (uint32_t)std::min<uint64_t>(nchunks, (uint64_t)device_cus() * 16);
-    HostKit kit = take_kit(2 * sizeof(uint64_t), false);
-    uint64_t *const host_cnt = static_cast<uint64_t *>(kit.host);
+    HostKit kit = take_kit(kCounts * sizeof(uint32_t), false);
+    const uint32_t *const host_cnt = static_cast<const uint32_t *>(kit.host);
     uint32_t *pc = cur.as<uint32_t>(), *pn = nxt.as<uint32_t>(), *sc = scur.as<uint32_t>(),
              *sn = snxt.as<uint32_t>();
     uint64_t F = 1, before = 0, seen = 1;
@@ -1673,6 +1744,14 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s, HeldBytes
     // layers whose neighbours are fewer than its words
     const uint32_t grid_all = (uint32_t)std::min<uint64_t>((W + 63) / 64, (uint64_t)device_cus() * 32);
     BmLists L = bm_lists(n, (uint32_t)k);
+    uint32_t lg_seg = 0;
+    double share = 1;  // of the fullest digit, spread evenly
+    if (L.per_piece)
+        with_bm_lists_n(n, [&](auto NN) {
+            using Seg = BmSeg<decltype(NN)::value>;
+            lg_seg = Seg::kLg;
+            share = (double)Seg::kSubs / (double)Seg::kSegs;
+        });
     // the lists are there from the first large layer on, if memory allows
     auto room_for_lists = [&]() {
         if (!lists.p) {
@@ -1699,15 +1778,23 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s, HeldBytes
                 status = CG_TRUNCATED;
                 break;
             }
-            const int kf = scattered[bm_density(F, S)];
-            const bool large = L.per_piece && F * (uint64_t)kf >= kBmListsMin;
+            // (a next layer too small for lists is not counted by digit)
+            const bool by_digit = L.per_piece && F * (uint64_t)k >= kBmSpreadMin;
+            if (!looked && L.per_piece && crowd <= kBmCrowdedMost && F >= kBmSpreadMin &&
+                F * (uint64_t)k >= bm_lists_min(n))
+                look_for_scattered();
+            const int density = bm_density(F, S), kf = scattered[density];
+            const bool even = crowd <= bm_crowded(n, all_far[density], some_far[density]);
+            const bool large = L.per_piece && even && F * (uint64_t)kf >= bm_lists_min(n);
             // (a scattered test costs two and a half neighbours that go through lists)
             const bool pull = F * (uint64_t)k >= W && pull_is_less(S - seen, F, before, (uint64_t)k,
                                                                    large ? 1.0 + 1.5 * (double)kf / (double)k : 1.0);
             bool by_lists = large && !pull && room_for_lists();
             if (by_lists) {
-                const uint32_t pieces = (uint32_t)((F * (uint64_t)kf + L.per_piece - 1) / L.per_piece);
-                uint32_t *const flag = cnt.as<uint32_t>() + 2;  // after the layer's count
+                // (the fullest list has a third more room than its even share)
+                const uint32_t pieces = (uint32_t)std::ceil(std::max(1.0, crowd / 1.2) * (double)F * (double)kf /
+                                                            (double)L.per_piece);
+                uint32_t *const flag = cnt.as<uint32_t>() + kFlagAt;
                 const PartShared<uint32_t> o{lists.as<uint32_t>(), (uint64_t)kBmSets * L.cap, L.cap,
                                              list_cnt.as<uint32_t>()};
                 with_bm_lists_n(n, [&](auto NN) {
@@ -1737,7 +1824,7 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s, HeldBytes
                     hipLaunchKernelGGL(bm_pull_kernel<N>, dim3(grid_all), dim3(kBmBlock), 0, s,
                                        vis.as<const uint32_t>(), pn, sn, W, sel + k, k);
                 } else if (by_lists) {
-                    expand(0, kf, cnt.as<const uint32_t>() + 2);  // if lists overran
+                    expand(0, kf, cnt.as<const uint32_t>() + kFlagAt);  // if lists overran
                     expand(kf, k, nullptr);
                 } else {
                     expand(0, k, nullptr);
@@ -1745,23 +1832,22 @@ void run_bitmask(const JobSpec &spec, cg_result_t *res, hipStream_t s, HeldBytes
             });
             CG_HIP(hipGetLastError());
             hipLaunchKernelGGL(bm_fold_kernel, dim3(grid), dim3(kBmBlock), 0, s, vis.as<uint32_t>(), pc, sc, pn, sn,
-                               W, nchunks, cnt.as<unsigned long long>());
+                               W, nchunks, cnt.as<unsigned long long>(),
+                               by_digit ? cnt.as<uint32_t>() + kDigitsAt : nullptr, lg_seg);
             CG_HIP(hipGetLastError());
             // the expanded layer's summary becomes the next layer's: clear it
             hipLaunchKernelGGL(bm_clear_kernel, dim3((uint32_t)std::min<uint64_t>((sw + 255) / 256, 4096)),
                                dim3(256), 0, s, sc, sw, (unsigned long long *)nullptr);
             CG_HIP(hipGetLastError());
-            CG_HIP(hipMemcpyAsync(host_cnt, cnt.p, 2 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-            hipLaunchKernelGGL(bm_clear_kernel, dim3(1), dim3(64), 0, s, cnt.as<uint32_t>() + 2, 1ull,
-                               cnt.as<unsigned long long>());
+            CG_HIP(hipMemcpyAsync(kit.host, cnt.p, (by_digit ? kCounts : 2) * sizeof(uint32_t),
+                                  hipMemcpyDeviceToHost, s));
+            hipLaunchKernelGGL(bm_clear_kernel, dim3(1), dim3(256), 0, s, cnt.as<uint32_t>() + kFlagAt,
+                               (uint64_t)(by_digit ? kCounts - kFlagAt : 1u), cnt.as<unsigned long long>());
             CG_HIP(hipStreamSynchronize(s));
-            const uint64_t N = host_cnt[0];
-            // an orbit in few segments, or crowded there, overruns every
-            // time: no more lists
-            if (by_lists && (uint32_t)host_cnt[1]) {
-                L.per_piece = 0;
-                lists.release();
-            }
+            const uint64_t N = host_cnt[0] | (uint64_t)host_cnt[1] << 32;
+            crowd = 1e9;
+            if (by_digit && N)
+                crowd = (double)*std::max_element(host_cnt + kDigitsAt, host_cnt + kCounts) / ((double)N * share);
             res->states_expanded += F;
             res->candidates += F * (uint64_t)k;
             std::swap(pc, pn);
