@@ -203,15 +203,29 @@ void Engine::export_layer(const JobSpec &spec, const uint64_t *d_keys, uint64_t 
 void fill_kstats(const Profiler &p, cg_result_t *res) {
     res->n_kstats = 0;
     if (!p.on) return;
-    for (int k = 0; k < K_NUM && res->n_kstats < CG_KSTAT_MAX; ++k) {
+    // a growth handed to the sort path may have more kinds than the result
+    // has room for: those of least time are counted as bookkeeping then
+    int kinds[K_NUM], n = 0;
+    for (int k = 0; k < K_NUM; ++k)
+        if (p.launches[k]) kinds[n++] = k;
+    std::stable_sort(kinds, kinds + n, [&](int a, int b) { return p.total_ms[a] > p.total_ms[b]; });
+    int into[K_NUM];
+    for (int i = 0; i < n; ++i) into[kinds[i]] = n <= CG_KSTAT_MAX || i < CG_KSTAT_MAX - 1 ? kinds[i] : K_AUX;
+    int at[K_NUM];
+    std::fill(at, at + K_NUM, -1);
+    for (int k = 0; k < K_NUM; ++k) {
         if (!p.launches[k]) continue;
-        cg_kstat_t &s = res->kstats[res->n_kstats++];
-        std::memset(&s, 0, sizeof s);
-        std::snprintf(s.name, sizeof s.name, "%s", kernel_kind_name(k));
-        s.launches = p.launches[k];
-        s.total_ms = p.total_ms[k];
-        s.alg_bytes = p.bytes[k];
-        s.items = p.items[k];
+        int &slot = at[into[k]];
+        if (slot < 0) {
+            slot = res->n_kstats++;
+            std::memset(&res->kstats[slot], 0, sizeof(cg_kstat_t));
+            std::snprintf(res->kstats[slot].name, sizeof res->kstats[slot].name, "%s", kernel_kind_name(into[k]));
+        }
+        cg_kstat_t &s = res->kstats[slot];
+        s.launches += p.launches[k];
+        s.total_ms += p.total_ms[k];
+        s.alg_bytes += p.bytes[k];
+        s.items += p.items[k];
     }
 }
 
