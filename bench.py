@@ -282,19 +282,11 @@ def growth_leg(name: str, steps: int, warmup: int) -> dict:
             "launches": int(d["launches"]),
         }
         out["kernel_ms_per_step"] = {k: round(v["total_ms"] / steps, 3) for k, v in sorted(agg.items())}
-        # bytes the kernels move by their own count (every sort pass
-        # included), and the method's floor: per expanded layer d,
-        # 8 [F + 2C + |L_d| + |L_{d-1}| + N] (frontier read, candidates
-        # written and read once, both reference layers read, new layer
-        # written)
+        # bytes the kernels move by their own count (every pass included),
+        # and what no method does without: each state written once and read
+        # back once, 8 bytes each way
         kern = sum(v["alg_bytes"] for v in agg.values()) / steps
-        floor = 0
-        k = len(gens)
-        for d in range(len(sizes) - 1 if results[0].status == 1 else len(sizes)):
-            F = sizes[d]
-            prev = sizes[d - 1] if d > 0 else 0
-            nxt = sizes[d + 1] if d + 1 < len(sizes) else 0
-            floor += 8 * (F + 2 * k * F + F + prev + nxt)
+        floor = 8 * (sum(sizes) + expanded)
         step_s = elapsed / steps
         out["pipeline"] = {"kernel_bytes_per_step": round(kern),
                            "kernel_gbs_over_wall": round(kern / step_s / 1e9, 1),
@@ -599,7 +591,7 @@ def _growth_line(name: str, leg: dict, steps: int, warmup: int, cpu) -> dict:
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        # candidates of n <= 12 are sorted and deduplicated as 32-bit ranks
+        # candidates of n <= 12 are 32-bit ranks
         "dtype": "u32" if n <= 12 else "u64",
         "data": "synthetic",
         "config": {"workload": leg["desc"], "n": n, "generators": leg["generators"], "layers": leg["layers"],

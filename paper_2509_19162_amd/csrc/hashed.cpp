@@ -464,6 +464,9 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
             p.status = CG_OK;
             return true;
         }
+        // (the candidates of tagged layers are counted as if each state had one
+        // way back: an upper bound of what the kernels move)
+        if (prof_.on) prof_.bytes[K_BUCKET] += 8.0 * (double)N;
         sizes[p.layers++] = N;
         const HashLayer next{out, N, tab_[tab_at].as<uint64_t>(), plan.lg_q(), tags_.on()};
         p.total += N;

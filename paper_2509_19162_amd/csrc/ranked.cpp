@@ -277,7 +277,9 @@ void Engine::run_ranked(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
         bool ended = false;
         for (uint32_t i = 0; i < chain && !ended; ++i) {
             if (spec.max_frontier && p.F > spec.max_frontier) break;  // it was not expanded
-            ended = !take_layer(spec, res, host_small_[16 + ((d0 + i + 1) % kRbWindow) * kRbStride], p);
+            const uint64_t N = host_small_[16 + ((d0 + i + 1) % kRbWindow) * kRbStride];
+            if (prof_.on) prof_.bytes[large && !pull ? K_BUCKET : K_STEP] += 8.0 * (double)N;
+            ended = !take_layer(spec, res, N, p);
         }
         if (ended) {
             p.status = CG_OK;
