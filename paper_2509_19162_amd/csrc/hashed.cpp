@@ -361,7 +361,8 @@ bool Engine::run_hashed(const JobSpec &spec, cg_result_t *res, uint64_t key0, Pr
             const double e = kExpectSlack * (double)p.F * (double)p.F / (double)p.np + 4096.0;
             if (e < (double)expect) expect = (uint64_t)e;
         }
-        expect = std::max<uint64_t>(expect, 1);
+        // (CG_EXPECT_FACTOR: times that, for tests of layers larger than expected)
+        expect = std::max<uint64_t>((uint64_t)((double)expect * plan_factor("CG_EXPECT_FACTOR")), 1);
         const uint64_t most = p.np + p.F + std::min(C, room);
         const bool all_tags = cur.tagged && tags_.all;
         const uint64_t states = std::max(states_try, (all_tags ? 0 : p.np) + p.F + expect);

@@ -148,6 +148,10 @@ struct DevBuf {
     T *as() const { return static_cast<T *>(p); }
 };
 
+// The factor in environment variable `name` (1 if it is not set), by which
+// tests make a plan expect less than it should.
+double plan_factor(const char *name);
+
 // cg_memory_stats: bytes held by the library's device buffers now and at
 // most since the last reset, and the arenas' reserved size.
 void memory_stats(cg_memory_stats_t *out, bool reset_peak);

@@ -13,6 +13,7 @@
 #include <cstdint>
 
 #include "device_util.h"
+#include "internal.h"
 
 namespace cg {
 
@@ -169,8 +170,9 @@ __device__ __forceinline__ void part_end(PartLds<K> &L, uint32_t lg, const PartS
 // Keys a part has to hold when `mean` are expected: every state may come up
 // to k times, so the variance is up to k times that of a uniform draw; seven
 // deviations, and a few whole states' copies for parts that expect next to
-// nothing.
+// nothing. (CG_PART_FACTOR: times that, for tests of parts that overrun.)
 inline uint32_t part_cap(double mean, uint32_t k) {
+    mean *= plan_factor("CG_PART_FACTOR");
     const double c = mean + 7.0 * __builtin_sqrt((double)k * mean) + 4.0 * (double)k + 48.0;
     return ((uint32_t)c + 32) / 32 * 32;
 }

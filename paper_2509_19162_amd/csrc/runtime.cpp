@@ -264,6 +264,11 @@ size_t device_bytes_available() {
     return under_limit(largest);
 }
 
+double plan_factor(const char *name) {
+    const char *e = std::getenv(name);
+    return e ? std::atof(e) : 1.0;
+}
+
 void memory_stats(cg_memory_stats_t *out, bool reset_peak) {
     out->held_bytes = g_held.load();
     out->peak_held_bytes = g_peak_held.load();

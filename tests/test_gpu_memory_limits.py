@@ -104,3 +104,12 @@ def test_batches_of_n_10_with_few_slots(mib, monkeypatch):
         assert [(r.status, r.sizes, r.states_expanded) for r in got] == [(r.status, r.sizes, r.states_expanded) for r in ref]
     monkeypatch.delenv("CG_DEVICE_BYTES")
     assert [r.sizes for r in api.growth_batch(jobs)] == [r.sizes for r in ref]
+
+
+@pytest.mark.parametrize("mib", [24, 64, 200])
+def test_bitmask_engine_without_room_for_lists(mib, monkeypatch):
+    """Three bitmaps of 5 MB, lists of some 90 MB where they fit."""
+    gens = I.random_perms_with_inverses(11, 2, I.rng_for(1, seed=51))
+    ref = api.growth_ex(11, gens, max_layers=256)
+    monkeypatch.setenv("CG_DEVICE_BYTES", str(api.memory_stats()["held_bytes"] + (mib << 20)))
+    _same(api.growth_ex(11, gens, max_layers=256, bitmask=True), ref)
