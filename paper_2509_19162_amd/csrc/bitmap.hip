@@ -112,8 +112,10 @@ WgSlots wg_slots(uint64_t words, uint32_t jobs, uint32_t blocks) {
 }
 
 // ---- states of n <= 8 ------------------------------------------------------------
-// A state is eight bytes, entry i in byte i (of fewer than eight entries the
-// rest stay in place: S_n as a subgroup of S_8, ranks in S_8). A generator is
+// A state is eight bytes, entry i in byte i (fewer than eight entries are the
+// last ones, above others that stay in place: S_n as a subgroup of S_8, whose
+// ranks are the first n!; with the others past them, S_n's ranks lay spread
+// over all 40320, and S_5 by LRX took 131 us, now 35). A generator is
 // two byte permutes. The rank is that of the first four entries times 24 plus
 // the order among the last four: two table lookups, each at the 12-bit number
 // made of four 3-bit entries; the way back is two lookups and one byte
@@ -269,19 +271,18 @@ struct WgLayers {
 // one state each however the bits lie. Either every state of the layer forms
 // its neighbours, and those not seen are set in `nxt`; or, when few states
 // are left, every unseen state looks for a seen predecessor and is set in
-// `nxt` at the first (the wave owns its word). `whole`: the bitmap holds no
-// bits of states outside S_n (then, and only then, unseen bits may be taken
-// from it).
+// `nxt` at the first (the wave owns its word). Bits of no state, in the last
+// word, are marked as seen.
 // The chain of a neighbour (two or three lookups, the test) times the layers
 // bounds it, so all lanes have to be busy: one growth of S_8 by its Coxeter
 // set is 94 us (29 layers; the call takes 160 us, and 440 when each lane
 // looped over a word's bits and computed ranks), 1024 growths of S_9 6.9 ms.
 template <class C>
-__device__ __forceinline__ void wg_run(const WgJobDev &J, const C &codec, uint32_t W, uint64_t states, bool whole,
-                                       uint32_t *vis, uint32_t *cur, uint32_t *nxt, uint16_t *list, uint32_t *fresh,
-                                       uint64_t *__restrict__ sizes, WgOutDev *__restrict__ out, uint32_t *s_acc) {
+__device__ __forceinline__ void wg_run(const WgJobDev &J, const C &codec, uint32_t states, uint32_t *vis, uint32_t *cur,
+                                       uint32_t *nxt, uint16_t *list, uint32_t *fresh, uint64_t *__restrict__ sizes,
+                                       WgOutDev *__restrict__ out, uint32_t *s_acc) {
     const uint32_t tid = threadIdx.x, nt = blockDim.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const uint32_t waves = nt / kWave;
+    const uint32_t waves = nt / kWave, W = (states + 31u) / 32u;
     const uint32_t k = J.k;
     for (uint32_t w = tid; w < W; w += nt) {
         vis[w] = 0u;
@@ -293,14 +294,15 @@ __device__ __forceinline__ void wg_run(const WgJobDev &J, const C &codec, uint32
     __syncthreads();
     if (tid == 0) {
         const uint32_t r = J.start_rank;
-        vis[r >> 5] = 1u << (r & 31u);
+        if (states % 32u) vis[W - 1] = ~0u << (states % 32u);
+        vis[r >> 5] |= 1u << (r & 31u);
         cur[r >> 5] = 1u << (r & 31u);
         sizes[0] = 1;
     }
     __syncthreads();
     WgLayers L;
     while (!L.done(J)) {
-        const bool pull = whole && pull_is_less(states - L.seen, L.F, L.before, k);
+        const bool pull = pull_is_less(states - L.seen, L.F, L.before, k);
         for (uint32_t c = wave; c * kWgChunk < W; c += waves) {
             if (pull) {
                 wg_pull(codec, k, vis, c, W, list, fresh);
@@ -634,13 +636,15 @@ __global__ __launch_bounds__(kWgMaxBlock) __attribute__((amdgpu_waves_per_eu(kBi
                 built = true;
                 for (uint32_t i = threadIdx.x; i < 2 * J.k * 8u; i += blockDim.x)
                     (&sm.sel[0].sel[0])[i] = (&gens[0].sel[0])[i];
-                wg_run(J, Wg8{sm.tables, sm.sel}, W, factorial(8), J.n == 8, sm.bits, sm.bits + W, sm.bits + 2 * W, list,
-                       fresh, sz, out, &s_acc);
+                uint32_t states = 1;
+                for (uint32_t i = 2; i <= J.n; ++i) states *= i;
+                wg_run(J, Wg8{sm.tables, sm.sel}, states, sm.bits, sm.bits + W, sm.bits + 2 * W, list, fresh, sz, out,
+                       &s_acc);
             } else if constexpr (kBig) {
                 uint32_t *bits = reinterpret_cast<uint32_t *>(s_area);
                 if (q == 1) {
                     constexpr uint32_t W = wg_words(9);
-                    wg_run(J, WgN<9>{gens}, W, factorial(9), true, bits, bits + W, bits + 2 * W, list, fresh, sz, out,
+                    wg_run(J, WgN<9>{gens}, (uint32_t)factorial(9), bits, bits + W, bits + 2 * W, list, fresh, sz, out,
                            &s_acc);
                 } else {
                     uint32_t *slot = a.gbits + (uint64_t)blockIdx.x * a.slot_words;
@@ -1209,13 +1213,14 @@ struct WgTables {
 // byte selectors of the eight-byte states, else the nibble selectors.
 GenSel wg_gensel(const JobSpec &s, int g, bool inverse) {
     const uint8_t *row = s.gens.data() + (size_t)g * s.n;
+    const int low = std::max(0, 8 - s.n);  // entries that stay in place
     uint8_t r[16];
     for (int i = 0; i < 16; ++i) r[i] = (uint8_t)i;
     for (int i = 0; i < s.n; ++i) {
         if (inverse)
-            r[row[i]] = (uint8_t)i;
+            r[low + row[i]] = (uint8_t)(low + i);
         else
-            r[i] = row[i];
+            r[low + i] = (uint8_t)(low + row[i]);
     }
     if (s.n > 8) return make_gensel(s.n, r);
     GenSel v{};
@@ -1247,10 +1252,10 @@ WgTables wg_tables(const std::vector<WgItem> &items) {
         d.n = (uint32_t)s.n;
         d.k = (uint32_t)s.k;
         d.goff = (uint32_t)T.gsel.size();
-        // up to n = 8 the states are those of S_8 that fix the entries past n
-        const int m = std::max(s.n, 8);
+        // up to n = 8 the states are those of S_8 that fix the first 8 - n
+        const int m = std::max(s.n, 8), low = m - s.n;
         uint64_t key = 0;
-        for (int q = 0; q < m; ++q) key |= (uint64_t)(q < s.n ? s.start[q] : q) << (4 * (m - 1 - q));
+        for (int q = 0; q < m; ++q) key |= (uint64_t)(q < low ? q : low + s.start[q - low]) << (4 * (m - 1 - q));
         d.start_rank = (uint32_t)host_rank64(key, m);
         d.max_layers = (uint32_t)s.max_layers;
         d.pad = 0;
