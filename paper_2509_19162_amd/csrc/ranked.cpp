@@ -70,8 +70,8 @@ bool rank_layers(const JobSpec &spec) {
     return !std::getenv("CG_CHUNK_CANDIDATES") && !std::getenv("CG_RANK_FULL");
 }
 
-// Reads the states of every layer back, in order: layers are sorted first,
-// in place (small ones all in one launch).
+// Reads the states of every layer back, in order: layers are sorted first
+// (small ones all in one launch, in place).
 void Engine::export_ranked(const JobSpec &spec, const uint64_t *sizes, int layers) {
     uint64_t off = 0, written = 0;
     uint64_t *all = arena_.as<uint64_t>();
@@ -87,8 +87,18 @@ void Engine::export_ranked(const JobSpec &spec, const uint64_t *sizes, int layer
         } else {
             run = sizes[d];
             e = d + 1;
-            order_[0].ensure(run * 8);
-            export_layer(spec, sort_keys(spec, all + off, order_[0].as<uint64_t>(), run), run, written);
+            const uint64_t *sorted;
+            try {
+                sorted = sorted_copy(spec, all + off, run, order_[0], order_[1]);
+            } catch (const Error &e) {
+                // one copy less, where the layer lies (not on whole lines:
+                // 0.1 ms more for 3e6 states)
+                if (e.code != CG_E_NOMEM) throw;
+                order_[1].release();
+                order_[0].ensure(run * 8);
+                sorted = sort_keys(spec, all + off, order_[0].as<uint64_t>(), run);
+            }
+            export_layer(spec, sorted, run, written);
         }
         off += run;
         d = e;
