@@ -44,13 +44,12 @@ bool takes_whole(const JobSpec &spec) {
 
 }  // namespace
 
-// The layer array (while it grows: the old one beside the new), the bitmaps,
-// the partition at every frontier size, one layer's copy and rows to read
-// states back.
+// The layer array (while it grows: the old one beside the new), the bitmaps and
+// the partition at every frontier size. (Queued jobs read no layers back.)
 uint64_t rank_layers_bytes(const JobSpec &spec) {
     const uint64_t orbit = spec.orbit_bound, k = (uint64_t)std::max(1, spec.k), most = most_states(spec);
     const uint64_t fmax = spec.max_frontier ? std::min(orbit, spec.max_frontier) : orbit;
-    const uint64_t layer = std::min(most, k * fmax), room = most + kSmallStates;
+    const uint64_t room = most + kSmallStates;
     uint64_t b = 8 * room;
     if (spec.n > 10) b += takes_whole(spec) ? 8 * (kRbFirstStates + kSmallStates) : 8 * room;
     b += (spec.n >= kRbLargeMinN ? 2 : 1) * 4 * rb_bitmap_words(spec.n);
@@ -60,7 +59,6 @@ uint64_t rank_layers_bytes(const JobSpec &spec) {
         parts = std::max(parts, p.bytes() + 4 * p.parts());
     }
     b += parts + parts / 2;
-    if (spec.layers_out) b += 8 * layer + 2 * (uint64_t)spec.n * std::min(layer, spec.layers_out_cap);
     return b + (64ull << 20);
 }
 
