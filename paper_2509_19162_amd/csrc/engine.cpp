@@ -39,7 +39,7 @@ JobSpec canonicalize(const cg_job_t &job, bool batch) {
     if (s.binary && !(job.flags & CG_START_STATE))
         throw Error(CG_E_INVAL, "binary states (n > 16 or CG_BINARY_STATE) need CG_START_STATE and a 0/1 start vector");
     if (s.binary && (job.flags & (CG_BITMASK | CG_SMALL_JOB)))
-        throw Error(CG_E_INVAL, "binary states take neither the bitmask nor the one-workgroup engine");
+        throw Error(CG_E_INVAL, "binary states take the hash buckets or the sort path, not the bitmask or one-workgroup engine");
     if (s.binary && batch) throw Error(CG_E_UNSUPPORTED, "batches and the serving queue use 4-bit states (n <= 16)");
     if (!job.gens || job.n_gens < 1) throw Error(CG_E_INVAL, "need at least one generator row");
     if (job.max_layers < 1) throw Error(CG_E_INVAL, "max_layers must be >= 1");
