@@ -273,10 +273,12 @@ struct WgLayers {
 // are left, every unseen state looks for a seen predecessor and is set in
 // `nxt` at the first (the wave owns its word). Bits of no state, in the last
 // word, are marked as seen.
-// The chain of a neighbour (two or three lookups, the test) times the layers
-// bounds it, so all lanes have to be busy: one growth of S_8 by its Coxeter
-// set is 94 us (29 layers; the call takes 160 us, and 440 when each lane
-// looped over a word's bits and computed ranks), 1024 growths of S_9 6.9 ms.
+// A job alone is bound by what its one CU issues: S_8 by three random
+// permutations and their inverses (10 layers, 242,000 neighbours) is 94 us,
+// VALU busy for 0.52 of the CU's cycles, LDS for 0.37 (39% of that in
+// conflicts); the call takes 154 us, and 440 when each lane looped over a
+// word's bits and computed ranks. A small layer is its passes and barriers,
+// 10 us (S_8 Coxeter, 29 layers: 300 us). 1024 growths of S_9 take 6.9 ms.
 template <class C>
 __device__ __forceinline__ void wg_run(const WgJobDev &J, const C &codec, uint32_t states, uint32_t *vis, uint32_t *cur,
                                        uint32_t *nxt, uint16_t *list, uint32_t *fresh, uint64_t *__restrict__ sizes,
